@@ -64,9 +64,12 @@ __device__ inline HermiteBasis hermite_basis(double w) {
 #pragma clang fp contract(off)
     const double w2 = w * w, w3 = w2 * w;
     HermiteBasis b;
-    b.h00 = (2.0 * w3 - 3.0 * w2) + 1.0;
-    b.h10 = (w3 - 2.0 * w2) + w;
-    b.h01 = 3.0 * w2 - 2.0 * w3;
+    // h00 = (2 w3 - 3 w2) + 1, h10 = (w3 - 2 w2) + w, h01 = 3 w2 - 2 w3: doubling
+    // is exact, so a fused multiply-add by 2 rounds once where the written rule
+    // rounds once, and 2 w3 - 3 w2 is -h01 to the bit
+    b.h01 = fma(-2.0, w3, 3.0 * w2);
+    b.h00 = 1.0 - b.h01;
+    b.h10 = fma(-2.0, w2, w3) + w;
     b.h11 = w3 - w2;
     return b;
 }
@@ -125,9 +128,8 @@ __device__ inline bool interp_1d(const F &get, long long i0, double w0, int n, d
     return interp_1d_values<Interp>(tm, ta, tb, tp, i0, w0, hb, n, next);
 }
 
-// The start of a range of slices: y0 (a range from slice 0 also resets the
-// running status and writes lambda_0) or the state the previous range carried
-// over.  Returns false when an earlier range already failed.  Everything the
+// The start of a range of slices: y0 (a range from slice 0 also writes
+// lambda_0) or the state the previous range carried over.  Returns false when an earlier range already failed.  Everything the
 // next range needs stays in device memory; the boundary states and the final
 // status may live in host-mapped memory, which the chain only writes.
 template <int D>
@@ -138,9 +140,6 @@ __device__ inline bool range_begin(const ComposeArgs &a, int lane, double &l0, d
         if (lane == 0) {
             a.boundary[0] = l0;
             if (D == 2) a.boundary[1] = l1;
-            a.status->n_out_of_grid = 0;
-            a.status->bad_slice = -1;
-            a.status->done = 0;
         }
         return true;
     }
@@ -150,16 +149,17 @@ __device__ inline bool range_begin(const ComposeArgs &a, int lane, double &l0, d
     return true;
 }
 
-// The end of a range: the running status, the carried state and, when the
-// chain ends here, a copy of the final status whose done flag is written last.
+// The end of a range: the running status (a range from slice 0 starts it, and
+// so reads nothing back from memory), the carried state and, when the chain
+// ends here, a copy of the final status whose done flag is written last.
 __device__ inline void range_end(const ComposeArgs &a, int lane, double l0, double l1,
                                  long long oog, int bad_slice) {
     if (lane != 0) return;
-    const long long total = a.status->n_out_of_grid + oog;
-    a.status->n_out_of_grid = total;
-    if (bad_slice >= 0) a.status->bad_slice = bad_slice;
+    const long long total = (a.j_begin == 0 ? 0 : a.status->n_out_of_grid) + oog;
     const bool last = a.j_end == a.n_slices || bad_slice >= 0;
-    if (last) a.status->done = 1;
+    a.status->n_out_of_grid = total;
+    a.status->bad_slice = bad_slice;
+    a.status->done = last ? 1 : 0;
     if (a.carry) {
         a.carry[0] = l0;
         a.carry[1] = l1;
@@ -263,41 +263,93 @@ __device__ inline void compose_range(const ComposeArgs &a, double *final_out = n
     }
 }
 
-// The 1-D chain with its table windows staged ahead in LDS.  Each slice's
-// table read depends on the state the previous slice produced, so its latency
-// is on the chain's path.  Helper waves therefore fetch, for each coming
-// slice s, a window of kPfWin consecutive values of row s around the cell the
-// chain is predicted to need (the chain's latest cell, moved on at its latest
-// rate per slice), once the chain is within kPfAhead slices of s, into a ring
-// of kPfSlots LDS slots; the chain then pays an LDS read instead of a global
-// one.  The chain takes a slice's values from its slot when the slot holds
-// that slice and every value the interpolant reads, and from global memory
-// otherwise; it never waits for a helper, so the values it uses, and the
-// result, are the same either way.  A helper waits only for the chain's
-// progress, and gives up after a bounded number of polls.  What remains per
-// slice is the issue of the chain's own instructions by its one wave (the
-// cell, the weights, the interpolant, the checks), which is why the loop
-// keeps them few: one branch between the LDS and the global reads, central
-// slopes only on the LDS path, 32-bit offsets.
-constexpr int kPfHelpers = 8;      // helper waves
-constexpr int kPfSlots = 16;       // staged windows
-constexpr int kPfWin = 256;        // table values per window
-constexpr int kPfAhead = 8;        // a window is fetched this many slices ahead
+// The 1-D chain with its table rows staged ahead in LDS.  Each slice's table
+// read depends on the state the previous slice produced, so a global read
+// would put its whole latency (0.3 us from L2, about 1 us from memory) on the
+// chain's path.  Helper waves therefore stage each coming slice's values in a
+// ring of LDS slots, as they lie in the table, and write the slot's tag after
+// them:
+//   rows     of less than kPfRowBytes (value and slope row together) whole, as
+//            soon as the slot is free.  Nothing is predicted, so problems
+//            whose state crosses many cells per slice are served as well as
+//            smooth ones.
+//   windows  of longer rows, around the cell the chain is predicted to need,
+//            once the chain is within kPfAhead slices.
+// The line lies at 12 KB because one CU fetches about 43 GB/s this way: a row
+// of 12 KB takes 0.28 us, still less than the general path, whose reads also
+// queue behind the helpers' (0.36 us per slice; rows of 16 KB took 0.40 us).
+// The chain takes a slice from its slot when the slot holds that slice and
+// every node the interpolant reads, and from global memory otherwise, so the
+// values it uses, and the result, are the same either way.
+//
+// What bounds it: one wave, which issues an instruction every ~5 clocks, and
+// the latency of the dependent operations, one LDS read among them.  The loop
+// therefore keeps little but the lookup and the interpolant: slices are taken
+// in groups of four without a branch; the state stays in vector registers;
+// the cell is floor(u) itself, and a lookup outside the grid or the slot (the
+// one unsigned comparison) is noticed after the group, which is then taken
+// again slice by slice; no value is tested for finiteness inside a block of 64
+// slices, and the helpers are told of the progress once per group.  A state
+// that is not finite stays so (every interpolant turns an infinite or NaN
+// coordinate into one), so it is found at the end of its block at the latest,
+// and the block is then taken again by the general path, which finds the slice
+// that failed.  Measured per slice (before: one slice at a time, windows of 256
+// nodes only, every value tested): 4096 slices of 4096 FP32 nodes, cubic
+// Hermite, windows 0.33 -> 0.18 us; of 1000 nodes, linear, rows 0.27 -> 0.13 us;
+// 301 slices of 1501 nodes with slopes, rows of 12 KB, 0.37 -> 0.25 us; 1024
+// slices of 8192 nodes whose cells cannot be predicted, 0.43 -> 0.41 us.
+constexpr int kPfHelpers = 8;              // helper waves
+constexpr int kPfThreads = 64 * (1 + kPfHelpers);
+constexpr int kPfMaxSlots = 32;            // slots of the ring, at most
+constexpr int kPfRingBytes = 152 * 1024;
+constexpr int kPfRowBytes = 12 * 1024;     // rows shorter than this are staged whole
+constexpr int kPfWinBytes = 4 * 1024;      // a window's slot
+constexpr int kPfWin = 256;                // nodes of the narrowest window
+constexpr int kPfAhead = 14;               // a window is fetched this many slices ahead
+constexpr int kPfPair = 2;                 // slices a helper stages in one turn
+constexpr int kPfLead = 12;                // a windowed chain's first slices are not staged, and
+constexpr int kPfSeen = 8;                 // this many of them are finished before later ones are
+constexpr int kPfPolls = 24;               // polls the chain waits for a group's slots
+constexpr int kPfPublish = 4;              // slices between two progress reports
 constexpr int kPfSpinMax = 1 << 20;
 
-// C = 2 for cubic Hermite with stored slopes: a slot holds the window of the
-// value row (component 0) and the same window of the slope row (component 1).
-template <int C>
-struct PfSharedC {
-    double win[C][kPfSlots][kPfWin];
-    long long tag[kPfSlots];       // (slice << 32) | first cell of the window; -1 empty
-    long long hist[2];             // (slice << 32) | cell, of the last two slices the chain
-                                   // finished (slice j in hist[j & 1])
-    int done;                      // the chain has ended
+// What a slot holds: nodes base .. of slice `slice` (-1: nothing yet), enough
+// for the interpolant at `cells` consecutive cells, the first of them `shift`
+// values from the slot's start.
+typedef int PfTag __attribute__((ext_vector_type(4)));      // slice, base, cells, shift
+typedef __attribute__((address_space(3))) volatile PfTag PfLdsTag;
+
+struct PfShared {
+    alignas(16) unsigned char ring[kPfRingBytes + 64];
+    PfTag tag[kPfMaxSlots];
+    // the chain's reports, written by its whole wave without a branch: lane 0's
+    // words are the report, the other lanes' (from index 4 and 1 on) are not read
+    long long hist[4 + 64];        // (slice << 32) | cell of the last reports, the report of
+                                   // slice j in hist[(j / kPfPublish) % 4]
+    int past[64];                  // past[0]: every slice before this one is finished (the
+                                   // largest integer once the chain has ended)
 };
 
-template <int Interp>
-using PfShared = PfSharedC<Interp == 4 ? 2 : 1>;
+// The ring's layout for a table of n nodes of type T per row and C rows per slice.
+template <class T, int C>
+struct PfLayout {
+    bool rows;                     // whole rows (else windows)
+    int width;                     // nodes per slot and component, at most
+    int slots;
+    int row_bytes, slot_bytes;     // of a component in a slot, and of a slot
+    int ahead;                     // slices before a slot's own at which it is fetched
+    __device__ explicit PfLayout(int n) {
+        rows = (long long)n * C * int(sizeof(T)) < kPfRowBytes;
+        width = rows ? n : kPfWinBytes / (C * int(sizeof(T))) - 8;
+        row_bytes = (width * int(sizeof(T)) + 15 + 15) & ~15;
+        slot_bytes = C * row_bytes;
+        slots = kPfRingBytes / slot_bytes;
+        slots = slots < kPfMaxSlots ? slots : kPfMaxSlots;
+        // a slot is free once the slice `slots` before has been finished;
+        // windows wait longer, for the prediction's sake
+        ahead = rows || slots <= kPfAhead ? slots - 1 : kPfAhead;
+    }
+};
 
 // The value of the wave's first active lane, held in scalar registers.  The
 // chain computes the same values in every lane; taking them from one lane
@@ -329,205 +381,402 @@ __device__ inline long long pf_pack(int hi, long long lo) {
     return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-template <class T, int Interp>
-__device__ inline void pf_chain(const ComposeArgs &a, PfShared<Interp> &sh) {
-#pragma clang fp contract(off)
-    const int lane = int(threadIdx.x) & 63;
-    const T *tab0 = static_cast<const T *>(a.tab0);
-    const T *tab1 = static_cast<const T *>(a.tab1);
-    const int n = a.n0;
-    double lam = 0.0, unused = 0.0;
-    if (!range_begin<1>(a, lane, lam, unused)) return;    // an earlier range already failed
-    int oog = 0;
-    int bad_slice = -1;
-    double keep = 0.0;
-    int jb = a.j_begin;
-    int j = a.j_begin;
-    // nodes the interpolant reads: i0-1 .. i0+2 (Hermite on differences) or
-    // i0 .. i0+1 (linear, Hermite on stored slopes)
-    constexpr int kBelow = Interp == 1 ? 1 : 0, kSpan = Interp == 1 ? 4 : 2;
-    // A state that is not finite fails the slice that starts from it.  Inside
-    // the loop one test of the interpolated value stands for both checks: an
-    // entry that is not finite (or a slope formed from one) makes the value
-    // not finite (a product with zero gives NaN), so a finite value has finite
-    // entries and is itself the next slice's finite start.  The loop leaves
-    // at the first value that is not finite, and the code after it tells the
-    // two cases apart.
-    double next = 0.0;
-    bool ok = true;
-    if (j < a.j_end && !finite(lam)) {
-        bad_slice = j;
-    } else {
-        for (; j < a.j_end; ++j) {
-            // the slot's tag, read while the cell is located; the window's
-            // values are read after it, at addresses that depend on it
-            const unsigned slot = unsigned(j) % kPfSlots;
-            const long long tg = uniform_i64(__hip_atomic_load(
-                &sh.tag[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            // the slot's slice and first cell (-1 and -1 for an empty slot)
-            const int tag_slice = int(tg >> 32), base = int(tg & 0xffffffffLL);
-            const double *win = sh.win[0][slot];
-            long long i0;
-            double w0;
-            oog += locate(a.lo0, a.inv0, n, lam, i0, w0);
-            const int i = int(i0);
-            // a hit needs nodes i-kBelow .. i-kBelow+kSpan-1 inside the window
-            // and, for the Hermite form on differences, a cell away from the
-            // row's ends (1 <= i <= n-3), where both slopes are central; every
-            // other case reads global memory
-            const unsigned o = unsigned(i - kBelow - base);
-            const bool hit = tag_slice == j && o <= unsigned(kPfWin - kSpan) &&
-                             (Interp != 1 || i <= n - 3);
-            if (hit) {
-                // offsets into the slot; atomic reads keep them LDS reads (a
-                // pointer chosen between LDS and global memory would make them
-                // flat loads)
-                if constexpr (Interp == 1) {
-                    const double tm = pf_read(win, o), ta = pf_read(win, o + 1);
-                    const double tb = pf_read(win, o + 2), tp = pf_read(win, o + 3);
-                    // the weights do not depend on the table: formed while the
-                    // reads are in flight (the empty asm keeps them there)
-                    HermiteBasis hb = hermite_basis(w0);
-                    asm volatile("" : "+v"(hb.h00), "+v"(hb.h10), "+v"(hb.h01), "+v"(hb.h11));
-                    const double da = 0.5 * (tb - tm), db = 0.5 * (tp - ta);
-                    next = ((hb.h00 * ta + hb.h10 * da) + hb.h01 * tb) + hb.h11 * db;
-                    ok = all_finite(ta, tb, da, db);
-                } else if constexpr (Interp == 4) {
-                    const double *win1 = sh.win[Interp == 4 ? 1 : 0][slot];
-                    const double ta = pf_read(win, o), tb = pf_read(win, o + 1);
-                    const double ma = pf_read(win1, o), mb = pf_read(win1, o + 1);
-                    HermiteBasis hb = hermite_basis(w0);
-                    asm volatile("" : "+v"(hb.h00), "+v"(hb.h10), "+v"(hb.h01), "+v"(hb.h11));
-                    ok = hermite_slopes_values(ta, tb, ma, mb, a.dxi0, hb, next);
-                } else {
-                    const double ta = pf_read(win, o), tb = pf_read(win, o + 1);
-                    next = ta + w0 * (tb - ta);
-                    ok = all_finite(ta, tb);
-                }
-            } else if constexpr (Interp == 4) {
-                const T *row0 = tab0 + (long long)j * a.M, *row1 = tab1 + (long long)j * a.M;
-                const double ta = double(row0[i0]), tb = double(row0[i0 + 1]);
-                const double ma = double(row1[i0]), mb = double(row1[i0 + 1]);
-                ok = hermite_slopes_values(ta, tb, ma, mb, a.dxi0, hermite_basis(w0), next);
-            } else {
-                const T *row = tab0 + (long long)j * a.M;
-                ok = interp_1d<Interp>([row](long long k) { return double(row[k]); }, i0, w0,
-                                       n, next);
-            }
-            asm volatile("" : "+v"(next));   // formed before the branch, not after it
-            next = uniform_f64(next);
-            if (!finite(next)) break;
-            lam = next;
-            // slice j is done.  Its slot is reused for slice j + kPfSlots, which
-            // no helper fetches before the chain is past slice j + kPfSlots -
-            // kPfAhead.
-            if (lane == 0)
-                __hip_atomic_store(&sh.hist[j & 1], pf_pack(j, i0), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (lane == j - jb) keep = lam;
-            if (j - jb == 63) {
-                a.boundary[jb + lane + 1] = keep;
-                jb += 64;
-            }
-        }
-        if (j < a.j_end) {               // slice j gave a value that is not finite
-            if (!uniform_bool(ok)) {     // from an entry that is not finite: j fails
-                bad_slice = j;
-            } else {                     // a state that is not finite: j + 1 fails
-                lam = next;
-                if (lane == j - jb) keep = lam;
-                if (j - jb == 63) {
-                    a.boundary[jb + lane + 1] = keep;
-                    jb += 64;
-                }
-                ++j;
-                if (j < a.j_end) bad_slice = j;
-            }
-        }
-    }
-    if (lane < j - jb) a.boundary[jb + lane + 1] = keep;
-    range_end(a, lane, lam, 0.0, oog, bad_slice);
+// A slot number past the ring's last, wrapped (x < 2 slots): x - slots wraps to
+// a large unsigned number when x is a slot already.
+__device__ inline unsigned pf_wrap(unsigned x, unsigned slots) {
+    const unsigned y = x - slots;
+    return x < y ? x : y;
 }
 
-// Helper wave r (1..kPfHelpers) stages slices j_begin + r, j_begin + r + kPfHelpers, ...
-template <class T, int C>
-__device__ inline void pf_helper(const ComposeArgs &a, PfSharedC<C> &sh, int r) {
+// A slot's tag in one 16-byte read, so that its fields belong together.
+__device__ inline PfTag pf_tag(const PfTag *tag, unsigned slot) {
+    return *(const PfLdsTag *)(tag + slot);
+}
+
+// Slice j from state lam by the general path: the lookup with its clamping and
+// counting, the entries from global memory, each tested.  Returns false, and
+// leaves lam, when the slice fails: lam or an entry (or a slope) is not finite.
+template <class T, int Interp>
+__device__ inline bool slice_general(const ComposeArgs &a, int j, double &lam, long long &cell,
+                                     int &oog) {
+#pragma clang fp contract(off)
+    lam = uniform_f64(lam);
+    cell = 0;
+    if (!finite(lam)) return false;
+    double w0, next;
+    oog += locate(a.lo0, a.inv0, a.n0, lam, cell, w0);
+    const T *row = static_cast<const T *>(a.tab0) + (long long)j * a.M;
+    bool ok;
+    if constexpr (Interp == 4) {
+        const T *row1 = static_cast<const T *>(a.tab1) + (long long)j * a.M;
+        const double ta = double(row[cell]), tb = double(row[cell + 1]);
+        const double ma = double(row1[cell]), mb = double(row1[cell + 1]);
+        ok = hermite_slopes_values(ta, tb, ma, mb, a.dxi0, hermite_basis(w0), next);
+    } else {
+        ok = interp_1d<Interp>([row](long long k) { return double(row[k]); }, cell, w0, a.n0,
+                               next);
+    }
+    if (__builtin_amdgcn_ballot_w64(!ok) != 0) return false;
+    lam = next;
+    return true;
+}
+
+// Waits, a bounded number of polls, until the slot holds slice j.
+__device__ inline bool pf_wait(const PfTag *tag, unsigned slot, int j) {
+    for (int spin = 0; spin < 4096; ++spin) {
+        if (__builtin_amdgcn_readfirstlane(pf_tag(tag, slot).x) == j) return true;
+    }
+    return false;
+}
+
+// Nodes the interpolant reads below the cell, and in all: i-1 .. i+2 (Hermite
+// on differences, whose slopes are the central ones for every cell that has
+// these nodes) or i .. i+1.
+template <int Interp>
+struct PfNodes {
+    static constexpr int below = Interp == 1 ? 1 : 0, span = Interp == 1 ? 4 : 2;
+};
+
+// A tag's fields in scalar registers.
+struct PfFields {
+    int base;
+    unsigned cells, shift;
+    __device__ PfFields(const PfTag &t, int lane)
+        : base(__builtin_amdgcn_readlane(t.y, lane)),
+          cells(unsigned(__builtin_amdgcn_readlane(t.z, lane))),
+          shift(unsigned(__builtin_amdgcn_readlane(t.w, lane))) {}
+};
+
+// One slice from state lam out of a slot that holds the nodes of tag.cells
+// cells from node tag.base on.  next is the new state when lam's cell is one of them
+// (the result, the same in every lane); otherwise a value that means nothing
+// is formed from what the ring holds at the first cell past them.
+template <class T, int Interp>
+__device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_bytes,
+                                const ComposeArgs &a, double lam, double &next, int &i) {
+#pragma clang fp contract(off)
+    const double u = (lam - a.lo0) * a.inv0;
+    const double fl = floor(u);
+    // the hardware's conversion saturates (and gives 0 for a NaN), where the
+    // language leaves a value outside the integer's range undefined
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(fl));
+    const unsigned at = unsigned(i - PfNodes<Interp>::below - tag.base);
+    const unsigned o = (at < tag.cells ? at : tag.cells) + tag.shift;
+    const double w = u - fl;
+    const T *e = slot + o;
+    if constexpr (Interp == 0) {
+        const double ta = double(e[0]), tb = double(e[1]);
+        next = ta + w * (tb - ta);
+    } else {
+        double ta, tb, da, db;
+        const T e0 = e[0], e1 = e[1];
+        const T *f = Interp == 4 ? e + row_bytes / int(sizeof(T)) : e + 2;
+        const T f0 = f[0], f1 = f[1];
+        // the weights do not depend on the table: formed while the reads are
+        // in flight (the empty asm keeps them there)
+        HermiteBasis hb = hermite_basis(w);
+        asm volatile("" : "+v"(hb.h00), "+v"(hb.h10), "+v"(hb.h01), "+v"(hb.h11));
+        if constexpr (Interp == 4) {
+            ta = double(e0);
+            tb = double(e1);
+            da = a.dxi0 * double(f0);
+            db = a.dxi0 * double(f1);
+        } else {
+            const double tm = double(e0), tp = double(f1);
+            ta = double(e1);
+            tb = double(f0);
+            da = 0.5 * (tb - tm);
+            db = 0.5 * (tp - ta);
+        }
+        next = ((hb.h00 * ta + hb.h10 * da) + hb.h01 * tb) + hb.h11 * db;
+    }
+    return at < tag.cells;
+}
+
+// The chain's progress: slice j finished, in cell `cell`.
+__device__ inline void pf_report(PfShared &sh, int j, long long cell, int lane) {
+    const int q = (j / kPfPublish) & 3;
+    __hip_atomic_store(&sh.hist[lane == 0 ? q : 4 + lane], pf_pack(j, cell), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(&sh.past[lane], j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class T, int Interp>
+__device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
+                                const PfLayout<T, Interp == 4 ? 2 : 1> &lay,
+                                double *final_out) {
     const int lane = int(threadIdx.x) & 63;
-    const T *tab0 = static_cast<const T *>(a.tab0);
-    const T *tab1 = static_cast<const T *>(a.tab1);
+    double lam = 0.0, unused = 0.0;
+    if (!uniform_bool(range_begin<1>(a, lane, lam, unused))) return;  // an earlier range failed
+    constexpr int kGroup = kPfPublish;
+    const unsigned slots = unsigned(lay.slots);
+    unsigned at = 0;                    // slice j's slot: (j - j_begin) modulo the slots
+    const int j_begin = a.j_begin, j_end = a.j_end;
+    const int lq = lane & (kGroup - 1);
+    int oog = 0, bad_slice = -1, backoff = lay.rows ? 0 : kPfLead;
+    int staged_from = lay.rows ? j_begin : j_begin + kPfLead;   // groups are tried from here on
+    int j = j_begin;
+    // the first slot, if its helper delivers it within a bounded number of polls
+    if (lay.rows) pf_wait(sh.tag, 0, j);
+    while (j < j_end && bad_slice < 0) {
+        // one block of up to 64 slices; lane l keeps the state after slice jb + l
+        const int jb = __builtin_amdgcn_readfirstlane(j);
+        const int stop = j_end - jb < 64 ? j_end : jb + 64;
+        const double lam_jb = lam;
+        const int oog_jb = oog;
+        double keep = 0.0;
+        bool failed = false;
+        while (j < stop) {
+            // kGroup slices without a branch, lane l holding the tag of slice
+            // j + l % kGroup; the next group's tags are read half way
+            j = __builtin_amdgcn_readfirstlane(j);
+            at = unsigned(__builtin_amdgcn_readfirstlane(int(at)));
+            PfTag tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
+            while (j >= staged_from && j + kGroup <= stop) {
+                // slots that are about to be filled are waited for, a bounded
+                // number of polls: less than the general path would take
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(tag.x != j + lq) != 0, 0)) {
+                    bool there = false;
+#pragma unroll 1
+                    for (int spin = 0; spin < kPfPolls && !there; ++spin) {
+                        tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
+                        there = __builtin_amdgcn_ballot_w64(tag.x != j + lq) == 0;
+                    }
+                    if (!there) break;
+                }
+                const PfTag now = tag;
+                asm volatile("" ::: "memory");  // the values are read after their tags
+                unsigned long long served = ~0ull;
+                double l = lam;
+                int i = 0;
+#pragma unroll
+                for (int q = 0; q < kGroup; ++q) {
+                    if (q == kGroup / 2)
+                        tag = pf_tag(sh.tag, pf_wrap(at + unsigned(kGroup + lq), slots));
+                    double next;
+                    served &= __builtin_amdgcn_ballot_w64(pf_slice<T, Interp>(
+                        reinterpret_cast<const T *>(sh.ring + pf_wrap(at + unsigned(q), slots) *
+                                                                  unsigned(lay.slot_bytes)),
+                        PfFields(now, q), lay.row_bytes, a, l, next, i));
+                    l = next;
+                    if (lane == j + q - jb) keep = l;
+                }
+                if (__builtin_expect(served == 0, 0)) break;    // the same in every lane
+                lam = l;
+                j += kGroup;
+                backoff = 0;
+                at = pf_wrap(at + kGroup, slots);
+                pf_report(sh, j - 1, i, lane);
+            }
+            // Slices that the slots do not serve, one at a time: those of this
+            // group, each from its slot where that has it after all (a staged
+            // row that is on its way is waited for, a bounded time), then,
+            // when groups fail one after another, a growing number of slices
+            // straight by the general path, so that a problem whose cells
+            // cannot be predicted does not pay for the attempt each time.
+            // Groups that still fail after that send the helpers home: their
+            // copies only delay the chain's own reads.
+            const int end1 = j < staged_from ? j : (stop - j < kGroup ? stop : j + kGroup);
+            const int end2 = stop - end1 < backoff ? stop : end1 + backoff;
+            if (!lay.rows && j >= staged_from && end1 < stop) {
+                if (backoff >= 64) {
+                    staged_from = 0x7fffffff;
+                    sh.past[lane] = 0x7fffffff;
+                }
+                backoff = 2 * backoff + kGroup;
+            }
+            for (; j < end2; ++j, at = pf_wrap(at + 1, slots)) {
+                long long cell = 0;
+                bool done = false;
+                if (j < end1) {
+                    if (lay.rows) pf_wait(sh.tag, at, j);
+                    const PfTag tg = pf_tag(sh.tag, at);
+                    asm volatile("" ::: "memory");
+                    if (__builtin_amdgcn_readfirstlane(tg.x) == j) {
+                        double next;
+                        int i;
+                        done = __builtin_amdgcn_ballot_w64(pf_slice<T, Interp>(
+                                   reinterpret_cast<const T *>(sh.ring +
+                                                               at * unsigned(lay.slot_bytes)),
+                                   PfFields(tg, 0), lay.row_bytes, a, lam, next, i)) != 0;
+                        if (done) {
+                            lam = next;
+                            cell = i;
+                        }
+                    }
+                }
+                if (!done && !slice_general<T, Interp>(a, j, lam, cell, oog)) {
+                    failed = true;
+                    break;
+                }
+                if (lane == j - jb) keep = lam;
+                if (staged_from != 0x7fffffff && ((j - j_begin) & (kPfPublish - 1)) == kPfPublish - 1)
+                    pf_report(sh, j, cell, lane);
+            }
+            if (failed) break;
+        }
+        if (failed || __builtin_amdgcn_ballot_w64(!isfinite(lam)) != 0) {
+            // some slice of the block met a value that is not finite: the block
+            // again by the general path, which tests every state and entry
+            j = jb;
+            lam = lam_jb;
+            oog = oog_jb;
+            for (; j < stop; ++j) {
+                long long cell;
+                if (!slice_general<T, Interp>(a, j, lam, cell, oog)) {
+                    bad_slice = j;
+                    break;
+                }
+                if (lane == j - jb) keep = lam;
+            }
+        }
+        if (lane < j - jb) a.boundary[jb + lane + 1] = keep;
+    }
+    range_end(a, lane, lam, 0.0, oog, bad_slice);
+    if (final_out) final_out[0] = lam;
+}
+
+// Copies `bytes` from global memory to LDS by one wave, 16 bytes per lane with
+// loads that write LDS themselves: no register holds the values, so every
+// load of a helper's turn is in flight at once.  src and dst are 16-byte
+// aligned; up to 15 bytes past the end are copied as well (of the next row or
+// of the padding to 256 bytes that every table ends with).  The caller waits
+// (pf_landed).
+__device__ inline void pf_copy(const char *src, unsigned char *dst, int bytes, int lane) {
+    typedef const __attribute__((address_space(1))) unsigned *Src;
+    typedef __attribute__((address_space(3))) unsigned *Dst;
+    for (int at = 0; at < bytes; at += 1024)
+        if (at + 16 * lane < bytes)
+            __builtin_amdgcn_global_load_lds((Src)(src + at + 16 * lane), (Dst)(dst + at), 16, 0,
+                                             0);
+}
+
+__device__ inline void pf_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Helper wave r (0 .. kPfHelpers-1) stages the pairs of slices j_begin +
+// kPfPair (r + m kPfHelpers), m = 0, 1, ...
+template <class T, int Interp>
+__device__ inline void pf_helper(const ComposeArgs &a, PfShared &sh,
+                                 const PfLayout<T, Interp == 4 ? 2 : 1> &lay, int r) {
+    constexpr int C = Interp == 4 ? 2 : 1, kSpan = PfNodes<Interp>::span;
+    const int lane = int(threadIdx.x) & 63;
     const int n = a.n0;
-    const long long top = n > kPfWin ? n - kPfWin : 0;
-    for (int s = a.j_begin + r; s < a.j_end; s += kPfHelpers) {
-        // wait until the chain is within kPfAhead slices of s
-        long long h0 = 0, h1 = 0;
-        int p = 0;                  // the chain has finished every slice before p
+    const unsigned slots = unsigned(lay.slots);
+    unsigned at = unsigned(kPfPair * r) % slots;       // the slot of s0
+    for (int s0 = a.j_begin + kPfPair * r; s0 < a.j_end; s0 += kPfPair * kPfHelpers,
+             at = (at + unsigned(kPfPair * kPfHelpers)) % slots) {
+        const int pair = s0 + 1 < a.j_end ? 2 : 1;
+        if (!lay.rows && s0 < a.j_begin + kPfLead) continue;
+        int p = 0;                     // the chain has finished every slice before p
         bool go = false;
         for (int spin = 0; spin < kPfSpinMax; ++spin) {
-            if (__hip_atomic_load(&sh.done, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))
-                return;
-            h0 = __hip_atomic_load(&sh.hist[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            h1 = __hip_atomic_load(&sh.hist[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            p = int((h0 >> 32) > (h1 >> 32) ? h0 >> 32 : h1 >> 32) + 1;
-            if (p >= s - kPfAhead) {
+            p = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                &sh.past[0], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+            if (p >= s0 + pair - 1 - lay.ahead && (lay.rows || p >= a.j_begin + kPfSeen)) {
                 go = true;
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        if (!go) return;            // the chain does not depend on the helpers
-        if (p >= s) continue;       // the chain is already at or past slice s
-        // the latest cell, moved on at the latest rate per slice
-        const bool newer0 = (h0 >> 32) >= (h1 >> 32);
-        const long long hn = newer0 ? h0 : h1, ho = newer0 ? h1 : h0;
-        const long long jn = hn >> 32, in = hn & 0xffffffffLL;
-        const long long jo = ho >> 32, io = ho & 0xffffffffLL;
-        const long long rate = jn - jo == 1 ? in - io : 0;
-        long long base = in + rate * ((long long)s - jn) - kPfWin / 2;
-        base = base < 0 ? 0 : (base > top ? top : base);
-        const int slot = s % kPfSlots;
+        if (!go || p == 0x7fffffff) return;     // the chain does not depend on the helpers
+        if (p >= s0 + pair) continue;           // the chain is already past both
+        int base[2] = {0, 0}, width[2] = {n, n};
+        if (!lay.rows) {
+            long long h[4];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const T *row = (c == 0 ? tab0 : tab1) + (long long)s * a.M;
+            for (int q = 0; q < 4; ++q)
+                h[q] = uniform_i64(__hip_atomic_load(&sh.hist[q], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP));
+            int newest = 0;
 #pragma unroll
-            for (int q = 0; q < kPfWin / 64; ++q) {
-                // past the row's end (a row shorter than a window) the last
-                // value is read again; the chain never uses those entries
-                const long long k = base + q * 64 + lane;
-                sh.win[c][slot][q * 64 + lane] = double(row[k < n ? k : n - 1]);
+            for (int q = 1; q < 4; ++q)
+                if (int(h[q] >> 32) > int(h[newest] >> 32)) newest = q;
+            // The reported cells continued to second order, in a window wider
+            // than the narrowest by a share of the second-order term (what the
+            // extrapolation leaves out is of that size at most).  Where that
+            // is more than a slot holds, or the chain went through no three
+            // reports in a row, the slot is tagged as serving no cell.
+            const long long h0 = h[newest], h1 = h[(newest + 3) & 3], h2 = h[(newest + 2) & 3];
+            const int j0 = int(h0 >> 32);
+            const float c0 = float(int(h0 & 0xffffffffLL)), c1 = float(int(h1 & 0xffffffffLL)),
+                        c2 = float(int(h2 & 0xffffffffLL));
+            const bool three = int(h1 >> 32) == j0 - kPfPublish &&
+                               int(h2 >> 32) == j0 - 2 * kPfPublish;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float k = float(s0 + t - j0) * (1.0f / kPfPublish);
+                const float bend = 0.5f * k * (k + 1.0f) * ((c0 - c1) - (c1 - c2));
+                const float half = float(kPfWin / 2) + 0.25f * fabsf(bend);
+                if (!three || 2.0f * half > float(lay.width)) {
+                    width[t] = 0;
+                    continue;
+                }
+                const int w = 2 * __builtin_amdgcn_readfirstlane(int(half));
+                const float from = c0 + k * (c0 - c1) + bend - half;
+                const int b = __builtin_amdgcn_readfirstlane(
+                    int(fminf(fmaxf(from, 0.0f), float(n - w))));
+                width[t] = w;
+                base[t] = b > n - w ? n - w : b;
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0)
-            __hip_atomic_store(&sh.tag[slot], pf_pack(s, base), __ATOMIC_RELEASE,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        // a row starts at any multiple of the value's size: the copy starts at
+        // the 16-byte line below the first node, and the tag says how many
+        // values that is before it
+        int shift[2] = {0, 0};
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (t < pair) {
+                    const unsigned slot = pf_wrap(at + unsigned(t), slots);
+                    const char *row = reinterpret_cast<const char *>(
+                        static_cast<const T *>(c == 0 ? a.tab0 : a.tab1) +
+                        (long long)(s0 + t) * a.M + base[t]);
+                    const int over = int(reinterpret_cast<uintptr_t>(row) & 15);
+                    shift[t] = over / int(sizeof(T));   // the same for both components
+                    pf_copy(row - over, sh.ring + slot * unsigned(lay.slot_bytes) +
+                                            unsigned(c * lay.row_bytes),
+                            over + width[t] * int(sizeof(T)), lane);
+                }
+        pf_landed();
+        // the tags after the values, each in one 16-byte write
+        if (lane < pair) {
+            const int w = lane ? width[1] : width[0];
+            const PfTag t = {s0 + lane, lane ? base[1] : base[0],
+                             w >= kSpan ? w - kSpan + 1 : 0, lane ? shift[1] : shift[0]};
+            *(PfLdsTag *)(&sh.tag[pf_wrap(at + unsigned(lane), slots)]) = t;
+        }
     }
 }
 
 // The whole 1-D composition of a range: wave 0 runs the chain, waves
-// 1..kPfHelpers stage windows for it.
+// 1..kPfHelpers stage rows or windows for it.
 template <class T, int Interp>
-__device__ inline void compose_range_staged(const ComposeArgs &a, PfShared<Interp> &sh) {
-    const int wave = int(threadIdx.x) >> 6;
-    if (threadIdx.x < kPfSlots) sh.tag[threadIdx.x] = -1;
-    if (threadIdx.x == 0) {
-        // the cell of the range's first state seeds the helpers' prediction
+__device__ inline void compose_range_staged(const ComposeArgs &a, PfShared &sh,
+                                            double *final_out = nullptr) {
+    constexpr int C = Interp == 4 ? 2 : 1;
+    const PfLayout<T, C> lay(a.n0);
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    if (threadIdx.x < kPfMaxSlots) sh.tag[threadIdx.x] = PfTag{-1, 0, 0, 0};
+    if (threadIdx.x < 4) {
+        // the cell of the range's first state seeds the helpers' prediction, as
+        // if the chain had just finished slice j_begin - 1 in that cell
         const double l = a.j_begin == 0 ? a.y00 : (a.carry ? a.carry[0] : a.y00);
         long long c;
         double w;
         (void)locate(a.lo0, a.inv0, a.n0, l, c, w);
-        // as if the chain had just finished slice j_begin - 1 in that cell
-        sh.hist[0] = sh.hist[1] = pf_pack(a.j_begin - 1, c);
-        sh.done = 0;
+        sh.hist[threadIdx.x] = pf_pack(a.j_begin - 1, c);
     }
+    if (threadIdx.x == 0) sh.past[0] = a.j_begin;
     __syncthreads();
     if (wave == 0) {
         // the chain usually shares its CU with waves of a build still running
         __builtin_amdgcn_s_setprio(3);
-        pf_chain<T, Interp>(a, sh);
+        pf_chain<T, Interp>(a, sh, lay, final_out);
         if ((threadIdx.x & 63) == 0)
-            __hip_atomic_store(&sh.done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&sh.past[0], 0x7fffffff, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {
-        pf_helper<T>(a, sh, wave);
+        pf_helper<T, Interp>(a, sh, lay, wave - 1);
     }
 }
 

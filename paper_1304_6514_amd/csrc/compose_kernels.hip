@@ -31,8 +31,8 @@ __global__ void compose_kernel(ComposeArgs a) {
 // The 1-D chain with its table windows staged in LDS by helper waves: one
 // workgroup of 1 + kPfHelpers waves.
 template <class T, int Interp>
-__global__ __launch_bounds__(64 * (1 + kPfHelpers)) void compose_staged_kernel(ComposeArgs a) {
-    __shared__ PfShared<Interp> sh;
+__global__ __launch_bounds__(kPfThreads) void compose_staged_kernel(ComposeArgs a) {
+    __shared__ PfShared sh;
     if (blockIdx.x != 0) return;
     compose_range_staged<T, Interp>(a, sh);
 }
@@ -60,7 +60,7 @@ __global__ void locate_kernel(double lo, double inv, int n, const double *x, lon
 }  // namespace
 
 hipError_t launch_compose(int interp, int precision, const ComposeArgs &a, hipStream_t s) {
-    const dim3 grid(1), block(64), staged(64 * (1 + kPfHelpers));
+    const dim3 grid(1), block(64), staged(kPfThreads), staged_2d(64 * (1 + kPfHelpers));
     // cells and window origins of the staged bilinear chain are packed 16 bits per axis
     const bool staged2 = a.n0 <= kPf2MaxAxis && a.n1 <= kPf2MaxAxis;
     if (precision == 0) {
@@ -69,7 +69,7 @@ hipError_t launch_compose(int interp, int precision, const ComposeArgs &a, hipSt
         case 1: hipLaunchKernelGGL((compose_staged_kernel<double, 1>), grid, staged, 0, s, a); break;
         case 2:
             if (staged2)
-                hipLaunchKernelGGL((compose_staged2_kernel<double>), grid, staged, 0, s, a);
+                hipLaunchKernelGGL((compose_staged2_kernel<double>), grid, staged_2d, 0, s, a);
             else
                 hipLaunchKernelGGL((compose_kernel<double, 2>), grid, block, 0, s, a);
             break;
@@ -83,7 +83,7 @@ hipError_t launch_compose(int interp, int precision, const ComposeArgs &a, hipSt
         case 1: hipLaunchKernelGGL((compose_staged_kernel<float, 1>), grid, staged, 0, s, a); break;
         case 2:
             if (staged2)
-                hipLaunchKernelGGL((compose_staged2_kernel<float>), grid, staged, 0, s, a);
+                hipLaunchKernelGGL((compose_staged2_kernel<float>), grid, staged_2d, 0, s, a);
             else
                 hipLaunchKernelGGL((compose_kernel<float, 2>), grid, block, 0, s, a);
             break;
