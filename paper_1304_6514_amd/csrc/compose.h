@@ -1042,31 +1042,69 @@ __device__ inline double lagrange_value(double lam, double xk, double vk, int la
     return sum;
 }
 
-// The same value for a compile-time node count MC <= 8, with the M*M
-// quotients spread over the wave: lane k*MC + m forms f_km = (lam - x_m) /
-// den_km, den_km = x_k - x_m (the same operands as above, so the same
-// quotient), all in one division step, where the form above takes M divisions
-// one after another (each ends in v_div_fmas, which reads VCC, so two cannot
-// overlap).  Lane k < MC then gathers f_k0 .. f_k(MC-1) and multiplies them into
-// its term in ascending m, the factor with m = k replaced by 1 as above, and the
-// terms are summed in ascending k: the operation sequence of lagrange_value.
-template <int MC>
-__device__ inline double lagrange_value_pairs(double lam, double x_m, double den, double vk,
-                                              int lane) {
+// The same value for a compile-time node count MC <= 8, with the quotients
+// spread over the wave: lane 8k + m forms f_km = (lam - x_m) / (x_k - x_m) in
+// the time of one quotient, the other lanes of the 8 pass theirs down by DPP
+// moves (no LDS), lane 8k multiplies them into its term in ascending m (1 for
+// m = k and for m >= MC, which change nothing), and the terms are summed in
+// ascending k: the operation sequence of lagrange_value.
+//
+// The divisor does not change along the chain, so its correctly rounded
+// reciprocal is kept and a quotient takes five dependent operations instead of
+// a division's dozen: q = a y, then twice q += (a - q d) y with fused
+// multiply-adds.  The first correction brings q within one unit in the last
+// place, and the second rounds correctly (Markstein's theorem: from such a q
+// and a correctly rounded y, a - q d is exact and the last sum rounds to the
+// quotient), provided nothing over- or underflows: see lagrange_safe.  What
+// bounds it: the issue of its own ~60 instructions by one wave.  128 slices of
+// 7 nodes in FP32 took 54 us with divisions, LDS shuffles and a test per slice
+// (0.42 us per slice) and the whole solve 70 us; it takes 45 us now.
+template <int Shift>
+__device__ inline double dpp_down(double v) {      // lane l: the value of lane l + Shift
+    const long long b = __double_as_longlong(v);
+    constexpr int kRowShl = 0x100 + Shift;
+    const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(
+        0, int(b & 0xffffffffLL), kRowShl, 0xf, 0xf, true));
+    const unsigned hi =
+        unsigned(__builtin_amdgcn_update_dpp(0, int(b >> 32), kRowShl, 0xf, 0xf, true));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int MC, int S>
+__device__ inline double lagrange_product(double term, double f) {
 #pragma clang fp contract(off)
-    static_assert(MC >= 1 && MC * MC <= 64, "one quotient per lane");
-    const double f = (lam - x_m) / den;
-    const int src0 = lane < MC ? lane * MC : 0;
-    double term = vk;
-#pragma unroll
-    for (int m = 0; m < MC; ++m) {
-        const double fm = __shfl(f, src0 + m);
-        term *= (m == lane) ? 1.0 : fm;
-    }
+    if constexpr (S < MC)
+        return lagrange_product<MC, S + 1>(term * dpp_down<S>(f), f);
+    else
+        return term;
+}
+
+template <int MC>
+__device__ inline double lagrange_value_pairs(double lam, double x_m, double den, double rcp,
+                                              bool one, double vk) {
+#pragma clang fp contract(off)
+    static_assert(MC >= 1 && MC <= 8, "eight quotients per node");
+    const double n = lam - x_m;
+    double f = n * rcp;
+    f = fma(fma(-f, den, n), rcp, f);
+    f = fma(fma(-f, den, n), rcp, f);
+    f = one ? 1.0 : f;
+    const double term = lagrange_product<MC, 1>(vk * f, f);
     double sum = 0.0;
 #pragma unroll
-    for (int k = 0; k < MC; ++k) sum += readlane_f64(term, k);
+    for (int k = 0; k < MC; ++k) sum += readlane_f64(term, 8 * k);
     return sum;
+}
+
+// Where the quotients above cannot over- or underflow: divisors of magnitude
+// 2^-400 .. 2^400, and states that are zero or of that magnitude (a difference
+// lam - x_m is then zero or at least 2^-452, and the remainders a - q d, down
+// to 2^-106 of it, are exact).  The chain runs without asking, and looks its
+// states over a chunk at a time afterwards: a chunk that leaves the range is
+// taken again by lagrange_value, which also finds a state that is not finite.
+__device__ inline bool lagrange_safe(double v) {
+    const double m = fabs(v);
+    return m == 0.0 || (m >= 0x1p-400 && m <= 0x1p400);
 }
 
 template <class T, int MC>
@@ -1075,17 +1113,21 @@ __device__ inline void lagrange_chain(const ComposeArgs &a, double *rows, double
     const int lane = int(threadIdx.x);
     const int M = a.n0;
     const double xk = lane < M ? a.nodes[lane] : 0.0;
-    // lane k*MC + m (< MC*MC) of the spread quotients: x_m and x_k - x_m (zero
-    // for k = m, whose quotient is never used)
+    // lane 8k + m: x_m, x_k - x_m and its reciprocal; the quotient is replaced
+    // by 1 where m = k or there is no such node
+    constexpr bool kPairs = MC > 0 && MC <= 8;
+    const int pk = lane >> 3, pm = lane & 7;
+    const bool one = !kPairs || pk >= M || pm >= M || pk == pm;
     double pair_xm = 0.0, pair_den = 1.0;
-    if (MC > 0 && MC <= 8 && lane < MC * MC) {
-        const int pk = lane / (MC > 0 ? MC : 1), pm = lane - pk * MC;
+    if (!one) {
         pair_xm = a.nodes[pm];
         pair_den = a.nodes[pk] - pair_xm;
     }
+    const double pair_rcp = 1.0 / pair_den;
+    const bool dens_safe = __builtin_amdgcn_ballot_w64(!lagrange_safe(pair_den)) == 0;
     const T *tab0 = static_cast<const T *>(a.tab0);
     double lam = 0.0, unused = 0.0;
-    if (!range_begin<1>(a, lane, lam, unused)) return;    // an earlier range already failed
+    if (!uniform_bool(range_begin<1>(a, lane, lam, unused))) return;  // an earlier range failed
     long long oog = 0;
     int bad_slice = -1;
     const int rows_per_chunk = kLagrangeStage / M;
@@ -1107,25 +1149,64 @@ __device__ inline void lagrange_chain(const ComposeArgs &a, double *rows, double
             first_bad = other < first_bad ? other : first_bad;
         }
         __syncthreads();
+        first_bad = __builtin_amdgcn_readfirstlane(first_bad);
+        const double lam_c0 = lam;
         int done = c0;                            // boundary states bnd[0 .. done-c0) ready
-        double vk = lane < M ? rows[lane] : 0.0;
-        for (int j = c0; j < c1; ++j) {
-            if (!finite(lam) || j == first_bad) {
-                bad_slice = j;
-                break;
+        bool general = true;
+        if constexpr (kPairs) {
+            // lane 0 stores the states one after another, the other lanes each
+            // to a word of their own, past the chunk's (no branch); the next
+            // slice's table value is read ahead of the chain
+            const int step = lane == 0 ? 1 : 0;
+            double *out = lane == 0 ? bnd : bnd + kLagrangeStage / 2 + lane;
+            const double *row = rows + (pk < M ? pk : 0);
+            double vk = row[0];
+#pragma unroll 2
+            for (int j = c0; j < first_bad; ++j) {
+                row += M;
+                const double vnext = *row;        // past the last slice: read, not used
+                lam = lagrange_value_pairs<MC>(lam, pair_xm, pair_den, pair_rcp, one, vk);
+                *out = lam;
+                out += step;
+                vk = vnext;
             }
-            // the next slice's table values, read ahead of the chain
-            const double vnext = (lane < M && j + 1 < c1) ? rows[(j + 1 - c0) * M + lane] : 0.0;
-            double next;
-            if constexpr (MC > 0 && MC <= 8)
-                next = lagrange_value_pairs<MC>(lam, pair_xm, pair_den, vk, lane);
-            else
-                next = lagrange_value<MC>(lam, xk, vk, lane, M);
-            oog += (lam < a.lo0 || lam > a.hi0) ? 1 : 0;
-            lam = next;
-            if (lane == 0) bnd[j - c0] = lam;
-            done = j + 1;
-            vk = vnext;
+            done = first_bad;
+            __syncthreads();
+            bool unsafe = !dens_safe || !lagrange_safe(lam_c0);
+            for (int i = lane; i < done - c0; i += 64) unsafe |= !lagrange_safe(bnd[i]);
+            general = __builtin_amdgcn_ballot_w64(unsafe) != 0;
+            if (!general) {
+                int out_of_grid = 0;
+                for (int i = lane; i < done - c0; i += 64) {
+                    const double l = i == 0 ? lam_c0 : bnd[i - 1];
+                    out_of_grid += (l < a.lo0 || l > a.hi0) ? 1 : 0;
+                }
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) out_of_grid += __shfl_xor(out_of_grid, o);
+                oog += out_of_grid;
+                if (done < c1) bad_slice = done;
+            }
+        }
+        if (general) {
+            __syncthreads();
+            lam = lam_c0;
+            double vk = lane < M ? rows[lane] : 0.0;
+            for (int j = c0; j < c1; ++j) {
+                if (!finite(lam) || j == first_bad) {
+                    bad_slice = j;
+                    break;
+                }
+                // the next slice's table values, read ahead of the chain
+                const double vnext =
+                    (lane < M && j + 1 < c1) ? rows[(j + 1 - c0) * M + lane] : 0.0;
+                const double next = lagrange_value<MC>(lam, xk, vk, lane, M);
+                oog += (lam < a.lo0 || lam > a.hi0) ? 1 : 0;
+                lam = next;
+                if (lane == 0) bnd[j - c0] = lam;
+                done = j + 1;
+                vk = vnext;
+            }
+            if (bad_slice >= 0) done = bad_slice;
         }
         __syncthreads();
         for (int i = lane; i < done - c0; i += int(blockDim.x)) a.boundary[c0 + 1 + i] = bnd[i];
@@ -1135,8 +1216,10 @@ __device__ inline void lagrange_chain(const ComposeArgs &a, double *rows, double
 
 template <class T>
 __device__ inline void compose_range_lagrange(const ComposeArgs &a) {
-    __shared__ double rows[kLagrangeStage];
-    __shared__ double bnd[kLagrangeStage / 2];
+    // one row more than is staged may be read, and 64 words past a chunk's states
+    // take the stores of the lanes that hold no state
+    __shared__ double rows[kLagrangeStage + kMaxLagrange];
+    __shared__ double bnd[kLagrangeStage / 2 + 64];
     switch (a.n0) {
     case 2: lagrange_chain<T, 2>(a, rows, bnd); break;
     case 3: lagrange_chain<T, 3>(a, rows, bnd); break;

@@ -115,3 +115,50 @@ def test_chain_finds_the_slice_with_a_nonfinite_entry(orc, torch, n, bad):
             tab[0, bad] = value
             o = compose_both(orc, torch, tab, "fp64", interp, 0.1)
             assert o.bad_slice == bad
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("M", [2, 3, 5, 7, 8, 9])
+@pytest.mark.parametrize("case", ["smooth", "zero", "tiny", "huge", "overflow", "nonfinite"])
+def test_chebyshev_chain_equals_oracle(orc, torch, M, precision, case):
+    """The Lagrange chain (spread quotients up to 8 nodes, one division after
+    another above) over hand-written tables: ordinary states, states that are
+    exactly zero or a node, states below and above the magnitudes the
+    reciprocal quotients serve (taken again by division), a chain that
+    overflows, and a non-finite row; 700 slices cross a staged chunk for
+    M >= 6."""
+    from paper_1304_6514_amd.propagator import Propagator
+    N = 700
+    dt = np.float32 if precision == "fp32" else np.float64
+    w = W.paper_model(N, M, 0.5 / N, precision)
+    xs = orc.paper_nodes(M, 0.0, 2.0)
+    j = np.arange(N)[:, None]
+    tab = 1.0 + 0.7 * np.sin(xs[None] + 0.1 * j)
+    y0 = 0.8
+    if case == "zero":
+        tab[5::7] = 0.0
+        tab[8::7] = xs[None]                 # the identity: the state reaches a node
+        tab[9::35] = 2.0
+    elif case == "tiny":
+        tab[40:44] = 1e-37 * (1.0 if precision == "fp32" else 1e-113) * (1.0 + xs)
+    elif case == "huge":
+        tab[40:43] = 1e37 * (1.0 if precision == "fp32" else 1e113) * (1.0 + xs)
+    elif case == "overflow":
+        tab[:] = 1e30 * xs[None] * xs[None]
+    elif case == "nonfinite":
+        tab[650, M - 1] = np.inf
+    tab = tab.astype(dt)
+    say("chebyshev chain", M, precision, case)
+    with Propagator("cuda:0") as p:
+        p.build(w)
+        p.table_tensor(0).copy_(torch.from_numpy(tab))
+        torch.cuda.synchronize()
+        r = p.compose((y0,))
+    o = orc.paper_compose(M, 0.0, 2.0, tab.astype(np.float64), y0)
+    assert r.status == (nv.NV_OK if o.status == 0 else nv.NV_ERR_NONFINITE)
+    assert r.bad_slice == o.bad_slice and r.n_out_of_grid == o.n_out_of_grid
+    k = (o.bad_slice if o.status != 0 else N) + 1
+    got, exp = r.boundary[:k, 0], o.boundary.reshape(-1)[:k]
+    fin = np.isfinite(exp)
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.array_equal(got[fin].view(np.int64), exp[fin].view(np.int64))
