@@ -26,8 +26,8 @@
  * Slices: L = (T - t0)/N; each slice takes floor(L/dt + 1e-9) steps of dt and
  * one step of the remainder when it exceeds 1e-12 L (step s of slice j ends at
  * T_j + (s+1) dt).  Everything is FP64 with one rounding per operation, and
- * a(t), beta(t) and sin(pi x_i) are evaluated on the host, so the tables and the
- * composition are specified to the bit.
+ * a(t), beta(t) and sin(pi x_i) are evaluated on the host, so the tables are
+ * specified to the bit.
  *
  * Conventions as in nv.h (status codes, nv_last_error, one thread per object).
  */
@@ -69,9 +69,15 @@ NV_API nv_status nv_lin_build(nv_lin *lin, const nv_heat *problem, double t0, do
 /* Communication phase: lambda_0 = y0 (host, M values), lambda_{j+1} = c_j +
  * G_j lambda_j, component i formed as c_i + (((p0 + p1) + (p2 + p3)) + ((p4 +
  * p5) + (p6 + p7))) with p_r = G_i,r l_r + G_i,r+8 l_r+8 + ... summed left to
- * right from 0 (k counted from 0): eight independent chains instead of one.  yT (host, M) receives lambda_N; boundary (host, (N+1) x M, may be
- * NULL) every lambda_j.  Synchronous.  Errors: INVALID_ARG, NOT_BUILT,
- * NONFINITE (a state became non-finite), HIP. */
+ * right from 0 (k counted from 0): eight independent chains instead of one.
+ * From 64 slices on the maps are first multiplied together in blocks of 8
+ * slices (and blocks of blocks), the states at the blocks' ends are formed
+ * that way from the products, and the states inside a block from the one at
+ * its start: every state is within the FP64 inner-product rounding bound of
+ * the slice-by-slice order (G_j is non-negative with row sums of at most 1, so
+ * the products cancel nothing).  yT (host, M) receives lambda_N; boundary
+ * (host, (N+1) x M, may be NULL) every lambda_j.  Synchronous.  Errors:
+ * INVALID_ARG, NOT_BUILT, NONFINITE (a state became non-finite), HIP. */
 NV_API nv_status nv_lin_compose(nv_lin *lin, const double *y0, double *yT, double *boundary);
 
 /* Communication phase for many initial values (sec. 5, equation
@@ -79,10 +85,12 @@ NV_API nv_status nv_lin_compose(nv_lin *lin, const double *y0, double *yT, doubl
  * chains lambda^q_{j+1} = c_j + G_j lambda^q_j, q = 0..count-1, evaluated as
  * FP64 matrix products G_j [lambda^q ... lambda^{q+15}] on the matrix cores,
  * 16 chains per workgroup (32, sharing the workgroup's table reads, when
- * count fills two such workgroups per compute unit and M <= 116).  Each component's sum c_i + sum_k G_ik l_k is
- * formed by the matrix cores in an order this interface does not fix (so
- * results are within the FP64 inner-product rounding bound of any order, not
- * bit-equal to nv_lin_compose).
+ * count fills two such workgroups per compute unit and M <= 116), from 64
+ * slices on through the products of blocks of slices as above (only those
+ * when no boundary states are asked for).  Each component's sum c_i + sum_k
+ * G_ik l_k is formed by the matrix cores in an order this interface does not
+ * fix (so results are within the FP64 inner-product rounding bound of any
+ * order, not bit-equal to nv_lin_compose).
  *   y0_dev        device, count x M doubles (chain q's initial value at q M)
  *   yT_dev        device, count x M doubles: lambda^q_N
  *   boundary_dev  device, count x (N + 1) x M doubles, chain-major

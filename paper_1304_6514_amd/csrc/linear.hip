@@ -274,12 +274,63 @@ __global__ __launch_bounds__(128) void lin_build_reg_kernel(BuildArgs a) {
     if (Ms > M) col[M] = 0.0;
 }
 
+// ---- blocks of slices ------------------------------------------------------
+//
+// The chain of N affine maps takes N dependent steps, whatever the chip could
+// do at once.  Composition is associative, so the maps are first multiplied
+// together in blocks of kBlock (every block on its own, as matrix products),
+// the blocks' maps again in blocks while there are more than kTopMaps of them,
+// and the states run through the few maps of the top level; the states inside
+// a block, where they are asked for, then follow from the state at its start,
+// every block on its own again.  A level's maps lie in memory as the slices'
+// do, so the same kernels run on all of them.  At M = 99, N = 1024 a chain's
+// dependent steps fall from 1024 to 7 + 7 + 16 (+ 7 + 7 for the inner states).
+//
+// Rounding.  a(t) is positive, so every G_j is the inverse of an M-matrix:
+// non-negative, with row sums of at most 1.  Products of such matrices have no
+// cancellation: a block's map carries a relative error of at most kBlock
+// gamma_M in every entry, and a state formed with it stays within the rounding
+// bound of any other order of the same sums.
+//
+// A state or a map that exceeds kLargest (or is not finite) is reported by the
+// kernels, and the chains are then run slice by slice, which names the slice.
+constexpr int kBlock = 8;               // 16 was no faster: the first products take longer
+constexpr int kTopMaps = 16;            // fewer maps are not worth another level's launches
+constexpr int kBlockedFrom = 64;        // slices; below, the launches cost what the steps save
+constexpr double kLargest = 1e300;
+constexpr int kNoSlice = 0x7fffffff;
+
+// Which maps a launch runs through: block b of the level starts at map
+// b kBlock (one block of all `maps` maps when whole); map m of the level
+// starts at slice m stride.
+struct LevelArgs {
+    const double *T;            // the level's maps, [maps][Ms (M + 1)]
+    int M, N;                   // interior points; slices of the whole chain
+    int maps, stride;
+    int whole;
+    double largest;             // a state beyond it is reported
+};
+
+struct LevelRange {
+    int first, count;           // the block's maps
+    __device__ LevelRange(const LevelArgs &a, int b) {
+        first = a.whole ? 0 : b * kBlock;
+        count = a.whole ? a.maps : (a.maps - first < kBlock ? a.maps - first : kBlock);
+    }
+};
+
+// The slice a state lies at after t maps of the block.
+__device__ inline long long level_slice(const LevelArgs &a, int first, int t) {
+    const long long s = (long long)(first + t) * a.stride;
+    return s < a.N ? s : a.N;
+}
+
 struct ComposeArgs {
-    const double *T;            // [N][Ms (M + 1)]
-    const double *y0;           // device [M]
+    LevelArgs lv;
+    const double *y0;           // device [M]: the state at slice 0 (whole level)
     double *boundary;           // device [(N+1)][M]
-    int *bad;                   // first slice whose state is not finite, or -1
-    int M, N;
+    int *bad;                   // a whole level sets it: the first map whose state is beyond the
+                                // limit, or -1; blocks set it to 0 when one of theirs is
 };
 
 __device__ inline double lin_readlane(double v, int l) {
@@ -316,7 +367,15 @@ __global__ __launch_bounds__(512) void lin_chain_kernel(ComposeArgs a) {
     __shared__ int bad_s;
     const int tid = int(threadIdx.x), lane = tid & 63;
     const int r = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int M = a.M, N = a.N, Ms = lin_stride(M), per = Ms * (M + 1);
+    const int M = a.lv.M, Ms = lin_stride(M), per = Ms * (M + 1);
+    const LevelRange rg(a.lv, int(blockIdx.x));
+    // a block ends one map early: the state after it is the next block's first
+    const int N = a.lv.whole ? rg.count : rg.count - 1;
+    if (N < 1) return;
+    const double *T = a.lv.T + (long long)rg.first * per;
+    const double *start = a.lv.whole
+                              ? a.y0
+                              : a.boundary + level_slice(a.lv, rg.first, 0) * M;
     const int mr = r < M ? (M - r + 7) / 8 : 0;        // components k = r + 8m < M
     const int i2 = 2 * lane;                           // the lane's first row
     // byte offsets within a slice block: column k starts at the wave-uniform
@@ -335,10 +394,10 @@ __global__ __launch_bounds__(512) void lin_chain_kernel(ComposeArgs a) {
 #pragma unroll
     for (int m = 0; m < KM; ++m) {
         const int k = r + 8 * m;
-        lam[m] = k < M ? a.y0[k] : 0.0;
+        lam[m] = k < M ? start[k] : 0.0;
     }
-    if (tid < M) a.boundary[tid] = a.y0[tid];
-    if (tid == 0) bad_s = 0x7fffffff;
+    if (a.lv.whole && tid < M) a.boundary[tid] = start[tid];
+    if (tid == 0) bad_s = kNoSlice;
 
     double2 g[D][KM];
     double cv[D];
@@ -353,7 +412,7 @@ __global__ __launch_bounds__(512) void lin_chain_kernel(ComposeArgs a) {
     do {                                                                                 \
         const int s_ = __builtin_amdgcn_readfirstlane((s) < N ? (s) : N - 1);            \
         const __amdgpu_buffer_rsrc_t rs_ = __builtin_amdgcn_make_buffer_rsrc(            \
-            (void *)(a.T + (long long)s_ * per), 0, per * 8, kBufferWord3);              \
+            (void *)(T + (long long)s_ * per), 0, per * 8, kBufferWord3);                \
         _Pragma("unroll") for (int m = 0; m < KM; ++m) {                                 \
             const int col_ = (r + 8 * m < M ? r + 8 * m : M - 1) * Ms * 8;               \
             g[slot][m] = __builtin_bit_cast(                                             \
@@ -386,8 +445,8 @@ __global__ __launch_bounds__(512) void lin_chain_kernel(ComposeArgs a) {
                              ((q[4 * kRow] + q[5 * kRow]) + (q[6 * kRow] + q[7 * kRow])); \
             v = (c_now) + s;                                                             \
             if ((j) < N) {                                                               \
-                a.boundary[(long long)((j) + 1) * M + k] = v;                            \
-                if (!isfinite(v)) atomicMin(&bad_s, (j));                                \
+                a.boundary[level_slice(a.lv, rg.first, (j) + 1) * M + k] = v;            \
+                if (!(fabs(v) <= a.lv.largest)) atomicMin(&bad_s, (j));                  \
             }                                                                            \
         }                                                                                \
         _Pragma("unroll") for (int m = 0; m < KM; ++m) lam[m] = lin_readlane(v, m);      \
@@ -416,7 +475,12 @@ __global__ __launch_bounds__(512) void lin_chain_kernel(ComposeArgs a) {
 #undef NV_LIN_PARTIAL
 #undef NV_LIN_COMBINE
     __syncthreads();
-    if (tid == 0) *a.bad = bad_s == 0x7fffffff ? -1 : bad_s;
+    if (tid == 0) {
+        if (a.lv.whole)
+            *a.bad = bad_s == kNoSlice ? -1 : bad_s;
+        else if (bad_s != kNoSlice)
+            *a.bad = 0;
+    }
 }
 
 // prefetch depth for KM loads per slice: a ring of about 72 doubles per lane
@@ -429,7 +493,9 @@ constexpr int lin_depth(int KM) {
 
 template <int KM>
 void lin_launch_chain(const ComposeArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL((lin_chain_kernel<KM, lin_depth(KM)>), dim3(1), dim3(512), 0, st, a);
+    const int blocks = a.lv.whole ? 1 : (a.lv.maps + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL((lin_chain_kernel<KM, lin_depth(KM)>), dim3(unsigned(blocks)), dim3(512), 0,
+                       st, a);
 }
 
 using LinLaunch = void (*)(const ComposeArgs &, hipStream_t);
@@ -459,14 +525,19 @@ const LinChainTable lin_chain;
 // registers while it computes slice j.  Every workgroup reads all N tables, so
 // the tables' traffic from the caches is (Q / 16 CB) x N x M (M + 1) doubles:
 // CB = 2 halves it for large Q.
+//
+// The same kernel multiplies the maps of a block together (`product`): the
+// M + 1 columns of the block's first map (c last) are the chains, run through
+// the block's other maps, c_j added to the last column only.
 struct ManyArgs {
-    const double *T;            // [N][Ms (M + 1)]
+    LevelArgs lv;
     const double *y0;           // [Q][M]
     double *yT;                 // [Q][M]
     double *boundary;           // [Q][N+1][M] or null
-    int *bad;                   // first slice whose state is not finite (atomic min), or -1
+    double *product;            // [blocks][Ms (M + 1)]: the blocks' maps, or null
+    int *bad;                   // first map whose state is beyond the limit (atomic min)
     long long Q;
-    int M, N;
+    int groups;                 // workgroups of one block of maps
 };
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -479,15 +550,38 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     __shared__ double lam[2][K][C];
     const int tid = int(threadIdx.x), lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int M = a.M, N = a.N, Ms = lin_stride(M), per = Ms * (M + 1);
+    const int M = a.lv.M, Ms = lin_stride(M), per = Ms * (M + 1);
+    // workgroup = column group + groups x block of maps
+    const int block = int(blockIdx.x / unsigned(a.groups)), group = int(blockIdx.x % unsigned(a.groups));
+    const LevelRange rg(a.lv, block);
+    const bool product = a.product != nullptr;
+    // the maps run through: all of a whole level; of a product all but the
+    // first (whose columns it starts from); of a block all but the last (the
+    // state after it is the next block's first)
+    const int N = a.lv.whole && !product ? rg.count : rg.count - 1;
+    const double *T0 = a.lv.T + (long long)rg.first * per;      // the block's first map
+    const double *T = product ? T0 + per : T0;
     const int col = lane & 15, kq = lane >> 4;
-    const long long q0 = (long long)blockIdx.x * C;
+    const long long Q = product ? M + 1 : a.Q;
+    const long long q0 = (long long)group * C;
+    const bool from_boundary = !product && !a.lv.whole;
+    const long long span = (long long)(a.lv.N + 1) * M;         // one chain's boundary states
+    int bad = kNoSlice;
+    if (product && blockIdx.x == 0 && tid == 0) *a.bad = kNoSlice;
     for (int e = tid; e < 2 * K * C; e += 512) {
         const int buf = e / (K * C), k = (e / C) % K, c = e % C;
-        const long long qq = q0 + c < a.Q ? q0 + c : a.Q - 1;
-        lam[buf][k][c] = (buf == 0 && k < M) ? a.y0[qq * M + k] : 0.0;
-        if (a.boundary && buf == 0 && k < M && q0 + c < a.Q)
-            a.boundary[(q0 + c) * (long long)(N + 1) * M + k] = a.y0[qq * M + k];
+        const long long qq = q0 + c < Q ? q0 + c : Q - 1;
+        double v = 0.0;
+        if (buf == 0 && k < M) {
+            v = product ? T0[qq * Ms + k]
+                        : (from_boundary
+                               ? a.boundary[qq * span + level_slice(a.lv, rg.first, 0) * M + k]
+                               : a.y0[qq * M + k]);
+            if (!product && a.lv.whole && a.boundary && q0 + c < Q)
+                a.boundary[qq * span + k] = v;
+            if (a.lv.largest < 1e301 && !(fabs(v) <= a.lv.largest)) bad = 0;
+        }
+        lam[buf][k][c] = v;
     }
     // the lane's A operand: row 16 w + col of G, columns 4 kk + kq (A[i][k] in
     // lane i + 16 k), B[k][j] in lane j + 16 k; the FP64 16 x 16 accumulator
@@ -496,12 +590,14 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     // of chain column col of each column block
     const int arow = 16 * w + col;
     const bool active = 16 * w < M;
-    bool live[CB];
-    long long q[CB];
+    bool live[CB], with_c[CB];
+    double *states[CB];                         // the chain's boundary states, or null
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-        q[cb] = q0 + 16 * cb + col;
-        live[cb] = q[cb] < a.Q;
+        const long long q = q0 + 16 * cb + col;
+        live[cb] = q < Q;
+        with_c[cb] = !product || q == M;
+        states[cb] = live[cb] && a.boundary ? a.boundary + q * span : nullptr;
     }
     // the A fragments and the c values of a slice, loaded unconditionally from
     // clamped (in-block) addresses, with no select after the load (which would
@@ -514,7 +610,7 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     double ga[KP], gb[KP], ca[4], cb4[4];
 #define NV_LIN_LOAD(g, cv, j)                                                            \
     do {                                                                                 \
-        const double *Tj_ = a.T + (long long)(j) * per;                                  \
+        const double *Tj_ = T + (long long)(j) * per;                                    \
         const int ar_ = arow < M ? arow : M - 1;                                         \
         _Pragma("unroll") for (int kk = 0; kk < KP; ++kk) {                              \
             const int k_ = 4 * kk + kq;                                                  \
@@ -551,12 +647,12 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
                 const v4d s_ = acc[cb] + acc1[cb];                                       \
                 _Pragma("unroll") for (int i = 0; i < 4; ++i) {                          \
                     const int r = 16 * w + 4 * i + kq;                                   \
-                    const double v = cv[i] + s_[i];                                      \
+                    const double v = (with_c[cb] ? cv[i] : 0.0) + s_[i];                 \
                     if (r < M) {                                                         \
                         lam[cur ^ 1][r][16 * cb + col] = v;                              \
-                        if (live[cb] && a.boundary)                                      \
-                            a.boundary[(q[cb] * (N + 1) + (j) + 1) * (long long)M + r] = v;  \
-                        if (live[cb] && !isfinite(v) && (j) < bad) bad = (j);            \
+                        if (states[cb])                                                  \
+                            states[cb][level_slice(a.lv, rg.first, (j) + 1) * M + r] = v;    \
+                        if (live[cb] && !(fabs(v) <= a.lv.largest) && (j) < bad) bad = (j);  \
                     }                                                                    \
                 }                                                                        \
             }                                                                            \
@@ -564,8 +660,8 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
         __syncthreads();                                                                 \
         cur ^= 1;                                                                        \
     } while (0)
-    int cur = 0, bad = 0x7fffffff;
-    if (active) NV_LIN_LOAD(ga, ca, 0);
+    int cur = 0;
+    if (active && N > 0) NV_LIN_LOAD(ga, ca, 0);
     __syncthreads();
     for (int j = 0; j < N; j += 2) {
         if (active) NV_LIN_LOAD(gb, cb4, j + 1 < N ? j + 1 : N - 1);
@@ -576,11 +672,30 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     }
 #undef NV_LIN_LOAD
 #undef NV_LIN_SLICE
-    for (int e = tid; e < M * C; e += 512) {
-        const int k = e / C, c = e % C;
-        if (q0 + c < a.Q) a.yT[(q0 + c) * M + k] = lam[cur][k][c];
+    if (product) {
+        // a column beyond the limit becomes NaN, so that a state formed with it
+        // is reported
+        __shared__ int beyond;
+        if (tid == 0) beyond = 0;
+        __syncthreads();
+        if (bad != kNoSlice) beyond = 1;
+        __syncthreads();
+        double *U = a.product + (long long)block * per;
+        for (int e = tid; e < Ms * C; e += 512) {
+            const int k = e % Ms, c = e / Ms;
+            if (q0 + c < Q)
+                U[(q0 + c) * Ms + k] =
+                    k < M ? (beyond ? __longlong_as_double(0x7ff8000000000000LL) : lam[cur][k][c])
+                          : 0.0;
+        }
+        return;
     }
-    if (bad != 0x7fffffff) atomicMin(a.bad, bad);
+    if (a.yT && a.lv.whole)
+        for (int e = tid; e < M * C; e += 512) {
+            const int k = e / C, c = e % C;
+            if (q0 + c < Q) a.yT[(q0 + c) * M + k] = lam[cur][k][c];
+        }
+    if (bad != kNoSlice) atomicMin(a.bad, bad);
 }
 
 // With enough chains for two workgroups of two column blocks on every CU, a
@@ -592,19 +707,23 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
 constexpr int kManyPairMaxKP = 29;
 
 template <int KP>
-void lin_launch_many(const ManyArgs &a, long long pair_from, hipStream_t st) {
+void lin_launch_many(ManyArgs a, long long pair_from, hipStream_t st) {
+    const long long Q = a.product ? a.lv.M + 1 : a.Q;
+    const long long blocks = a.lv.whole ? 1 : (a.lv.maps + kBlock - 1) / kBlock;
     if constexpr (KP <= kManyPairMaxKP) {
-        if (a.Q >= pair_from) {
-            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), dim3(unsigned((a.Q + 31) / 32)),
+        if (!a.product && Q * blocks >= pair_from && Q > 16) {
+            a.groups = int((Q + 31) / 32);
+            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), dim3(unsigned(a.groups * blocks)),
                                dim3(512), 0, st, a);
             return;
         }
     }
-    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), dim3(unsigned((a.Q + 15) / 16)), dim3(512), 0,
+    a.groups = int((Q + 15) / 16);
+    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), dim3(unsigned(a.groups * blocks)), dim3(512), 0,
                        st, a);
 }
 
-using ManyLaunch = void (*)(const ManyArgs &, long long, hipStream_t);
+using ManyLaunch = void (*)(ManyArgs, long long, hipStream_t);
 template <int... K>
 constexpr void many_fill(ManyLaunch *t, std::integer_sequence<int, K...>) {
     ((t[K] = &lin_launch_many<K + 1>), ...);
@@ -619,6 +738,8 @@ const LinManyTable lin_many;
 
 }  // namespace
 
+constexpr int kMaxLevels = 12;          // 8^12 exceeds any number of slices
+
 struct nv_lin {
     hipStream_t stream = nullptr;
     char *mem = nullptr;
@@ -626,6 +747,8 @@ struct nv_lin {
     // layout of the last build
     double *step = nullptr, *w = nullptr, *c = nullptr, *s = nullptr, *T = nullptr,
            *y0 = nullptr, *boundary = nullptr;
+    double *product[kMaxLevels] = {};   // the maps of level 1, 2, ...
+    int levels = 0;                     // of products, each of kBlock maps of the one below
     int *bad = nullptr;
     int M = 0, N = 0, S_tot = 0;
     bool built = false;
@@ -674,6 +797,45 @@ long long step_scalars(const nv_heat &p, double t0, double L, double dt, int S, 
         }
     }
     return -1;
+}
+
+// The maps of level v: the slices' (0), or the products of blocks of level v - 1.
+LevelArgs level_args(const nv_lin *l, int v, bool blocked, bool whole) {
+    LevelArgs a{};
+    a.T = v == 0 ? l->T : l->product[v - 1];
+    a.M = l->M;
+    a.N = l->N;
+    a.maps = l->N;
+    a.stride = 1;
+    for (int u = 0; u < v; ++u) {
+        a.maps = (a.maps + kBlock - 1) / kBlock;
+        a.stride *= kBlock;
+    }
+    a.whole = whole ? 1 : 0;
+    a.largest = blocked ? kLargest : 1.7976931348623157e308;
+    return a;
+}
+
+// The products of every level (the first launch also clears l->bad).
+hipError_t launch_products(nv_lin *l) {
+    for (int v = 0; v < l->levels; ++v) {
+        ManyArgs a{};
+        a.lv = level_args(l, v, true, false);
+        a.product = l->product[v];
+        a.bad = l->bad;
+        lin_many.f[(l->M + 3) / 4 - 1](a, 0, l->stream);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// One chain through level v: all of it from y0, or every block of it from the
+// state at its start.
+hipError_t launch_chain(nv_lin *l, int v, bool whole) {
+    ComposeArgs a{level_args(l, v, v > 0 || !whole, whole), l->y0, l->boundary, l->bad};
+    lin_chain.f[(l->M + 7) / 8 - 1](a, l->stream);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -771,6 +933,15 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
     const size_t o_y0 = off;   off = al(off + size_t(M) * 8);
     const size_t o_b = off;    off = al(off + (size_t(n_slices) + 1) * M * 8);
     const size_t o_bad = off;  off = al(off + sizeof(int));
+    // the products of blocks of slices, level by level
+    size_t o_prod[kMaxLevels] = {};
+    int levels = 0;
+    if (n_slices >= kBlockedFrom && n_slices <= (1 << 30))
+        for (int maps = n_slices; maps > kTopMaps && levels < kMaxLevels; ++levels) {
+            maps = (maps + kBlock - 1) / kBlock;
+            o_prod[levels] = off;
+            off = al(off + size_t(maps) * lin_stride(M) * (M + 1) * 8);
+        }
     if (off > l->mem_bytes) {
         if (l->mem) {
             NV_HIP(hipStreamSynchronize(l->stream));
@@ -792,6 +963,8 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
     l->y0 = reinterpret_cast<double *>(l->mem + o_y0);
     l->boundary = reinterpret_cast<double *>(l->mem + o_b);
     l->bad = reinterpret_cast<int *>(l->mem + o_bad);
+    l->levels = levels;
+    for (int v = 0; v < levels; ++v) l->product[v] = reinterpret_cast<double *>(l->mem + o_prod[v]);
     l->M = M;
     l->N = n_slices;
     l->S_tot = S_tot;
@@ -839,18 +1012,22 @@ NV_API nv_status nv_lin_compose(nv_lin *l, const double *y0, double *yT, double 
     const int M = l->M, N = l->N;
     NV_HIP(hipMemcpyAsync(l->y0, y0, size_t(M) * 8, hipMemcpyHostToDevice, l->stream));
     NV_HIP(hipEventRecord(l->e2, l->stream));
-    ComposeArgs a{l->T, l->y0, l->boundary, l->bad, M, N};
-    lin_chain.f[(M + 7) / 8 - 1](a, l->stream);
-    NV_HIP(hipGetLastError());
-    NV_HIP(hipEventRecord(l->e3, l->stream));
     int bad = -1;
-    NV_HIP(hipMemcpyAsync(&bad, l->bad, sizeof(int), hipMemcpyDeviceToHost, l->stream));
-    NV_HIP(hipMemcpyAsync(yT, l->boundary + size_t(N) * M, size_t(M) * 8, hipMemcpyDeviceToHost,
-                          l->stream));
-    if (boundary)
-        NV_HIP(hipMemcpyAsync(boundary, l->boundary, (size_t(N) + 1) * M * 8,
+    // by blocks; then, should a state be beyond what that serves, slice by slice
+    for (int levels = l->levels;; levels = 0) {
+        if (levels > 0) NV_HIP(launch_products(l));
+        NV_HIP(launch_chain(l, levels, true));
+        for (int v = levels - 1; v >= 0; --v) NV_HIP(launch_chain(l, v, false));
+        NV_HIP(hipEventRecord(l->e3, l->stream));
+        NV_HIP(hipMemcpyAsync(&bad, l->bad, sizeof(int), hipMemcpyDeviceToHost, l->stream));
+        NV_HIP(hipMemcpyAsync(yT, l->boundary + size_t(N) * M, size_t(M) * 8,
                               hipMemcpyDeviceToHost, l->stream));
-    NV_HIP(hipStreamSynchronize(l->stream));
+        if (boundary)
+            NV_HIP(hipMemcpyAsync(boundary, l->boundary, (size_t(N) + 1) * M * 8,
+                                  hipMemcpyDeviceToHost, l->stream));
+        NV_HIP(hipStreamSynchronize(l->stream));
+        if (levels == 0 || bad < 0) break;
+    }
     NV_HIP(hipEventElapsedTime(&l->compose_ms, l->e2, l->e3));
     if (bad >= 0) return fail(NV_ERR_NONFINITE, "the state became non-finite in slice %d", bad);
     return NV_OK;
@@ -862,22 +1039,44 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     if (count < 1) return fail(NV_ERR_INVALID_ARG, "count = %lld", count);
     if ((count + 15) / 16 > 0x7fffffffLL) return fail(NV_ERR_INVALID_ARG, "too many chains");
     if (!l->built) return fail(NV_ERR_NOT_BUILT, "no successful nv_lin_build");
-    const int M = l->M, N = l->N;
-    const int init = 0x7fffffff;
-    NV_HIP(hipMemcpyAsync(l->bad, &init, sizeof(int), hipMemcpyHostToDevice, l->stream));
-    NV_HIP(hipEventRecord(l->e2, l->stream));
-    ManyArgs a{l->T, y0_dev, yT_dev, boundary_dev, l->bad, count, M, N};
+    const int init = kNoSlice;
     int dev = 0, n_cu = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         n_cu < 1)
         n_cu = 256;
-    lin_many.f[(M + 3) / 4 - 1](a, 2LL * n_cu * 32, l->stream);
-    NV_HIP(hipGetLastError());
-    NV_HIP(hipEventRecord(l->e3, l->stream));
+    const long long pair_from = 2LL * n_cu * 32;
+    const ManyLaunch run = lin_many.f[(l->M + 3) / 4 - 1];
+    ManyArgs a{};
+    a.y0 = y0_dev;
+    a.yT = yT_dev;
+    a.boundary = boundary_dev;
+    a.bad = l->bad;
+    a.Q = count;
+    NV_HIP(hipEventRecord(l->e2, l->stream));
     int bad = init;
-    NV_HIP(hipMemcpyAsync(&bad, l->bad, sizeof(int), hipMemcpyDeviceToHost, l->stream));
-    NV_HIP(hipStreamSynchronize(l->stream));
+    // by blocks (if one launch can number all its workgroups); then, should a
+    // state be beyond what that serves, slice by slice
+    const long long most = ((count + 15) / 16) * ((l->N + kBlock - 1LL) / kBlock);
+    for (int levels = boundary_dev && most > 0x7fffffffLL ? 0 : l->levels;; levels = 0) {
+        if (levels > 0)
+            NV_HIP(launch_products(l));
+        else
+            NV_HIP(hipMemcpyAsync(l->bad, &init, sizeof(int), hipMemcpyHostToDevice, l->stream));
+        a.lv = level_args(l, levels, levels > 0, true);
+        run(a, pair_from, l->stream);
+        NV_HIP(hipGetLastError());
+        if (boundary_dev)
+            for (int v = levels - 1; v >= 0; --v) {
+                a.lv = level_args(l, v, true, false);
+                run(a, pair_from, l->stream);
+                NV_HIP(hipGetLastError());
+            }
+        NV_HIP(hipEventRecord(l->e3, l->stream));
+        NV_HIP(hipMemcpyAsync(&bad, l->bad, sizeof(int), hipMemcpyDeviceToHost, l->stream));
+        NV_HIP(hipStreamSynchronize(l->stream));
+        if (levels == 0 || bad == init) break;
+    }
     NV_HIP(hipEventElapsedTime(&l->compose_ms, l->e2, l->e3));
     if (bad != init)
         return fail(NV_ERR_NONFINITE, "a state became non-finite in slice %d", bad);

@@ -256,3 +256,73 @@ def test_compose_many_reports_a_nonfinite_chain(lin):
     with pytest.raises(nv.NvError) as e:
         nv.nv_lin_compose_many(lin.h, None, 4, None)
     assert e.value.status == nv.NV_ERR_INVALID_ARG
+
+
+# ---- chains long enough to run through products of blocks of slices ----------
+
+BLOCKED = [(M, N) for M in (1, 9, 16, 63, 99, 116, 127) for N in (64, 71)] + \
+          [(9, 128), (9, 129), (19, 300), (33, 1025), (8, 1500)]
+
+
+@pytest.mark.parametrize("M,N", BLOCKED, ids=[f"M{m}-N{n}" for m, n in BLOCKED])
+def test_blocked_chains_within_rounding_bound_of_oracle(lin, M, N):
+    """From 64 slices on the maps are multiplied together in blocks of 8 (one
+    or two levels, ragged last blocks): every boundary state of the single
+    chain and of many chains (ragged groups, one and two column blocks per
+    workgroup) lies within the rounding bound of the oracle's slice-by-slice
+    chain over the same tables, and final states do not depend on whether
+    the boundary states are asked for, nor on the number of chains."""
+    import torch
+    w = HeatWorkload(f"heat-M{M}-N{N}", M, 0.0013, N, T=0.0031 * N)
+    say("linear blocked", w.name)
+    lin.build(w)
+    G, c = lin.tables()
+    rng = np.random.default_rng(91)
+    y0 = rng.normal(0.0, 1.0, (300, M))
+    st, yT, bnd = lin.compose(y0[0])
+    assert st == nv.NV_OK and np.array_equal(yT, bnd[-1])
+    check_chain(G, c, bnd, lo.compose(G, c, y0[0]), w.name)
+    st, yT2, _ = lin.compose(y0[0], want_boundary=False)
+    assert st == nv.NV_OK and np.array_equal(yT2, yT)
+    for Q in (1, 37, 300):
+        st, yT, bnd = lin.compose_many(y0[:Q], want_boundary=True)
+        torch.cuda.synchronize()
+        assert st == nv.NV_OK
+        yT, bnd = yT.cpu().numpy(), bnd.cpu().numpy()
+        assert np.array_equal(yT, bnd[:, -1]) and np.array_equal(bnd[:, 0], y0[:Q])
+        for q in {0, Q // 2, Q - 1}:
+            check_chain(G, c, bnd[q], lo.compose(G, c, y0[q]), f"{w.name} Q={Q} chain {q}")
+        st, yT2, _ = lin.compose_many(y0[:Q])
+        assert st == nv.NV_OK and np.array_equal(yT2.cpu().numpy(), yT)
+        if Q == 1:
+            first = bnd[0]
+        assert np.array_equal(bnd[0], first)
+
+
+def test_blocked_chains_beyond_their_range_run_slice_by_slice(lin):
+    """Initial values beyond 1e300 (finite), where the blocks' products are not
+    used, and a NaN: the results of the slice-by-slice chain, and its slice
+    in the error."""
+    import torch
+    w = HeatWorkload("heat-M9-N100-range", 9, 0.01, 100, T=1.0)
+    lin.build(w)
+    G, c = lin.tables()
+    big = np.full(9, 1e304)
+    ref = lo.compose(G, c, big)
+    st, yT, bnd = lin.compose(big)
+    assert st == nv.NV_OK and np.all(np.isfinite(ref))
+    check_chain(G, c, bnd, ref, "1e304")
+    st, yT, bnd = lin.compose_many(np.stack([big, big]), want_boundary=True)
+    torch.cuda.synchronize()
+    assert st == nv.NV_OK
+    check_chain(G, c, bnd[1].cpu().numpy(), ref, "1e304 many")
+    y0 = np.tile(lo.exact(0.0, 9), (20, 1))
+    y0[17, 3] = np.nan
+    st, yT, bnd = lin.compose(y0[17])
+    assert st == nv.NV_ERR_NONFINITE and "slice 0" in nv.nv_last_error()
+    assert not np.all(np.isfinite(bnd[1]))
+    st, yT, _ = lin.compose_many(y0)
+    torch.cuda.synchronize()
+    assert st == nv.NV_ERR_NONFINITE and "slice 0" in nv.nv_last_error()
+    yT = yT.cpu().numpy()
+    assert not np.all(np.isfinite(yT[17])) and np.all(np.isfinite(np.delete(yT, 17, 0)))
