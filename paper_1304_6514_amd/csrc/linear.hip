@@ -4,12 +4,12 @@
 //   lin_coef_kernel   one thread per (slice, step): the Thomas coefficients
 //                     w_i, c_i of that step's tridiagonal matrix (a chain of M
 //                     divisions that every solve of the slice shares);
-//   lin_build_reg_kernel<MP> (M <= 104) / lin_build_kernel (larger M)
+//   lin_build_kernel<MP>
 //                     one workgroup per slice, one lane per solve: lane 0 the
 //                     forced solve from 0, lane k the homogeneous solve from
 //                     e_k; each lane's vector lives in registers (the sweeps
-//                     unrolled over MP rows) or, for the largest M, in LDS,
-//                     and the step's coefficients are staged in LDS.
+//                     unrolled over MP rows), a step's coefficients in the
+//                     lanes of the wave.
 // Communication phase: lin_chain_kernel, one workgroup of eight waves, wave r
 // forming the partial sums of residue r of the fixed summation order for
 // every component from table values prefetched into its registers several
@@ -46,19 +46,38 @@ struct CoefArgs {
     int M;
 };
 
-__global__ __launch_bounds__(256) void lin_coef_kernel(CoefArgs a) {
+// A thread's coefficients lie M values apart from the next thread's, so they go
+// through LDS kCoefRows rows at a time and leave as runs of consecutive values.
+// 20,480 steps of 99 rows: 38 -> 22 us.
+constexpr int kCoefRows = 16;
+
+__global__ __launch_bounds__(64) void lin_coef_kernel(CoefArgs a) {
 #pragma clang fp contract(off)
-    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (q >= a.count) return;
+    __shared__ double tile[2][64][kCoefRows + 1];
+    const int lane = int(threadIdx.x), M = a.M;
+    const long long q0 = (long long)blockIdx.x * 64;
+    const long long q = q0 + lane < a.count ? q0 + lane : a.count - 1;
     const double r = a.step[2 * q];
     const double diag = 1.0 + 2.0 * r, off = -r;
     double cp = 0.0;
-    for (int i = 0; i < a.M; ++i) {
-        const double den = i == 0 ? diag : diag - off * cp;
-        const double w = 1.0 / den;
-        cp = off * w;
-        a.w[q * a.M + i] = w;
-        a.c[q * a.M + i] = cp;
+    for (int i0 = 0; i0 < M; i0 += kCoefRows) {
+        const int rows = M - i0 < kCoefRows ? M - i0 : kCoefRows;
+        for (int i = 0; i < rows; ++i) {
+            const double den = i0 + i == 0 ? diag : diag - off * cp;
+            const double w = 1.0 / den;
+            cp = off * w;
+            tile[0][lane][i] = w;
+            tile[1][lane][i] = cp;
+        }
+        __syncthreads();
+        const int i = lane % kCoefRows;
+        if (i < rows)
+            for (int t = lane / kCoefRows; t < 64; t += 64 / kCoefRows)
+                if (q0 + t < a.count) {
+                    a.w[(q0 + t) * M + i0 + i] = tile[0][t][i];
+                    a.c[(q0 + t) * M + i0 + i] = tile[1][t][i];
+                }
+        __syncthreads();
     }
 }
 
@@ -76,203 +95,117 @@ struct BuildArgs {
 
 __host__ __device__ inline int lin_stride(int M) { return M + (M & 1); }
 
-// LDS of lin_build_kernel, in doubles: the lanes' vectors xs[M][M + 1]
-// (lane k's vector is column k, so the lanes of a wave touch consecutive
-// words), two buffers of one step's Thomas coefficients (w then c, M each)
-// and sin(pi x_i).
-inline size_t lin_build_lds_bytes(int M) { return size_t(M) * (M + 6) * sizeof(double); }
-
-// The coefficients of the step being solved are read from LDS (a broadcast
-// read whose address does not depend on the recurrence, so it can be issued
-// ahead of it); those of the next step are loaded into registers meanwhile
-// and published to the other buffer at the end of the step.
-__global__ __launch_bounds__(128) void lin_build_kernel(BuildArgs a) {
-#pragma clang fp contract(off)
-    constexpr int kPre = 2;                  // ceil(M / 64) for M <= 127
-    constexpr int kLook = 4;                 // rows read ahead of the recurrences
-    extern __shared__ double lds[];
-    const int nt = int(blockDim.x), lane = int(threadIdx.x), M = a.M, ncol = M + 1;
-    double *xs = lds, *wc = lds + M * ncol, *ss = wc + 4 * M;
-    const int j = int(blockIdx.x);
-    const bool live = lane <= M;             // lane 0: forced solve; lane k: from e_k
-    const bool forced = lane == 0 && a.forcing;
-    const long long q0 = (long long)j * a.S_tot;
-    if (live)
-        for (int i = 0; i < M; ++i) xs[i * ncol + lane] = (lane >= 1 && i == lane - 1) ? 1.0 : 0.0;
-    for (int v = lane; v < M; v += nt) {
-        ss[v] = a.s[v];
-        wc[v] = a.w[q0 * M + v];
-        wc[M + v] = a.c[q0 * M + v];
-    }
-    __syncthreads();
-    for (int st = 0; st < a.S_tot; ++st) {
-        const long long q = q0 + st;
-        const double off = -a.step[2 * q], hb = a.step[2 * q + 1];
-        // the next step's coefficients (the last step reloads its own), every
-        // load unconditional from a clamped index
-        const long long qn = st + 1 < a.S_tot ? q + 1 : q;
-        double pw[kPre], pc[kPre];
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int v = lane + u * nt < M ? lane + u * nt : M - 1;
-            pw[u] = a.w[qn * M + v];
-            pc[u] = a.c[qn * M + v];
-        }
-        const double *w = wc + (st & 1) * 2 * M, *c = w + M;
-        if (live) {
-            // Both sweeps read the rows, coefficients and sin values kLook rows
-            // ahead of the recurrence into a register ring (the row read ahead
-            // is written only later, when the sweep reaches it; a clamped index
-            // past the end reads a value that is never used).
-            double fr[kLook], wr[kLook], sr[kLook];
-#pragma unroll
-            for (int u = 0; u < kLook; ++u) {
-                const int iu = u < M ? u : M - 1;
-                fr[u] = xs[iu * ncol + lane];
-                wr[u] = w[iu];
-                sr[u] = ss[iu];
-            }
-            // forward elimination, in place
-            double fp = 0.0;
-            for (int i0 = 0; i0 < M; i0 += kLook) {
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    const int i = i0 + u;
-                    if (i < M) {
-                        double f = fr[u];
-                        const double wi = wr[u], si = sr[u];
-                        const int in = i + kLook < M ? i + kLook : M - 1;
-                        fr[u] = xs[in * ncol + lane];
-                        wr[u] = w[in];
-                        sr[u] = ss[in];
-                        if (forced) f = f + hb * si;
-                        fp = i == 0 ? f * wi : (f - off * fp) * wi;
-                        xs[i * ncol + lane] = fp;
-                    }
-                }
-            }
-            // back substitution, in place, rows M - 2 down to 0
-#pragma unroll
-            for (int u = 0; u < kLook; ++u) {
-                const int iu = M - 2 - u >= 0 ? M - 2 - u : 0;
-                fr[u] = xs[iu * ncol + lane];
-                wr[u] = c[iu];
-            }
-            double y = fp;
-            for (int i0 = M - 2; i0 >= 0; i0 -= kLook) {
-#pragma unroll
-                for (int u = 0; u < kLook; ++u) {
-                    const int i = i0 - u;
-                    if (i >= 0) {
-                        const double xi = fr[u], ci = wr[u];
-                        const int in = i - kLook >= 0 ? i - kLook : 0;
-                        fr[u] = xs[in * ncol + lane];
-                        wr[u] = c[in];
-                        y = xi - ci * y;
-                        xs[i * ncol + lane] = y;
-                    }
-                }
-            }
-        }
-        double *wn = wc + ((st + 1) & 1) * 2 * M;
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int v = lane + u * nt;
-            if (v < M) {
-                wn[v] = pw[u];
-                wn[M + v] = pc[u];
-            }
-        }
-        __syncthreads();
-    }
-    if (!live) return;
-    const int Ms = lin_stride(M);
-    double *blk = a.T + (long long)j * Ms * (M + 1);
-    double *col = lane == 0 ? blk + Ms * M : blk + (lane - 1) * Ms;
-    for (int i = 0; i < M; ++i) col[i] = xs[i * ncol + lane];
-    if (Ms > M) col[M] = 0.0;
+__device__ inline double lin_readlane(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(b & 0xffffffffLL), l));
+    const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(b >> 32), l));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// The same solves with each lane's vector in registers, for M <= MP: the
-// sweeps are unrolled over MP rows, so every row is a register of its own,
-// and LDS holds only the coefficients, which lets four workgroups share a CU
-// instead of one.  The staged coefficients are padded with zeros to MP rows,
-// so that every row reads its coefficient at a fixed offset; rows M .. MP-1 of
-// the forward sweep then hold zeros that no row below M reads, and the back
-// substitution starts at row M - 1 by a test on the wave-uniform M.  The
-// operations on rows 0 .. M-1 are those of lin_build_kernel, in the same order.
-template <int MP>
-__global__ __launch_bounds__(128) void lin_build_reg_kernel(BuildArgs a) {
+// Value i of 128 that the wave's lanes hold two each (i in lane i, 64 + i in
+// lane i again), in scalar registers.
+__device__ inline double lin_pick(const double (&v)[2], int i) { return lin_readlane(v[i >> 6], i & 63); }
+
+// One backward Euler step of the lane's solve: the Thomas sweeps over MP >= M
+// rows, a row's coefficients taken from the lanes that hold them.  Rows M ..
+// MP-1 have coefficients 0 and stay 0, so that row M-1 of the back substitution
+// subtracts c * 0 and is x itself.  Forced: the lane's right-hand side is f + m
+// fs, m being 1 in the lane of the forced solve and 0 in the others: the
+// product is exact, so the fused operation rounds once, as f + fs does, and
+// leaves f alone elsewhere.
+template <int MP, bool Forced>
+__device__ inline void lin_step(double (&x)[MP], double off, const double (&w)[2],
+                                const double (&c)[2], const double (&fs)[2], double m) {
 #pragma clang fp contract(off)
-    constexpr int kPre = (MP + 63) / 64;     // staged rows per lane
-    __shared__ double wc[2][2][MP];          // [buffer][w, c][row]
-    __shared__ double ss[MP];
-    const int nt = int(blockDim.x), lane = int(threadIdx.x), M = a.M;
+    double fp = 0.0;
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+        double f = x[i];
+        if constexpr (Forced) f = fma(m, lin_pick(fs, i), f);
+        fp = i == 0 ? f * lin_pick(w, 0) : (f - off * fp) * lin_pick(w, i);
+        x[i] = fp;
+    }
+    double y = x[MP - 1];
+#pragma unroll
+    for (int i = MP - 2; i >= 0; --i) {
+        y = x[i] - lin_pick(c, i) * y;
+        x[i] = y;
+    }
+}
+
+// What bounds it: the issue of each wave's FP64 operations, five per row and
+// step, and of the four lane reads that bring the row's two coefficients into
+// scalar registers (with the coefficients staged in LDS, two to four waves per
+// SIMD waited for a read every other row: 226 us at M = 99, 1024 slices of 20
+// steps, where this takes 115 us; M = 127, 512 slices: 1059 -> 124 us).  Up to MP = 104 two waves share a SIMD;
+// above, a wave has the SIMD's registers to itself.
+template <int MP>
+__global__ __launch_bounds__(128, MP <= 104 ? 2 : 1) void lin_build_kernel(BuildArgs a) {
+#pragma clang fp contract(off)
+    const int solve = int(threadIdx.x), lane = solve & 63, M = a.M;
     const int j = int(blockIdx.x);
-    const bool live = lane <= M;             // lane 0: forced solve; lane k: from e_k
-    const bool forced = lane == 0 && a.forcing;
+    const bool forced = a.forcing && solve < 64;     // the wave of the forced solve
+    const double m = solve == 0 ? 1.0 : 0.0;
     const long long q0 = (long long)j * a.S_tot;
     double x[MP];
 #pragma unroll
-    for (int i = 0; i < MP; ++i) x[i] = (lane >= 1 && i == lane - 1) ? 1.0 : 0.0;
-    for (int v = lane; v < MP; v += nt) {
-        ss[v] = v < M ? a.s[v] : 0.0;
-        wc[0][0][v] = v < M ? a.w[q0 * M + v] : 0.0;
-        wc[0][1][v] = v < M ? a.c[q0 * M + v] : 0.0;
-    }
-    __syncthreads();
+    for (int i = 0; i < MP; ++i) x[i] = i == solve - 1 ? 1.0 : 0.0;
+    // rows lane and 64 + lane of a step's coefficients (0 past row M - 1)
+    const int r0 = lane < M ? lane : M - 1, r1 = 64 + lane < M ? 64 + lane : M - 1;
+    const bool in0 = lane < M, in1 = 64 + lane < M;
+    const double s[2] = {in0 ? a.s[r0] : 0.0, in1 ? a.s[r1] : 0.0};
+    double w[2], c[2];
+    w[0] = a.w[q0 * M + r0];
+    w[1] = a.w[q0 * M + r1];
+    c[0] = a.c[q0 * M + r0];
+    c[1] = a.c[q0 * M + r1];
     for (int st = 0; st < a.S_tot; ++st) {
         const long long q = q0 + st;
         const double off = -a.step[2 * q], hb = a.step[2 * q + 1];
+        // the next step's coefficients (the last step reloads its own)
         const long long qn = st + 1 < a.S_tot ? q + 1 : q;
-        double pw[kPre], pc[kPre];
+        const double wn[2] = {a.w[qn * M + r0], a.w[qn * M + r1]};
+        const double cn[2] = {a.c[qn * M + r0], a.c[qn * M + r1]};
+        const double ww[2] = {in0 ? w[0] : 0.0, in1 ? w[1] : 0.0};
+        const double cc[2] = {in0 ? c[0] : 0.0, in1 ? c[1] : 0.0};
+        const double fs[2] = {hb * s[0], hb * s[1]};
+        if (forced)
+            lin_step<MP, true>(x, off, ww, cc, fs, m);
+        else
+            lin_step<MP, false>(x, off, ww, cc, fs, m);
 #pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int v = lane + u * nt < M ? lane + u * nt : M - 1;
-            pw[u] = a.w[qn * M + v];
-            pc[u] = a.c[qn * M + v];
+        for (int u = 0; u < 2; ++u) {
+            w[u] = wn[u];
+            c[u] = cn[u];
         }
-        const double *w = wc[st & 1][0], *c = wc[st & 1][1];
-        // forward elimination
-        double fp = 0.0;
-#pragma unroll
-        for (int i = 0; i < MP; ++i) {
-            double f = x[i];
-            if (forced) f = f + hb * ss[i];
-            fp = i == 0 ? f * w[0] : (f - off * fp) * w[i];
-            x[i] = fp;
-        }
-        // back substitution from row M - 1
-        double y = 0.0;
-#pragma unroll
-        for (int i = MP - 1; i >= 0; --i) {
-            if (i == M - 1) {
-                y = x[i];
-            } else if (i < M - 1) {
-                y = x[i] - c[i] * y;
-                x[i] = y;
-            }
-        }
-        double(*wn)[MP] = wc[(st + 1) & 1];
-#pragma unroll
-        for (int u = 0; u < kPre; ++u) {
-            const int v = lane + u * nt;
-            if (v < MP) {
-                wn[0][v] = v < M ? pw[u] : 0.0;
-                wn[1][v] = v < M ? pc[u] : 0.0;
-            }
-        }
-        __syncthreads();
     }
-    if (!live) return;
+    if (solve > M) return;
     const int Ms = lin_stride(M);
     double *blk = a.T + (long long)j * Ms * (M + 1);
-    double *col = lane == 0 ? blk + Ms * M : blk + (lane - 1) * Ms;
+    double2 *col = reinterpret_cast<double2 *>(solve == 0 ? blk + Ms * M : blk + (solve - 1) * Ms);
 #pragma unroll
-    for (int i = 0; i < MP; ++i)
-        if (i < M) col[i] = x[i];
-    if (Ms > M) col[M] = 0.0;
+    for (int i = 0; i < MP; i += 2)             // row M of an odd M is padding: 0
+        if (i < M) col[i / 2] = double2{x[i], x[i + 1]};
 }
+
+template <int MP>
+void lin_launch_build(const BuildArgs &a, int n_slices, hipStream_t st) {
+    hipLaunchKernelGGL(lin_build_kernel<MP>, dim3(unsigned(n_slices)),
+                       dim3(unsigned(64 * ((a.M + 1 + 63) / 64))), 0, st, a);
+}
+
+using BuildLaunch = void (*)(const BuildArgs &, int, hipStream_t);
+template <int... K>
+constexpr void build_fill(BuildLaunch *t, std::integer_sequence<int, K...>) {
+    ((t[K] = &lin_launch_build<8 * (K + 1)>), ...);
+}
+
+// lin_build.f[k - 1] launches the build for ceil(M/8) = k
+struct LinBuildTable {
+    BuildLaunch f[16];
+    LinBuildTable() { build_fill(f, std::make_integer_sequence<int, 16>{}); }
+};
+const LinBuildTable lin_build;
 
 // ---- blocks of slices ------------------------------------------------------
 //
@@ -332,13 +265,6 @@ struct ComposeArgs {
     int *bad;                   // a whole level sets it: the first map whose state is beyond the
                                 // limit, or -1; blocks set it to 0 when one of theirs is
 };
-
-__device__ inline double lin_readlane(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = unsigned(__builtin_amdgcn_readlane(int(b & 0xffffffffLL), l));
-    const unsigned hi = unsigned(__builtin_amdgcn_readlane(int(b >> 32), l));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
 
 // third word of a buffer resource on gfx9-family chips (32-bit data format,
 // no swizzle): raw buffer loads then read num_records bytes from the base
@@ -975,26 +901,11 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
     NV_HIP(hipMemcpyAsync(l->s, sv.data(), sv.size() * 8, hipMemcpyHostToDevice, l->stream));
     NV_HIP(hipEventRecord(l->e0, l->stream));
     CoefArgs ca{l->step, l->w, l->c, nq, M};
-    hipLaunchKernelGGL(lin_coef_kernel, dim3(unsigned((nq + 255) / 256)), dim3(256), 0,
+    hipLaunchKernelGGL(lin_coef_kernel, dim3(unsigned((nq + 63) / 64)), dim3(64), 0,
                        l->stream, ca);
     NV_HIP(hipGetLastError());
     BuildArgs ba{l->step, l->w, l->c, l->s, l->T, M, S_tot, p->forcing ? 1 : 0};
-    const int ncol = 64 * ((M + 1 + 63) / 64);                // threads: one per solve
-    const dim3 grid{unsigned(n_slices)}, block{unsigned(ncol)};
-    if (M <= 8) hipLaunchKernelGGL(lin_build_reg_kernel<8>, grid, block, 0, l->stream, ba);
-    else if (M <= 16) hipLaunchKernelGGL(lin_build_reg_kernel<16>, grid, block, 0, l->stream, ba);
-    else if (M <= 24) hipLaunchKernelGGL(lin_build_reg_kernel<24>, grid, block, 0, l->stream, ba);
-    else if (M <= 32) hipLaunchKernelGGL(lin_build_reg_kernel<32>, grid, block, 0, l->stream, ba);
-    else if (M <= 48) hipLaunchKernelGGL(lin_build_reg_kernel<48>, grid, block, 0, l->stream, ba);
-    else if (M <= 64) hipLaunchKernelGGL(lin_build_reg_kernel<64>, grid, block, 0, l->stream, ba);
-    else if (M <= 80) hipLaunchKernelGGL(lin_build_reg_kernel<80>, grid, block, 0, l->stream, ba);
-    else if (M <= 104) hipLaunchKernelGGL(lin_build_reg_kernel<104>, grid, block, 0, l->stream, ba);
-    else {
-        const size_t lds = lin_build_lds_bytes(M);             // at most 127 x 133 x 8 bytes
-        NV_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(lin_build_kernel),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-        hipLaunchKernelGGL(lin_build_kernel, grid, block, lds, l->stream, ba);
-    }
+    lin_build.f[(M + 7) / 8 - 1](ba, n_slices, l->stream);
     NV_HIP(hipGetLastError());
     NV_HIP(hipEventRecord(l->e1, l->stream));
     // the host vectors must outlive the copies
