@@ -196,46 +196,36 @@ __device__ inline bool hermite_slopes_values(double ta, double tb, double ma, do
     return all_finite(ta, tb, da, db);
 }
 
-template <class T, int Interp>
-__device__ inline void compose_range(const ComposeArgs &a, double *final_out = nullptr) {
+template <class T>
+__device__ inline void compose_range_bilinear(const ComposeArgs &a, double *final_out = nullptr) {
 #pragma clang fp contract(off)
-    static_assert(Interp != 4, "stored slopes compose through the staged chain");
-    constexpr int D = Interp == 2 ? 2 : 1;
     const int lane = int(threadIdx.x) & 63;
     const T *tab0 = static_cast<const T *>(a.tab0);
     const T *tab1 = static_cast<const T *>(a.tab1);
     double lam0 = 0.0, lam1 = 0.0;
-    if (!range_begin<D>(a, lane, lam0, lam1)) return;     // an earlier range already failed
+    if (!range_begin<2>(a, lane, lam0, lam1)) return;     // an earlier range already failed
     long long oog = 0;
     int bad_slice = -1;
     double keep0 = 0.0, keep1 = 0.0;
     int jb = a.j_begin;                           // first slice of the current block
     int j = a.j_begin;
     for (; j < a.j_end; ++j) {
-        if (!finite(lam0) || (D == 2 && !finite(lam1))) {
+        if (!finite(lam0) || !finite(lam1)) {
             bad_slice = j;
             break;
         }
-        const T *row0 = tab0 + (long long)j * a.M;
+        const T *row0 = tab0 + (long long)j * a.M, *row1 = tab1 + (long long)j * a.M;
         long long i0, i1;
         double w0, w1;
         oog += locate(a.lo0, a.inv0, a.n0, lam0, i0, w0);
-        double next0, next1 = 0.0;
-        bool bad = false;
-        if constexpr (Interp == 0 || Interp == 1) {
-            bad = !interp_1d<Interp>([row0](long long k) { return double(row0[k]); }, i0, w0,
-                                     a.n0, next0);
-        } else {
-            oog += locate(a.lo1, a.inv1, a.n1, lam1, i1, w1);
-            const long long c00 = i0 * a.n1 + i1, c10 = (i0 + 1) * a.n1 + i1;
-            const T *row1 = tab1 + (long long)j * a.M;
-            const double p00 = double(row0[c00]), p01 = double(row0[c00 + 1]);
-            const double p10 = double(row0[c10]), p11 = double(row0[c10 + 1]);
-            const double q00 = double(row1[c00]), q01 = double(row1[c00 + 1]);
-            const double q10 = double(row1[c10]), q11 = double(row1[c10 + 1]);
-            bad = bilinear_values(p00, p01, p10, p11, q00, q01, q10, q11, w0, w1, next0, next1);
-        }
-        if (bad) {
+        oog += locate(a.lo1, a.inv1, a.n1, lam1, i1, w1);
+        const long long c00 = i0 * a.n1 + i1, c10 = (i0 + 1) * a.n1 + i1;
+        const double p00 = double(row0[c00]), p01 = double(row0[c00 + 1]);
+        const double p10 = double(row0[c10]), p11 = double(row0[c10 + 1]);
+        const double q00 = double(row1[c00]), q01 = double(row1[c00 + 1]);
+        const double q10 = double(row1[c10]), q11 = double(row1[c10 + 1]);
+        double next0, next1;
+        if (bilinear_values(p00, p01, p10, p11, q00, q01, q10, q11, w0, w1, next0, next1)) {
             bad_slice = j;
             break;
         }
@@ -246,20 +236,20 @@ __device__ inline void compose_range(const ComposeArgs &a, double *final_out = n
             keep1 = lam1;
         }
         if (j - jb == 63) {
-            a.boundary[(long long)(jb + lane + 1) * D] = keep0;
-            if (D == 2) a.boundary[(long long)(jb + lane + 1) * D + 1] = keep1;
+            a.boundary[(long long)(jb + lane + 1) * 2] = keep0;
+            a.boundary[(long long)(jb + lane + 1) * 2 + 1] = keep1;
             jb += 64;
         }
     }
     // the states of the last, partial block (slices jb .. j-1)
     if (lane < j - jb) {
-        a.boundary[(long long)(jb + lane + 1) * D] = keep0;
-        if (D == 2) a.boundary[(long long)(jb + lane + 1) * D + 1] = keep1;
+        a.boundary[(long long)(jb + lane + 1) * 2] = keep0;
+        a.boundary[(long long)(jb + lane + 1) * 2 + 1] = keep1;
     }
     range_end(a, lane, lam0, lam1, oog, bad_slice);
     if (final_out) {
         final_out[0] = lam0;
-        if (D == 2) final_out[1] = lam1;
+        final_out[1] = lam1;
     }
 }
 
@@ -803,7 +793,7 @@ struct PfShared2 {
 };
 
 template <class T>
-__device__ inline void pf2_chain(const ComposeArgs &a, PfShared2 &sh) {
+__device__ inline void pf2_chain(const ComposeArgs &a, PfShared2 &sh, double *final_out) {
 #pragma clang fp contract(off)
     const int lane = int(threadIdx.x) & 63;
     const T *tab0 = static_cast<const T *>(a.tab0);
@@ -910,6 +900,10 @@ __device__ inline void pf2_chain(const ComposeArgs &a, PfShared2 &sh) {
         a.boundary[(long long)(jb + lane + 1) * 2 + 1] = keep1;
     }
     range_end(a, lane, lam0, lam1, oog, bad_slice);
+    if (final_out) {
+        final_out[0] = lam0;
+        final_out[1] = lam1;
+    }
 }
 
 // Helper wave r (1..kPfHelpers) stages slices j_begin + r, j_begin + r + kPfHelpers, ...
@@ -971,7 +965,8 @@ __device__ inline void pf2_helper(const ComposeArgs &a, PfShared2 &sh, int r) {
 }
 
 template <class T>
-__device__ inline void compose_range_staged2(const ComposeArgs &a, PfShared2 &sh) {
+__device__ inline void compose_range_staged2(const ComposeArgs &a, PfShared2 &sh,
+                                             double *final_out = nullptr) {
     const int wave = int(threadIdx.x) >> 6;
     if (threadIdx.x < kPf2Slots) sh.tag[threadIdx.x] = -1;
     if (threadIdx.x == 0) {
@@ -989,7 +984,7 @@ __device__ inline void compose_range_staged2(const ComposeArgs &a, PfShared2 &sh
     __syncthreads();
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
-        pf2_chain<T>(a, sh);
+        pf2_chain<T>(a, sh, final_out);
         if ((threadIdx.x & 63) == 0)
             __hip_atomic_store(&sh.done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else {

@@ -25,7 +25,7 @@ __global__ void compose_kernel(ComposeArgs a) {
     if constexpr (Interp == 3)
         compose_range_lagrange<T>(a);
     else
-        compose_range<T, Interp>(a);
+        compose_range_bilinear<T>(a);
 }
 
 // The 1-D chain with its table windows staged in LDS by helper waves: one
