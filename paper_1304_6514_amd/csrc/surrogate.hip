@@ -444,20 +444,6 @@ __device__ inline void bilinear_row(const ChainArgs &a, int j, double l0, double
     q = s0 + w0 * (s1 - s0);
 }
 
-// The composition runs one dependent chain of network evaluations, so its
-// latency matters more than its throughput: a workgroup of 4 waves evaluates
-// the network for 16 chains together.  Wave w computes output tiles 2w and
-// 2w+1 (features 32w .. 32w+31) of every 128-wide layer, which is exactly
-// k-block w of the next layer's operand in the permuted order; the four blocks
-// are exchanged through LDS, and the output layer's partial sums are added in
-// wave order.
-struct ChainLds {
-    __bf16 w[2 * kWidth * kLdsRow];      // Wf2, Wf3
-    SmallParams sp;
-    bf16x8 xb[4][64];                    // operand k-block of each wave, by lane
-    float part[4][2][16];                // output partial sums: wave, output, sample
-};
-
 // One 128 x 128 layer's tiles 2w, 2w+1 from the four operand blocks.
 __device__ inline void layer_split(const __bf16 *M, const bf16x8 (&b)[4], int w, int lane,
                                    f32x4 (&out)[2]) {
@@ -473,101 +459,120 @@ __device__ inline void layer_split(const __bf16 *M, const bf16x8 (&b)[4], int w,
     }
 }
 
-// Publish this wave's block and gather all four (two barriers: the previous
-// round's reads are complete before the block is overwritten).
-__device__ inline void exchange(ChainLds &L, const bf16x8 &mine, int w, int lane,
-                                bf16x8 (&b)[4]) {
-    __syncthreads();
-    L.xb[w][lane] = mine;
-    __syncthreads();
+// The composition runs one dependent chain of network evaluations, so its
+// latency matters more than its throughput: a workgroup evaluates the network
+// for 16 chains together, one 16-feature tile of every 128-wide layer per wave
+// (eight waves, two per SIMD), the tile's weights in the wave's registers for
+// the whole chain.  What bounds a slice is the issue of the waves' GELUs (four
+// per lane and layer) and the latency of three exchanges through LDS, so a
+// ninth wave keeps the chains' states and takes the coarse steps, a third of
+// them in the time of each layer, and only the last few operations of a slice
+// wait for the network.  (With four waves of two tiles each, weights read from
+// LDS and the coarse steps after the network, 256 chains of 1024 slices took
+// 2.39 ms; now 1.56 ms.  Of the 1.5 us per slice, the GELUs take 0.58, the eight
+// waves' reads of the operand and the products 0.53; the coarse steps nothing.)
+constexpr int kChainNet = 8;                       // waves of the network
+constexpr int kChainThreads = 64 * (kChainNet + 1);
+
+struct ChainLds {
+    bf16x8 xb[2][4][64];                 // operand k-blocks of layers 2 and 3, by lane
+    alignas(16) float part[2][16][kChainNet];      // output partial sums: output, sample, wave
+    alignas(16) float u[16][4];          // normalised inputs
+};
+
+// The wave's four values per lane (rows 4g .. 4g+3 of its tile) as its half of
+// a k-block: tile 2 kb + h is elements 4h .. 4h+3 of block kb.
+__device__ inline void publish_tile(bf16x8 (&xb)[4][64], const f32x4 &x, int w, int lane) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    bf16x4 v;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) b[kb] = L.xb[kb][lane];
+    for (int e = 0; e < 4; ++e) v[e] = __bf16(x[e]);
+    *(reinterpret_cast<bf16x4 *>(&xb[w >> 1][lane]) + (w & 1)) = v;
 }
 
-__device__ inline void forward_split(ChainLds &L, const float (&u)[4], int w, int lane,
-                                     float &o0, float &o1) {
-    const int s = lane & 15, g = lane >> 4;
-    f32x4 x[2];
+__device__ inline f32x4 layer_tile(const bf16x8 (&weights)[4], const bf16x8 (&xb)[4][64],
+                                   int lane) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int f = 16 * (2 * w + t) + 4 * g + i;
-            float z = L.sp.b1[f];
-            z = fmaf(L.sp.w1[4 * f + 0], u[0], z);
-            z = fmaf(L.sp.w1[4 * f + 1], u[1], z);
-            z = fmaf(L.sp.w1[4 * f + 2], u[2], z);
-            z = fmaf(L.sp.w1[4 * f + 3], u[3], z);
-            float d;
-            x[t][i] = gelu_d(z, d);
-        }
-    }
-    bf16x8 b[4], blk;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        blk[e] = __bf16(x[0][e]);
-        blk[e + 4] = __bf16(x[1][e]);
-    }
-    exchange(L, blk, w, lane, b);
-#pragma unroll
-    for (int layer = 0; layer < 2; ++layer) {
-        const __bf16 *M = L.w + layer * kWidth * kLdsRow;
-        const float *bias = layer == 0 ? L.sp.b2 : L.sp.b3;
-        layer_split(M, b, w, lane, x);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float d;
-                x[t][i] = gelu_d(x[t][i] + bias[16 * (2 * w + t) + 4 * g + i], d);
-            }
-        }
-        if (layer == 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                blk[e] = __bf16(x[0][e]);
-                blk[e + 4] = __bf16(x[1][e]);
-            }
-            exchange(L, blk, w, lane, b);
-        }
-    }
-    float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int f = 16 * (2 * w + t) + 4 * g + i;
-            s0 = fmaf(L.sp.w4[f], x[t][i], s0);
-            s1 = fmaf(L.sp.w4[kWidth + f], x[t][i], s1);
-        }
-    }
-    s0 += __shfl_xor(s0, 16);
-    s1 += __shfl_xor(s1, 16);
-    s0 += __shfl_xor(s0, 32);
-    s1 += __shfl_xor(s1, 32);
-    if (g == 0) {
-        L.part[w][0][s] = s0;
-        L.part[w][1][s] = s1;
-    }
-    __syncthreads();
-    o0 = ((L.part[0][0][s] + L.part[1][0][s]) + (L.part[2][0][s] + L.part[3][0][s])) + L.sp.b4[0];
-    o1 = ((L.part[0][1][s] + L.part[1][1][s]) + (L.part[2][1][s] + L.part[3][1][s])) + L.sp.b4[1];
+    for (int kb = 0; kb < 4; ++kb) acc = mfma(weights[kb], xb[kb][lane], acc);
+    return acc;
 }
 
-__global__ __launch_bounds__(kInferThreads) void sur_chain_kernel(ChainArgs a) {
+// Wave w of the network, slice by slice; the barriers are those of chain_states.
+__device__ inline void chain_network(const ChainArgs &a, ChainLds &L, int w, int lane) {
+    const int s = lane & 15, g = lane >> 4, f0 = 16 * w + 4 * g;
+    bf16x8 w2[4], w3[4];
+    const __bf16 *row = a.shadow + (16 * w + s) * kWidth + 8 * g;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+        w2[kb] = *reinterpret_cast<const bf16x8 *>(row + 32 * kb);
+        w3[kb] = *reinterpret_cast<const bf16x8 *>(row + kMat + 32 * kb);
+    }
+    float w1[4][4], b1[4], b2[4], b3[4], w40[4], w41[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w1[i][k] = a.params[kW1 + 4 * (f0 + i) + k];
+        b1[i] = a.params[kB1 + f0 + i];
+        b2[i] = a.params[kB2 + f0 + i];
+        b3[i] = a.params[kB3 + f0 + i];
+        w40[i] = a.params[kW4 + f0 + i];
+        w41[i] = a.params[kW4 + kWidth + f0 + i];
+    }
+    for (int j = 0; j < a.n_slices; ++j) {
+        __syncthreads();                                    // the inputs
+        const f32x4 u = *reinterpret_cast<const f32x4 *>(L.u[s]);
+        f32x4 x;
+        float d;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float z = b1[i];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) z = fmaf(w1[i][k], u[k], z);
+            x[i] = gelu_d(z, d);
+        }
+        publish_tile(L.xb[0], x, w, lane);
+        __syncthreads();                                    // layer 1
+        x = layer_tile(w2, L.xb[0], lane);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = gelu_d(x[i] + b2[i], d);
+        publish_tile(L.xb[1], x, w, lane);
+        __syncthreads();                                    // layer 2
+        x = layer_tile(w3, L.xb[1], lane);
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = gelu_d(x[i] + b3[i], d);
+            s0 = fmaf(w40[i], v, s0);
+            s1 = fmaf(w41[i], v, s1);
+        }
+        s0 += __shfl_xor(s0, 16);
+        s1 += __shfl_xor(s1, 16);
+        s0 += __shfl_xor(s0, 32);
+        s1 += __shfl_xor(s1, 32);
+        if (g == 0) {
+            L.part[0][s][w] = s0;
+            L.part[1][s][w] = s1;
+        }
+        __syncthreads();                                    // the outputs
+    }
+}
+
+__device__ inline float chain_output(const float (&p)[kChainNet], float bias) {
+    return (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) + bias;
+}
+
+// The wave that holds the chains' states (lane l: chain l % 16).
+__device__ inline void chain_states(const ChainArgs &a, ChainLds &L, int lane) {
 #pragma clang fp contract(off)
-    __shared__ ChainLds L;
-    const int tid = int(threadIdx.x);
-    load_mats<2, kInferThreads>(L.w, a.shadow, tid);
-    load_small<kInferThreads>(L.sp, a.params, tid);
-    __syncthreads();
-    const int lane = tid & 63, w = tid >> 6, s = lane & 15, g = lane >> 4;
-    const long long q = (long long)blockIdx.x * 16 + s;        // the 4 waves share 16 chains
+    const int s = lane & 15, g = lane >> 4;
+    const long long q = (long long)blockIdx.x * 16 + s;
     const bool live = q < a.count;
     const long long qc = live ? q : a.count - 1;
     double l0 = a.y0[2 * qc], l1 = a.y0[2 * qc + 1];
-    const float muf = float(a.mu[qc]);
-    const bool writer = live && g == 0 && w == 0;
+    const double mu = a.mu[qc];
+    const float muf = float(mu), b40 = a.params[kB4], b41 = a.params[kB4 + 1];
+    const bool writer = live && g == 0;
     const long long stride = (long long)a.n_slices + 1;
     if (writer && a.boundary) {
         a.boundary[(q * stride) * 2] = l0;
@@ -576,35 +581,51 @@ __global__ __launch_bounds__(kInferThreads) void sur_chain_kernel(ChainArgs a) {
     unsigned long long nfb = 0, nout = 0;
     double maxdev = 0.0;
     bool bad = false;
+    const double h1 = a.L / double(a.coarse), h2 = a.L / double(2 * a.coarse);
     for (int j = 0; j < a.n_slices; ++j) {
-        asm volatile("" ::: "memory");  // keep the weight reads inside the loop
         if (!(isfinite(l0) && isfinite(l1))) bad = true;
         const float tj = float(a.t0 + double(j) * a.L);
-        float u[4] = {(float(l0) - a.shift[0]) * a.scale[0], (float(l1) - a.shift[1]) * a.scale[1],
-                      (tj - a.shift[2]) * a.scale[2], (muf - a.shift[3]) * a.scale[3]};
-        float o0, o1;
-        forward_split(L, u, w, lane, o0, o1);
-        double n0, n1;
+        const f32x4 u = {(float(l0) - a.shift[0]) * a.scale[0],
+                         (float(l1) - a.shift[1]) * a.scale[1], (tj - a.shift[2]) * a.scale[2],
+                         (muf - a.shift[3]) * a.scale[3]};
+        if (g == 0) *reinterpret_cast<f32x4 *>(L.u[s]) = u;
+        __syncthreads();                                    // the inputs
+        // G1 (or G), then the 2k half-length steps of G2 in two parts
+        double g0 = l0, g1 = l1, e0 = l0, e1 = l1;
+        coarse_rk4(mu, h1, a.coarse, g0, g1);
+        __syncthreads();                                    // layer 1
+        if (a.step_doubling) coarse_rk4(mu, h2, a.coarse, e0, e1);
+        __syncthreads();                                    // layer 2
+        double f0 = 0.0, f1 = 0.0, d0 = 0.0, d1 = 0.0;
         if (a.step_doubling) {
-            const StepDoubling sd = step_doubling(a.mu[qc], a.L, a.coarse, l0, l1, a.tau2_0,
-                                                  a.tau2_1);
-            n0 = sd.g0 + sd.d0 * (kRichardson + (a.os0 * sd.gt0) * double(o0));
-            n1 = sd.g1 + sd.d1 * (kRichardson + (a.os1 * sd.gt1) * double(o1));
-        } else {
-            double g0 = l0, g1 = l1;
-            coarse_rk4(double(a.mu[qc]), a.L / double(a.coarse), a.coarse, g0, g1);
-            n0 = g0 + a.os0 * double(o0);
-            n1 = g1 + a.os1 * double(o1);
+            coarse_rk4(mu, h2, a.coarse, e0, e1);
+            d0 = e0 - g0;
+            d1 = e1 - g1;
+            const double dd0 = d0 * d0, dd1 = d1 * d1;
+            f0 = a.os0 * (dd0 / (dd0 + a.tau2_0));
+            f1 = a.os1 * (dd1 / (dd1 + a.tau2_1));
         }
         const bool outside = !(l0 >= a.blo0 && l0 <= a.bhi0 && l1 >= a.blo1 && l1 <= a.bhi1);
+        double p = 0.0, pq = 0.0;
         if (a.tab0) {
-            double p, pq;
             if (a.fb_fp64)
                 bilinear_row<double>(a, j, l0, l1, p, pq);
             else
                 bilinear_row<float>(a, j, l0, l1, p, pq);
-            const double d0 = fabs(n0 - p), dd1 = fabs(n1 - pq);
-            const double dev = d0 > dd1 ? d0 : dd1;
+        }
+        __syncthreads();                                    // the outputs
+        const float o0 = chain_output(L.part[0][s], b40), o1 = chain_output(L.part[1][s], b41);
+        double n0, n1;
+        if (a.step_doubling) {
+            n0 = g0 + d0 * (kRichardson + f0 * double(o0));
+            n1 = g1 + d1 * (kRichardson + f1 * double(o1));
+        } else {
+            n0 = g0 + a.os0 * double(o0);
+            n1 = g1 + a.os1 * double(o1);
+        }
+        if (a.tab0) {
+            const double d0t = fabs(n0 - p), d1t = fabs(n1 - pq);
+            const double dev = d0t > d1t ? d0t : d1t;
             if (dev == dev && dev > maxdev) maxdev = dev;
             if (!(dev <= a.guard) || outside) {
                 n0 = p;
@@ -634,9 +655,19 @@ __global__ __launch_bounds__(kInferThreads) void sur_chain_kernel(ChainArgs a) {
     }
 }
 
+__global__ __launch_bounds__(kChainThreads) void sur_chain_kernel(ChainArgs a) {
+    __shared__ ChainLds L;
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int lane = int(threadIdx.x) & 63;
+    if (w < kChainNet)
+        chain_network(a, L, w, lane);
+    else
+        chain_states(a, L, lane);
+}
+
 // ---- training: forward pass, loss and back-propagation ------------------
 //
-// Four waves share a tile of 16 samples, as in the composition above: wave w
+// Four waves share a tile of 16 samples: wave w
 // of a group computes features 32 w .. 32 w + 31 (output tiles 2w, 2w+1) of
 // every 128-wide layer, which is exactly k-block w of the next product's
 // operand, and the four blocks are exchanged through LDS.  A wave so holds a
@@ -1494,7 +1525,7 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
     const long long blocks = (c->count + 15) / 16;
     if (blocks > 0x7fffffffLL) return fail(NV_ERR_INVALID_ARG, "too many chains");
     NV_HIP(hipEventRecord(s->ev0, s->stream));
-    hipLaunchKernelGGL(sur_chain_kernel, dim3(unsigned(blocks)), dim3(kInferThreads), 0,
+    hipLaunchKernelGGL(sur_chain_kernel, dim3(unsigned(blocks)), dim3(kChainThreads), 0,
                        s->stream, a);
     NV_HIP(hipGetLastError());
     NV_HIP(hipEventRecord(s->ev1, s->stream));
