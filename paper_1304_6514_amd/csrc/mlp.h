@@ -33,22 +33,6 @@ constexpr int kMat = kWidth * kWidth;  // elements of one 128 x 128 matrix
 constexpr int kLdsRow = kWidth + 8;    // padded bf16 row in LDS: 272 bytes, 16-lane reads
                                        // of 16 bytes from 16 rows hit disjoint banks
 
-// Training workspace S: bfloat16 rows of one value per sample of the minibatch.
-constexpr int kRowD = 0;      // 384 rows: dL/dz of layers 1, 2, 3
-constexpr int kRowH = 384;    // 384 rows: bf16 activations a1, a2, a3
-constexpr int kRowXO = 768;   // 16 rows: u0..u3, 1, dL/dout0, dL/dout1, zeros
-constexpr int kRowsS = 784;
-
-// Weight-gradient sums G = A B^T over the minibatch, A and B row blocks of S.
-// Their outputs, concatenated, form one partial vector per split of the sum.
-constexpr int kG_W2 = 0;                    // [128 x 128]  D2 . H1^T
-constexpr int kG_W3 = 16384;                // [128 x 128]  D3 . H2^T
-constexpr int kG_D_XO = 32768;              // [384 x 16]   D . XO^T  (dW1, db1; db2, db3 in column 4)
-constexpr int kG_XO_H3 = 32768 + 384 * 16;  // [16 x 144]   XO . [H3; XO]^T  (dW4, db4)
-constexpr int kGradEntries = kG_XO_H3 + 16 * 144;
-constexpr int kGemmWaveTiles = 16 + 16 + 4 + 5;
-constexpr int kGemmSmallFirst = 32;         // wave tiles of the two small products
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -194,48 +178,10 @@ __device__ inline void load_mats(__bf16 *lds, const __bf16 *src, int tid) {
     }
 }
 
-// Where the training kernel writes a tile's rows: the workspace S (row r,
-// sample n at S[r * ld + n]) at the tile's first sample.  Each lane writes its
-// 32 features of its sample; the row offsets are the same in every lane, so
-// they stay scalar instead of occupying vector registers.  (Routing the stores
-// through an LDS transpose into 16-byte runs was measured slower.)
-struct RowSink {
-    __bf16 *tile;               // S + 16 * tile
-    long long ld;
-};
-
-// Rows row0 + f (f = 0..127) of the tile from the lane's B operands b[kb]
-// (element e of b[kb] is feature 32 kb + perm32(8 g + e)).
-__device__ inline void store_rows(const RowSink &o, int row0, const bf16x8 (&b)[4], int lane) {
-    const int s = lane & 15, g = lane >> 4;
-    __bf16 *col = o.tile + (long long)(4 * g) * o.ld + s;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int f = 32 * kb + (e < 4 ? e : 16 + (e - 4));
-            col[(long long)(row0 + f) * o.ld] = b[kb][e];
-        }
-    }
-}
-
-// The 16 rows starting at row0 from four values per lane (rows 4 g + r).
-__device__ inline void store_rows16(const RowSink &o, int row0, const __bf16 (&v)[4], int lane) {
-    const int s = lane & 15, g = lane >> 4;
-    __bf16 *col = o.tile + (long long)(4 * g) * o.ld + s;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) col[(long long)(row0 + r) * o.ld] = v[r];
-}
-
 // Forward pass of the lane's sample, u = normalised input.  Returns the two
-// outputs (identical in the four lanes that share a sample) and a3.  When
-// Train, also fills the hidden layers' GELU derivatives d1..d3 and stores the
-// bf16 inputs of the two matrix layers (a1, a2) to the workspace rows kRowH
-// and kRowH + 128 through the sink.
-template <bool Train>
+// outputs (identical in the four lanes that share a sample).
 __device__ inline void forward(const SmallParams &sp, const __bf16 *Wf2, const __bf16 *Wf3,
-                               const float (&u)[4], int lane, Layer &d1, Layer &d2, Layer &d3,
-                               Layer &a3, float &o0, float &o1, const RowSink *sink) {
+                               const float (&u)[4], int lane, float &o0, float &o1) {
     const int g = lane >> 4;
     Layer x;
     bf16x8 b[4];
@@ -251,11 +197,9 @@ __device__ inline void forward(const SmallParams &sp, const __bf16 *Wf2, const _
             z = fmaf(sp.w1[4 * f + 3], u[3], z);
             float d;
             x.v[mt][i] = gelu_d(z, d);
-            if (Train) d1.v[mt][i] = d;
         }
     }
     pack(x, b);
-    if (Train) store_rows(*sink, kRowH, b, lane);
     matmul(Wf2, b, x, lane);
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) {
@@ -264,11 +208,9 @@ __device__ inline void forward(const SmallParams &sp, const __bf16 *Wf2, const _
             const float z = x.v[mt][i] + sp.b2[16 * mt + 4 * g + i];
             float d;
             x.v[mt][i] = gelu_d(z, d);
-            if (Train) d2.v[mt][i] = d;
         }
     }
     pack(x, b);
-    if (Train) store_rows(*sink, kRowH + 128, b, lane);
     matmul(Wf3, b, x, lane);
     float s0 = 0.f, s1 = 0.f;
 #pragma unroll
@@ -279,8 +221,6 @@ __device__ inline void forward(const SmallParams &sp, const __bf16 *Wf2, const _
             const float z = x.v[mt][i] + sp.b3[f];
             float d;
             const float a = gelu_d(z, d);
-            if (Train) d3.v[mt][i] = d;
-            a3.v[mt][i] = a;
             s0 = fmaf(sp.w4[f], a, s0);
             s1 = fmaf(sp.w4[kWidth + f], a, s1);
         }

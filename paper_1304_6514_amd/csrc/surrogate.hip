@@ -26,9 +26,20 @@ using namespace nv::mlp;
 namespace {
 
 constexpr int kInferThreads = 256;       // 4 waves
-constexpr int kMaxSplits = 128;          // weight-gradient sums: splits of the minibatch
-constexpr long long kMinSplit = 512;      // samples per split, at least
+constexpr int kMaxSplits = 256;          // training workgroups, each with its own gradient sums
 constexpr long long kMaxBatch = 1LL << 20;
+
+// A workgroup's gradient sums: the flat parameter order, except that W2 and W3
+// are kept as the training waves hold them (four rows of a column per lane, so
+// that the sums leave in 16-byte stores).  Entry e is the gradient of parameter
+// grad_param(e).
+constexpr int kPartRow = (kParams + 63) / 64 * 64;
+__device__ inline int grad_param(int e) {
+    const int base = e >= kW3 ? kW3 : kW2, r = e - base;
+    if (r < 0 || r >= kMat) return e;
+    const int i = r & 3, lane = (r >> 2) & 63, w = (r >> 8) & 7, ct = r >> 11;
+    return base + (16 * w + 4 * (lane >> 4) + i) * kWidth + 16 * ct + (lane & 15);
+}
 
 enum { kModeReduce = 1, kModeAdam = 2 };
 constexpr int kMaxCoarse = 16;
@@ -84,204 +95,12 @@ struct TrainArgs {
     long long ld, start, n;      // minibatch = samples start .. start+n-1
     const float *params;
     const __bf16 *shadow;        // Wf2, Wf3, Wb2, Wb3 (permuted bf16)
-    __bf16 *S;                   // workspace, kRowsS rows of ldS
-    long long ldS;
-    float *loss_part;            // one sum per 16 samples
+    float *part;                 // [workgroups][kPartRow] gradient sums
+    float *loss_part;            // [workgroups]
     float shift[4], scale[4];
     float inv_n;
     int weighted;                // targets are rho_0, rho_1, w_0, w_1: e = w out - rho
 };
-
-// Weight-gradient sums G = A B^T over samples k0..k1-1 of the minibatch, A and
-// B row blocks of S; blockIdx.y of the launch is the split of the sum.  In the
-// small products each wave computes a 32 x 32 block (wave tiles
-// kGemmSmallFirst.. of kGemmWaveTiles: D1 . XO^T, giving dW1 and db1, and
-// XO . [H3; XO]^T, giving dW4 and db4; db2 and db3 are row sums that the
-// 128 x 128 products form from the rows they stage anyway).
-struct GemmArgs {
-    const __bf16 *S;
-    long long ldS, n, k_per_split;
-    float *part;                 // [splits][kGradEntries]
-};
-
-__device__ inline void grad_small(const GemmArgs &a, int bx) {
-    const int lane = int(threadIdx.x) & 63, r = lane & 15, g = lane >> 4;
-    const int wt = kGemmSmallFirst + bx * 4 + (int(threadIdx.x) >> 6);
-    if (wt >= kGemmWaveTiles) return;
-    int a_row, b_row, M, N, out, t, tiles_n;
-    if (wt < 16) {
-        a_row = kRowD + 128; b_row = kRowH; M = N = 128; out = kG_W2; t = wt; tiles_n = 4;
-    } else if (wt < 32) {
-        a_row = kRowD + 256; b_row = kRowH + 128; M = N = 128; out = kG_W3; t = wt - 16;
-        tiles_n = 4;
-    } else if (wt < 36) {
-        a_row = kRowD; b_row = kRowXO; M = 128; N = 16; out = kG_D_XO; t = wt - 32; tiles_n = 1;
-    } else {
-        a_row = kRowXO; b_row = kRowH + 256; M = 16; N = 144; out = kG_XO_H3; t = wt - 36;
-        tiles_n = 5;
-    }
-    const int mt0 = 2 * (t / tiles_n), nt0 = 2 * (t % tiles_n);
-    const bool m1 = mt0 + 1 < M / 16, n1 = nt0 + 1 < N / 16;
-    const long long k0 = (long long)blockIdx.y * a.k_per_split;
-    const long long k1 = std::min(k0 + a.k_per_split, a.n);
-    const __bf16 *pa0 = a.S + (long long)(a_row + 16 * mt0 + r) * a.ldS + 8 * g;
-    const __bf16 *pa1 = pa0 + 16 * a.ldS;
-    const __bf16 *pb0 = a.S + (long long)(b_row + 16 * nt0 + r) * a.ldS + 8 * g;
-    const __bf16 *pb1 = pb0 + 16 * a.ldS;
-    f32x4 c00 = {0.f, 0.f, 0.f, 0.f}, c01 = c00, c10 = c00, c11 = c00;
-    const bf16x8 zero = {};
-    constexpr int U = 4;                         // k-steps of 32 samples per iteration
-    long long k = k0;
-    for (; k + 32 * U <= k1; k += 32 * U) {
-        bf16x8 A0[U], A1[U], B0[U], B1[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            A0[u] = *reinterpret_cast<const bf16x8 *>(pa0 + k + 32 * u);
-            B0[u] = *reinterpret_cast<const bf16x8 *>(pb0 + k + 32 * u);
-            A1[u] = m1 ? *reinterpret_cast<const bf16x8 *>(pa1 + k + 32 * u) : zero;
-            B1[u] = n1 ? *reinterpret_cast<const bf16x8 *>(pb1 + k + 32 * u) : zero;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            c00 = mfma(A0[u], B0[u], c00);
-            if (n1) c01 = mfma(A0[u], B1[u], c01);
-            if (m1) c10 = mfma(A1[u], B0[u], c10);
-            if (m1 && n1) c11 = mfma(A1[u], B1[u], c11);
-        }
-    }
-    for (; k < k1; k += 32) {
-        const bool ok = k + 8 * g < k1;          // the minibatch ends on a multiple of 16
-        const bf16x8 A0 = ok ? *reinterpret_cast<const bf16x8 *>(pa0 + k) : zero;
-        const bf16x8 B0 = ok ? *reinterpret_cast<const bf16x8 *>(pb0 + k) : zero;
-        const bf16x8 A1 = (ok && m1) ? *reinterpret_cast<const bf16x8 *>(pa1 + k) : zero;
-        const bf16x8 B1 = (ok && n1) ? *reinterpret_cast<const bf16x8 *>(pb1 + k) : zero;
-        c00 = mfma(A0, B0, c00);
-        if (n1) c01 = mfma(A0, B1, c01);
-        if (m1) c10 = mfma(A1, B0, c10);
-        if (m1 && n1) c11 = mfma(A1, B1, c11);
-    }
-    float *P = a.part + (long long)blockIdx.y * kGradEntries + out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row0 = 16 * mt0 + 4 * g + i, col0 = 16 * nt0 + r;
-        P[row0 * N + col0] = c00[i];
-        if (n1) P[row0 * N + col0 + 16] = c01[i];
-        if (m1) P[(row0 + 16) * N + col0] = c10[i];
-        if (m1 && n1) P[(row0 + 16) * N + col0 + 16] = c11[i];
-    }
-}
-
-// The two 128 x 128 weight gradients, dW2 = D2 . H1^T and dW3 = D3 . H2^T
-// (job 0, 1), over samples k0..k1-1 (blockIdx.y = split), and the
-// bias gradients db2, db3, the row sums of D2 and D3.  The workgroup stages
-// each 32-sample step of its 128 A rows and 128 B rows in LDS once (rows
-// padded to 80 bytes: 16 lanes reading 16 bytes from 16 rows hit disjoint
-// banks) and each wave multiplies a 64 x 64 quadrant; two threads per A row
-// add its 32 staged values into FP32 row sums; the next step's rows are loaded
-// into registers while the current one is multiplied.
-constexpr int kGmPad = 40;                 // bf16 per LDS row
-
-struct GradMatLds {
-    __bf16 As[128 * kGmPad], Bs[128 * kGmPad];
-};
-
-__device__ inline void grad_mat(const GemmArgs &a, GradMatLds &L, int job) {
-    __bf16 *As = L.As, *Bs = L.Bs;
-    const int a_row = job == 0 ? kRowD + 128 : kRowD + 256;
-    const int b_row = job == 0 ? kRowH : kRowH + 128;
-    const int out = job == 0 ? kG_W2 : kG_W3;
-    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 15, g = lane >> 4, mh = wave >> 1, nh = wave & 1;
-    const long long k0 = (long long)blockIdx.y * a.k_per_split;
-    const long long k1 = std::min(k0 + a.k_per_split, a.n);
-    // this thread's share of a step: chunks tid and tid + 256 of 4 x 128 16-byte chunks
-    const int row0 = tid >> 2, part0 = tid & 3, row1 = (tid + 256) >> 2, part1 = (tid + 256) & 3;
-    const bf16x8 zero = {};
-    auto load = [&](long long k, bf16x8 &a0, bf16x8 &a1, bf16x8 &b0, bf16x8 &b1) {
-        const bool ok0 = k + 8 * part0 < k1, ok1 = k + 8 * part1 < k1;
-        a0 = ok0 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(a_row + row0) * a.ldS + k +
-                                                     8 * part0) : zero;
-        a1 = ok1 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(a_row + row1) * a.ldS + k +
-                                                     8 * part1) : zero;
-        b0 = ok0 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(b_row + row0) * a.ldS + k +
-                                                     8 * part0) : zero;
-        b1 = ok1 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(b_row + row1) * a.ldS + k +
-                                                     8 * part1) : zero;
-    };
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // row sum of A row tid / 2, samples 16 (tid & 1) .. + 15 of every step
-    const int srow = tid >> 1, shalf = tid & 1;
-    float bsum = 0.0f;
-    bf16x8 ra0, ra1, rb0, rb1;
-    if (k0 < k1) load(k0, ra0, ra1, rb0, rb1);
-    for (long long k = k0; k < k1; k += 32) {
-        *reinterpret_cast<bf16x8 *>(As + row0 * kGmPad + 8 * part0) = ra0;
-        *reinterpret_cast<bf16x8 *>(As + row1 * kGmPad + 8 * part1) = ra1;
-        *reinterpret_cast<bf16x8 *>(Bs + row0 * kGmPad + 8 * part0) = rb0;
-        *reinterpret_cast<bf16x8 *>(Bs + row1 * kGmPad + 8 * part1) = rb1;
-        __syncthreads();
-        if (k + 32 < k1) load(k + 32, ra0, ra1, rb0, rb1);
-        bf16x8 fa[4], fb[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            fa[t] = *reinterpret_cast<const bf16x8 *>(As + (64 * mh + 16 * t + r) * kGmPad + 8 * g);
-            fb[t] = *reinterpret_cast<const bf16x8 *>(Bs + (64 * nh + 16 * t + r) * kGmPad + 8 * g);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(As + srow * kGmPad + 16 * shalf + 8 * h);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bsum += float(v[e]);
-        }
-        __syncthreads();
-    }
-    // the two halves of a row are adjacent lanes
-    const float rsum = bsum + __shfl_xor(bsum, 1);
-    if (shalf == 0)
-        a.part[(long long)blockIdx.y * kGradEntries + kG_D_XO + (128 * (job + 1) + srow) * 16 + 4] =
-            rsum;
-    float *P = a.part + (long long)blockIdx.y * kGradEntries + out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                P[(64 * mh + 16 * i + 4 * g + e) * 128 + 64 * nh + 16 * j + r] = acc[i][j][e];
-}
-
-// All weight-gradient sums of one step in one launch: blockIdx.x 0 and 1 are
-// the two 128 x 128 products (the long-running workgroups, dispatched first),
-// the others the small products; blockIdx.y is the split of the sum.
-constexpr int kGradSmallBlocks = (kGemmWaveTiles - kGemmSmallFirst + 3) / 4;
-
-__global__ __launch_bounds__(256) void sur_grad_kernel(GemmArgs a) {
-    __shared__ GradMatLds L;
-    if (blockIdx.x < 2)
-        grad_mat(a, L, int(blockIdx.x));
-    else
-        grad_small(a, int(blockIdx.x) - 2);
-}
-
-// Offset of parameter p's gradient in the partial vector.
-__device__ inline int grad_source(int p) {
-    if (p < kB1) return kG_D_XO + (p >> 2) * 16 + (p & 3);                 // W1[f][k]
-    if (p < kW2) return kG_D_XO + (p - kB1) * 16 + 4;                      // b1
-    if (p < kB2) return kG_W2 + (p - kW2);                                 // W2
-    if (p < kW3) return kG_D_XO + (128 + p - kB2) * 16 + 4;                // b2
-    if (p < kB3) return kG_W3 + (p - kW3);                                 // W3
-    if (p < kW4) return kG_D_XO + (256 + p - kB3) * 16 + 4;                // b3
-    if (p < kB4) return kG_XO_H3 + (5 + ((p - kW4) >> 7)) * 144 + ((p - kW4) & 127);  // W4
-    return kG_XO_H3 + (5 + (p - kB4)) * 144 + 128 + 4;                     // b4
-}
 
 struct UpdateArgs {
     float *params, *m, *v, *grad;
@@ -290,30 +109,28 @@ struct UpdateArgs {
     int splits, mode;
     float lr, beta1, beta2, eps, inv_bc1, inv_bc2;
     const float *loss_part;
-    long long n_loss;
     float inv_n;
     float *loss_out;
 };
 
-// 64 parameters per workgroup: wave q (q = 0..3) sums splits 32q .. 32q+31 of
-// each parameter's gradient in split order (all 32 loads in flight at once);
-// wave 0 then combines the four sums as ((s0 + s1) + (s2 + s3)), takes the Adam
+// 64 parameters per workgroup: wave q (q = 0..7) sums the training workgroups
+// 32q .. 32q+31's shares of each parameter's gradient in order (all 32 loads in
+// flight at once); wave 0 then combines the eight sums as a tree, takes the Adam
 // step and refreshes the permuted bf16 copies.
 constexpr int kUpdateParams = 64;
-constexpr int kUpdateGroups = 4;
+constexpr int kUpdateGroups = 8;
+constexpr int kUpdateThreads = 64 * kUpdateGroups;
 
-__global__ __launch_bounds__(256) void sur_update_kernel(UpdateArgs a) {
+__global__ __launch_bounds__(kUpdateThreads) void sur_update_kernel(UpdateArgs a) {
     static_assert(kMaxSplits % kUpdateGroups == 0, "splits per group");
     constexpr int kPer = kMaxSplits / kUpdateGroups;
     if (int(blockIdx.x) == int(gridDim.x) - 1 && a.loss_out) {
-        // the extra last workgroup: the minibatch loss from the per-tile sums
-        __shared__ float red[256];
-        float s = 0.0f;
-#pragma unroll 16
-        for (long long i = threadIdx.x; i < a.n_loss; i += 256) s += a.loss_part[i];
-        red[threadIdx.x] = s;
+        // the extra last workgroup: the minibatch loss from the workgroups' sums
+        __shared__ float red[kMaxSplits];
+        if (int(threadIdx.x) < kMaxSplits)
+            red[threadIdx.x] = int(threadIdx.x) < a.splits ? a.loss_part[threadIdx.x] : 0.0f;
         __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
+        for (int w = kMaxSplits / 2; w > 0; w >>= 1) {
             if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
             __syncthreads();
         }
@@ -322,15 +139,22 @@ __global__ __launch_bounds__(256) void sur_update_kernel(UpdateArgs a) {
     }
     __shared__ float sums[kUpdateGroups][kUpdateParams];
     const int pl = int(threadIdx.x) & (kUpdateParams - 1), grp = int(threadIdx.x) >> 6;
-    const int p = int(blockIdx.x) * kUpdateParams + pl;
-    const int pc = p < kParams ? p : kParams - 1;
+    const int e = int(blockIdx.x) * kUpdateParams + pl;
+    const int ec = e < kParams ? e : kParams - 1, p = grad_param(ec);
+    float th = 0.0f, m0 = 0.0f, v0 = 0.0f;
+    if (grp == 0) {
+        th = a.params[p];
+        if (a.mode & kModeAdam) {
+            m0 = a.m[p];
+            v0 = a.v[p];
+        }
+    }
     if (a.mode & kModeReduce) {
-        const int src = grad_source(pc);
         float part[kPer];
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int sp = grp * kPer + u;
-            part[u] = a.part[(long long)(sp < a.splits ? sp : a.splits - 1) * kGradEntries + src];
+            part[u] = a.part[(sp < a.splits ? sp : a.splits - 1) * kPartRow + ec];
         }
         float gs = 0.0f;
 #pragma unroll
@@ -339,14 +163,14 @@ __global__ __launch_bounds__(256) void sur_update_kernel(UpdateArgs a) {
         sums[grp][pl] = gs;
     }
     __syncthreads();
-    if (grp != 0 || p >= kParams) return;
-    float th = a.params[p];
+    if (grp != 0 || e >= kParams) return;
     if (a.mode & kModeReduce) {
-        const float gsum = (sums[0][pl] + sums[1][pl]) + (sums[2][pl] + sums[3][pl]);
+        const float gsum = ((sums[0][pl] + sums[1][pl]) + (sums[2][pl] + sums[3][pl])) +
+                           ((sums[4][pl] + sums[5][pl]) + (sums[6][pl] + sums[7][pl]));
         a.grad[p] = gsum;
         if (a.mode & kModeAdam) {
-            const float m = a.beta1 * a.m[p] + (1.0f - a.beta1) * gsum;
-            const float v = a.beta2 * a.v[p] + (1.0f - a.beta2) * gsum * gsum;
+            const float m = a.beta1 * m0 + (1.0f - a.beta1) * gsum;
+            const float v = a.beta2 * v0 + (1.0f - a.beta2) * gsum * gsum;
             a.m[p] = m;
             a.v[p] = v;
             th -= a.lr * (m * a.inv_bc1) / (sqrtf(v * a.inv_bc2) + a.eps);
@@ -390,9 +214,8 @@ __global__ __launch_bounds__(kInferThreads) void sur_forward_kernel(ForwardArgs 
     float u[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) u[k] = (a.x[k * a.n + nc] - a.shift[k]) * a.scale[k];
-    Layer d1, d2, d3, a3;
     float o0, o1;
-    forward<false>(L.sp, L.w, L.w + kWidth * kLdsRow, u, lane, d1, d2, d3, a3, o0, o1, nullptr);
+    forward(L.sp, L.w, L.w + kWidth * kLdsRow, u, lane, o0, o1);
     if (n < a.n && g == 0) {
         a.out[n] = o0;
         a.out[a.n + n] = o1;
@@ -442,21 +265,6 @@ __device__ inline void bilinear_row(const ChainArgs &a, int j, double l0, double
     const double s0 = q00 + w1 * (q01 - q00), s1 = q10 + w1 * (q11 - q10);
     p = r0 + w0 * (r1 - r0);
     q = s0 + w0 * (s1 - s0);
-}
-
-// One 128 x 128 layer's tiles 2w, 2w+1 from the four operand blocks.
-__device__ inline void layer_split(const __bf16 *M, const bf16x8 (&b)[4], int w, int lane,
-                                   f32x4 (&out)[2]) {
-    const int r = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const __bf16 *row = M + (16 * (2 * w + t) + r) * kLdsRow + 8 * g;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-            acc = mfma(*reinterpret_cast<const bf16x8 *>(row + 32 * kb), b[kb], acc);
-        out[t] = acc;
-    }
 }
 
 // The composition runs one dependent chain of network evaluations, so its
@@ -665,258 +473,322 @@ __global__ __launch_bounds__(kChainThreads) void sur_chain_kernel(ChainArgs a) {
         chain_states(a, L, lane);
 }
 
-// ---- training: forward pass, loss and back-propagation ------------------
+// ---- training: forward pass, loss, back-propagation and gradient sums -----
 //
-// Four waves share a tile of 16 samples: wave w
-// of a group computes features 32 w .. 32 w + 31 (output tiles 2w, 2w+1) of
-// every 128-wide layer, which is exactly k-block w of the next product's
-// operand, and the four blocks are exchanged through LDS.  A wave so holds a
-// quarter of each layer's values and GELU derivatives, which lets two groups
-// (two waves per SIMD) share the workgroup's one copy of the four bf16
-// weight matrices in LDS: the second group's instructions fill the first's
-// latency.  Each product's output element is summed over the same k-blocks in
-// the same order as a whole-layer product; the network's two outputs are the
-// four waves' partial sums added in wave order.
-constexpr int kTrainGroups = 3;                        // tiles in flight per workgroup
-constexpr int kTrainThreads = 256 * kTrainGroups;
-// Inputs and targets of kStageTiles tiles are staged in LDS before the tiles
-// are processed: a global load inside the tile loop would have to wait for
-// every store of the previous tile (the memory counter is in order).
-constexpr int kStageTiles = 8;
+// One launch does the whole pass over a minibatch and leaves one share of every
+// gradient per workgroup; nothing per sample goes to memory.  (With the bf16
+// activations and errors of every sample written to a workspace and the
+// gradient products formed from it by a second launch, a step of 65,536
+// samples took 44 + 24 us; it takes 54 us, 4.4 us per pass of 8,192 samples on
+// the 256 compute units, 7 us to load the weights and start and 12 us to write
+// the workgroups' 35 MB of gradient sums.  Eight training steps: 645 -> 515 us.)
+//
+// Eight waves per workgroup, wave w owning features 16w .. 16w+15 of every
+// 128-wide layer: its rows of the four bf16 weight matrices (64 registers) and
+// of the two 128 x 128 gradients (64 registers) stay in registers for the whole
+// launch, so LDS holds only activations.  A pass takes 32 samples.  Layers are
+// computed samples x features (act . W^T), so that lane l holds feature 16w + c,
+// c = l % 16, of samples 16t + 4g + i (t = 0, 1; i = 0..3; g = l / 16).  Those
+// eight values, packed, are the lane's share of an operand whose k index runs
+// over the 32 samples (in the order 8g + 4t + i, the same for both operands):
+// exactly what the gradient products D . H^T take, the errors' from the wave's
+// own registers and the activations' from what every wave publishes as it is.
+// The next layer's operand runs over features instead; it goes through LDS as
+// rows of samples, neighbouring lanes pairing their values so that every store
+// is a whole dword.  Six barriers per pass.  Layer 1 and the outputs stay FP32
+// and use the FP32 matrix instruction, which takes its four products in order
+// as a chain of fused multiply-adds.
+//
+// What bounds it: issue of vector instructions (the GELU and its derivative, 16
+// per value, are about half of them), then the reads of the operands from LDS, 64 KB for each of the six products and pass, and the
+// latency of the exchange for the outputs.  Products of the gradients delayed
+// into the next pass's vector phases, and the output weights in registers,
+// measured the same.  A third of a step is fixed: weights in, sums out, update.
+constexpr int kTrainWaves = 8;
+constexpr int kTrainThreads = 64 * kTrainWaves;
+constexpr int kTrainPass = 32;                          // samples per pass
+constexpr int kActRow = kWidth + 8;                     // bf16 per sample row in LDS: 16 rows
+                                                        // of 16-byte reads hit disjoint banks
 
 struct TrainLds {
-    __bf16 w[4 * kWidth * kLdsRow];         // Wf2, Wf3, Wb2, Wb3
-    SmallParams sp;
-    float xs[4 * kStageTiles * 16];
-    float ts[4 * kStageTiles * 16];         // targets and weights (1 when unweighted)
-    bf16x8 xb[kTrainGroups][4][64];         // per group: each wave's operand k-block
-    float part[kTrainGroups][4][2][16];     // per group: the outputs' partial sums
+    __bf16 act[4][kTrainPass][kActRow];     // operands over features: h1, h2, D3, D2
+    bf16x8 act_t[2][kTrainWaves][64];       // operands over samples: h1, h2
+    float h3[kWidth][kTrainPass + 4];       // layer 3 by features, FP32
+    float w4[kOut][kWidth];
+    float part[4][kOut][kTrainPass];        // the outputs over 32 features each
+    float dout[kTrainWaves][2][kTrainPass]; // dL/dout, a copy per wave, and the same in
+    __bf16 dout_t[kTrainWaves][2][kTrainPass];  // bf16 as an operand over samples
+    // per pass, double buffered: normalised inputs, targets and weights (1 when
+    // unweighted); the inputs and a row of ones as an operand over samples
+    float u[2][4][kTrainPass], t[2][4][kTrainPass];
+    __bf16 u_t[2][5][kTrainPass];
 };
-static_assert(sizeof(TrainLds) <= 160 * 1024, "the training kernel's LDS exceeds 160 KiB");
 
-// Publish this wave's block to its group and gather all four (two barriers:
-// the group's previous reads are complete before the block is overwritten).
-__device__ inline void train_exchange(TrainLds &L, int gi, const bf16x8 &mine, int w, int lane,
-                                      bf16x8 (&b)[4]) {
-    __syncthreads();
-    L.xb[gi][w][lane] = mine;
-    __syncthreads();
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) b[kb] = L.xb[gi][kb][lane];
-}
-
-__device__ inline bf16x8 pack_block(const f32x4 (&x)[2]) {
-    bf16x8 blk;
+// The lane's eight values (t, i) as bf16, in operand order.
+__device__ inline bf16x8 pack8(const f32x4 (&x)[2]) {
+    bf16x8 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        blk[e] = __bf16(x[0][e]);
-        blk[e + 4] = __bf16(x[1][e]);
+        v[e] = __bf16(x[0][e]);
+        v[e + 4] = __bf16(x[1][e]);
     }
-    return blk;
+    return v;
 }
 
-// Rows row0 + 32 w + (features of the block) of the tile: element e of the
-// block is feature 4 g + e (e < 4) or 16 + 4 g + (e - 4) of the wave's 32.
-__device__ inline void store_block(const RowSink &o, int row0, int w, const bf16x8 &blk,
-                                   int lane) {
-    const int s = lane & 15, g = lane >> 4;
-    __bf16 *col = o.tile + (long long)(row0 + 32 * w + 4 * g) * o.ld + s;
+// The lane's eight values (feature c of samples 16t + 4g + i) to the rows of
+// their samples: lanes c and c ^ 1 exchange their packed pairs of samples, the
+// even lane stores both features of the first sample of each pair, the odd lane
+// of the second.  at: the lane's dword for sample 4g + (c & 1); select: which
+// halves the lane's dword is made of.
+__device__ inline void publish_rows(unsigned *at, const bf16x8 &v, unsigned select) {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 mine = __builtin_bit_cast(u32x4, v);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) col[(long long)(e < 4 ? e : 12 + e) * o.ld] = blk[e];
-}
-
-// One tile (16 samples, staged at li0 .. li0 + 15 of the chunk) by wave w of
-// group gi.  When !live the group computes and stores nothing but passes the
-// same barriers (every barrier below is outside the `live` conditions, so all
-// waves of the workgroup meet the same sequence of them).
-__device__ inline void train_tile(const TrainArgs &a, TrainLds &L, long long tile, int li0,
-                                  bool live, int gi, int w, int lane) {
-    const int s = lane & 15, g = lane >> 4, li = li0 + s;
-    const __bf16 *Wf2 = L.w, *Wf3 = L.w + kWidth * kLdsRow;
-    const __bf16 *Wb2 = L.w + 2 * kWidth * kLdsRow, *Wb3 = L.w + 3 * kWidth * kLdsRow;
-    const RowSink sink{a.S + tile * 16, a.ldS};
-    float u[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) u[k] = (L.xs[k * kStageTiles * 16 + li] - a.shift[k]) * a.scale[k];
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 x[2] = {zero, zero}, d1[2] = {zero, zero}, d2[2] = {zero, zero}, d3[2] = {zero, zero};
-    bf16x8 b[4], blk = {};
-    // layer 1 (FP32): the wave's 32 features
-    if (live) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 16 * (2 * w + t) + 4 * g + i;
-                float z = L.sp.b1[f];
-                z = fmaf(L.sp.w1[4 * f + 0], u[0], z);
-                z = fmaf(L.sp.w1[4 * f + 1], u[1], z);
-                z = fmaf(L.sp.w1[4 * f + 2], u[2], z);
-                z = fmaf(L.sp.w1[4 * f + 3], u[3], z);
-                float d;
-                x[t][i] = gelu_d(z, d);
-                d1[t][i] = d;
-            }
-        }
-        blk = pack_block(x);
-        store_block(sink, kRowH, w, blk, lane);
-    }
-    train_exchange(L, gi, blk, w, lane, b);
-    // layers 2 and 3 on the matrix cores
-#pragma unroll
-    for (int layer = 0; layer < 2; ++layer) {
-        if (live) {
-            layer_split(layer == 0 ? Wf2 : Wf3, b, w, lane, x);
-            const float *bias = layer == 0 ? L.sp.b2 : L.sp.b3;
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float d;
-                    x[t][i] = gelu_d(x[t][i] + bias[16 * (2 * w + t) + 4 * g + i], d);
-                    if (layer == 0)
-                        d2[t][i] = d;
-                    else
-                        d3[t][i] = d;
-                }
-            }
-            blk = pack_block(x);
-            store_block(sink, kRowH + 128 * (layer + 1), w, blk, lane);
-        }
-        if (layer == 0) train_exchange(L, gi, blk, w, lane, b);
-    }
-    // the two outputs: the wave's partial sums over its 32 features of a3
-    if (live) {
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 16 * (2 * w + t) + 4 * g + i;
-                s0 = fmaf(L.sp.w4[f], x[t][i], s0);
-                s1 = fmaf(L.sp.w4[kWidth + f], x[t][i], s1);
-            }
-        }
-        s0 += __shfl_xor(s0, 16);
-        s1 += __shfl_xor(s1, 16);
-        s0 += __shfl_xor(s0, 32);
-        s1 += __shfl_xor(s1, 32);
-        if (g == 0) {
-            L.part[gi][w][0][s] = s0;
-            L.part[gi][w][1][s] = s1;
-        }
-    }
-    __syncthreads();
-    float e0 = 0.f, e1 = 0.f, dout0 = 0.f, dout1 = 0.f;
-    if (live) {
-        const float o0 = ((L.part[gi][0][0][s] + L.part[gi][1][0][s]) +
-                          (L.part[gi][2][0][s] + L.part[gi][3][0][s])) + L.sp.b4[0];
-        const float o1 = ((L.part[gi][0][1][s] + L.part[gi][1][1][s]) +
-                          (L.part[gi][2][1][s] + L.part[gi][3][1][s])) + L.sp.b4[1];
-        // the error of the sample, e = w out - target (w = 1 unweighted, where
-        // this is out - target to the bit), and dL/dout = 2 e w / n.  Rows 2 and 3
-        // of the staged targets hold the weights, 1 when unweighted: an
-        // unconditional read keeps the kernel within its register budget.
-        const float t0 = L.ts[li], t1 = L.ts[kStageTiles * 16 + li];
-        const float w0 = L.ts[2 * kStageTiles * 16 + li], w1 = L.ts[3 * kStageTiles * 16 + li];
-        e0 = w0 * o0 - t0;
-        e1 = w1 * o1 - t1;
-        dout0 = 2.0f * e0 * w0 * a.inv_n;
-        dout1 = 2.0f * e1 * w1 * a.inv_n;
-        // back-propagation: dL/dz3 = (W4^T dout) * gelu'(z3) for the wave's features
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 16 * (2 * w + t) + 4 * g + i;
-                x[t][i] = (L.sp.w4[f] * dout0 + L.sp.w4[kWidth + f] * dout1) * d3[t][i];
-            }
-        }
-        blk = pack_block(x);
-        store_block(sink, kRowD + 256, w, blk, lane);
-    }
-    train_exchange(L, gi, blk, w, lane, b);
-    if (live) {
-        layer_split(Wb3, b, w, lane, x);                  // W3^T dL/dz3
-#pragma unroll
-        for (int t = 0; t < 2; ++t) x[t] *= d2[t];
-        blk = pack_block(x);
-        store_block(sink, kRowD + 128, w, blk, lane);
-    }
-    train_exchange(L, gi, blk, w, lane, b);
-    if (live) {
-        layer_split(Wb2, b, w, lane, x);                  // W2^T dL/dz2
-#pragma unroll
-        for (int t = 0; t < 2; ++t) x[t] *= d1[t];
-        blk = pack_block(x);
-        store_block(sink, kRowD, w, blk, lane);
-    }
-
-    if (live && w == 0) {
-        // rows of XO: group 0 writes u0..u3, group 1 writes 1, dout0, dout1, 0,
-        // groups 2 and 3 the zero rows
-        __bf16 xo[4];
-        if (g == 0) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) xo[r] = __bf16(u[r]);
-        } else if (g == 1) {
-            xo[0] = __bf16(1.0f);
-            xo[1] = __bf16(dout0);
-            xo[2] = __bf16(dout1);
-            xo[3] = __bf16(0.0f);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) xo[r] = __bf16(0.0f);
-        }
-        store_rows16(sink, kRowXO, xo, lane);
-        float sq = g == 0 ? e0 * e0 + e1 * e1 : 0.0f;
-        sq += __shfl_xor(sq, 1);
-        sq += __shfl_xor(sq, 2);
-        sq += __shfl_xor(sq, 4);
-        sq += __shfl_xor(sq, 8);
-        if (lane == 0) a.loss_part[tile] = sq;
+    for (int d = 0; d < 4; ++d) {               // samples 16 (d / 2) + 4g + 2 (d % 2), + 1
+        const unsigned other = unsigned(__builtin_amdgcn_update_dpp(
+            0, int(mine[d]), 0xB1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true));
+        at[(16 * (d >> 1) + 2 * (d & 1)) * (kActRow / 2)] =
+            __builtin_amdgcn_perm(other, mine[d], select);
     }
 }
 
-__global__ __launch_bounds__(kTrainThreads) void sur_train_kernel(TrainArgs a) {
+// Pins a value where it is computed: the compiler otherwise moves the GELU
+// derivative's last operation to its use, behind the following barriers, and
+// holds its three inputs in registers instead of the one result.
+__device__ inline float computed(float v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// One layer of the pass for the wave's features: act . M^T.
+__device__ inline void layer_rows(const __bf16 (&act)[kTrainPass][kActRow], const bf16x8 (&m)[4],
+                                  int lane, f32x4 (&out)[2]) {
+    const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+            acc = mfma(*reinterpret_cast<const bf16x8 *>(&act[16 * t + r][32 * kb + 8 * g]), m[kb],
+                       acc);
+        out[t] = acc;
+    }
+}
+
+__global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a) {
     __shared__ TrainLds L;
-    const int tid = int(threadIdx.x);
-    load_mats<4, kTrainThreads>(L.w, a.shadow, tid);
-    load_small<kTrainThreads>(L.sp, a.params, tid);
-    const int lane = tid & 63;
-    const int gi = __builtin_amdgcn_readfirstlane(tid >> 8);        // group
-    const int w = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave in the group
-    const long long tiles = a.n / 16;
-    // workgroup b owns the contiguous tiles [b * per, (b+1) * per), staged in
-    // chunks of kStageTiles; group gi takes tiles c0 + gi, c0 + gi + G, ...
-    const long long per = (tiles + gridDim.x - 1) / gridDim.x;
-    const long long tb = (long long)blockIdx.x * per;
-    const long long te = tb + per < tiles ? tb + per : tiles;
-    for (long long c0 = tb; c0 < te; c0 += kStageTiles) {
-        const long long c1 = c0 + kStageTiles < te ? c0 + kStageTiles : te;
-        const int cn = int(c1 - c0) * 16;
-        __syncthreads();                              // the previous chunk is consumed
-        for (int i = tid; i < cn; i += kTrainThreads) {
-            const long long src = a.start + c0 * 16 + i;
+    const int tid = int(threadIdx.x), lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4, f = 16 * w + c;
+    // inputs and targets of a pass: wave w reads row w of (x, t), one value per
+    // lane of its first half; without weights rows 6 and 7 are ones
+    const bool ones = w >= 6 && !a.weighted;
+    const float *row = (w < 4 ? a.x + w * a.ld : a.t + (ones ? 0 : (w - 4) * a.ld)) + a.start;
+    const float shift = a.shift[w & 3], scale = a.scale[w & 3];
+    const int count = int(a.n);
+    const auto fetch = [&](int pass) {
+        const int n = kTrainPass * pass + (lane & 31);
+        return ones ? 1.0f : row[n < count ? n : count - 1];
+    };
+    const float first = fetch(int(blockIdx.x));
+    const float w1 = a.params[kW1 + 4 * f + g];
+    const float b1 = a.params[kB1 + f], b2 = a.params[kB2 + f], b3 = a.params[kB3 + f];
+    const float w40 = a.params[kW4 + f], w41 = a.params[kW4 + kWidth + f];
+    // the wave's rows of Wf2, Wf3, Wb2, Wb3
+    bf16x8 wf2[4], wf3[4], wb2[4], wb3[4];
+    {
+        const __bf16 *row = a.shadow + f * kWidth + 8 * g;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) L.xs[k * kStageTiles * 16 + i] = a.x[k * a.ld + src];
-            L.ts[i] = a.t[src];
-            L.ts[kStageTiles * 16 + i] = a.t[a.ld + src];
-            L.ts[2 * kStageTiles * 16 + i] = a.weighted ? a.t[2 * a.ld + src] : 1.0f;
-            L.ts[3 * kStageTiles * 16 + i] = a.weighted ? a.t[3 * a.ld + src] : 1.0f;
+        for (int kb = 0; kb < 4; ++kb) {
+            wf2[kb] = *reinterpret_cast<const bf16x8 *>(row + 32 * kb);
+            wf3[kb] = *reinterpret_cast<const bf16x8 *>(row + kMat + 32 * kb);
+            wb2[kb] = *reinterpret_cast<const bf16x8 *>(row + 2 * kMat + 32 * kb);
+            wb3[kb] = *reinterpret_cast<const bf16x8 *>(row + 3 * kMat + 32 * kb);
+        }
+    }
+    const int my_out = c >> 3;                  // the output and the sample whose error the
+                                                // lane forms
+    const int my_sample = 16 * ((c >> 2) & 1) + 4 * g + (c & 3);
+    // where the lane's dwords go in the sample rows: the position of feature f in
+    // the permuted order of the weights' columns, rounded down to a pair
+    const int pos = 32 * (w >> 1) + perm32_inv(16 * (w & 1) + c);
+    const int at = ((4 * g + (c & 1)) * kActRow + (pos & ~1)) / 2;
+    const unsigned select = c & 1 ? 0x03020706u : 0x05040100u;
+
+    // gradient sums, rows features 16w + 4g + i: W2, W3 (column tiles); gx1 the
+    // errors of layer 1 times (u0..u3, 1), gx2 and gx3 likewise, where only the
+    // ones matter; gw4 the activations of layer 3 times dL/dout (column c & 1)
+    f32x4 gw2[8], gw3[8], gx1 = {0.f, 0.f, 0.f, 0.f}, gx2 = gx1, gx3 = gx1, gw4 = gx1;
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct) gw2[ct] = gw3[ct] = gx1;
+    float gb4 = 0.f, loss = 0.f;
+    const float b4 = a.params[kB4 + my_out];
+
+    const auto stage = [&](int buf, float v) {
+        if (lane >= 32) return;
+        if (w < 4) {
+            const float u = (v - shift) * scale;
+            L.u[buf][w][lane] = u;
+            L.u_t[buf][w][perm32_inv(lane)] = __bf16(u);
+        } else {
+            L.t[buf][w - 4][lane] = v;
+        }
+    };
+    const int passes = (count + kTrainPass - 1) / kTrainPass;
+    if (w == 4) L.u_t[lane >> 5][4][lane & 31] = __bf16(1.0f);
+    if (g < kOut) L.w4[g][f] = g == 0 ? w40 : w41;
+    stage(0, first);
+    __syncthreads();
+    int buf = 0;
+    for (int pass = int(blockIdx.x); pass < passes; pass += int(gridDim.x), buf ^= 1) {
+        const bool more = pass + int(gridDim.x) < passes;
+        float coming = 0.f;
+        if (more) coming = fetch(pass + int(gridDim.x));
+        f32x4 x[2], d1[2], d2[2], d3[2];
+        // layer 1 (FP32, all four inputs in one instruction)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const f32x4 z = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                L.u[buf][g][16 * t + c], w1, f32x4{b1, b1, b1, b1}, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d;
+                x[t][i] = gelu_d(z[i], d);
+                d1[t][i] = computed(d);
+            }
+        }
+        bf16x8 h = pack8(x);
+        L.act_t[0][w][lane] = h;
+        publish_rows(reinterpret_cast<unsigned *>(&L.act[0][0][0]) + at, h, select);
+        __syncthreads();
+        // layers 2 and 3
+        layer_rows(L.act[0], wf2, lane, x);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d;
+                x[t][i] = gelu_d(x[t][i] + b2, d);
+                d2[t][i] = computed(d);
+            }
+        h = pack8(x);
+        L.act_t[1][w][lane] = h;
+        publish_rows(reinterpret_cast<unsigned *>(&L.act[1][0][0]) + at, h, select);
+        __syncthreads();
+        layer_rows(L.act[1], wf3, lane, x);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d;
+                x[t][i] = gelu_d(x[t][i] + b3, d);
+                d3[t][i] = computed(d);
+            }
+        const bf16x8 h3 = pack8(x);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            *reinterpret_cast<f32x4 *>(&L.h3[16 * w + c][16 * t + 4 * g]) = x[t];
+        __syncthreads();
+        // the outputs of 16 samples over 32 features (FP32): the features 4q .. 4q+3
+        // of two tiles in a chain, then the four q; columns c & 1 are the outputs
+        {
+            const int p = w >> 1, t = w & 1;
+            f32x4 s[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int fk = 32 * p + 16 * k + 4 * q + g;
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(L.h3[fk][16 * t + c], L.w4[c & 1][fk],
+                                                               acc, 0, 0, 0);
+                }
+                s[q] = acc;
+            }
+            const f32x4 sum = (s[0] + s[1]) + (s[2] + s[3]);
+            if (c < kOut) *reinterpret_cast<f32x4 *>(&L.part[p][c][16 * t + 4 * g]) = sum;
         }
         __syncthreads();
-        // every group runs the same number of rounds (the barriers inside a
-        // tile are the workgroup's); a group past the chunk's end only passes
-        // the barriers
-        const int rounds = (int(c1 - c0) + kTrainGroups - 1) / kTrainGroups;
-        for (int r = 0; r < rounds; ++r) {
-            asm volatile("" ::: "memory");            // keep the weight reads inside the loop
-            const long long tile = c0 + r * kTrainGroups + gi;
-            const bool live = tile < c1;
-            const long long tt = live ? tile : c0;
-            train_tile(a, L, tt, int(tt - c0) * 16, live, gi, w, lane);
+        if (more) stage(buf ^ 1, coming);
+        // the output and its error, one per lane: e = w out - target (w = 1
+        // unweighted, where this is out - target to the bit), dL/dout = 2 e w / n;
+        // samples past the minibatch's end have no error
+        {
+            const auto part = [&](int p) { return L.part[p][my_out][my_sample]; };
+            const float out = ((part(0) + part(1)) + (part(2) + part(3))) + b4;
+            const float wgt = L.t[buf][2 + my_out][my_sample];
+            float e = wgt * out - L.t[buf][my_out][my_sample];
+            if (pass * kTrainPass + my_sample >= count) e = 0.f;
+            const float dout = 2.0f * e * wgt * a.inv_n;
+            const __bf16 rounded = __bf16(dout);
+            L.dout[w][my_out][my_sample] = dout;
+            L.dout_t[w][my_out][perm32_inv(my_sample)] = rounded;
+            loss += e * e;
+            gb4 += float(rounded);
         }
+        // back-propagation: dL/dz3 = (W4^T dout) * gelu'(z3)
+        gw4 = mfma(h3, *reinterpret_cast<const bf16x8 *>(&L.dout_t[w][c & 1][8 * g]), gw4);
+        const bf16x8 *ut = reinterpret_cast<const bf16x8 *>(&L.u_t[buf][c < 4 ? c : 4][8 * g]);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const f32x4 o0 = *reinterpret_cast<const f32x4 *>(&L.dout[w][0][16 * t + 4 * g]);
+            const f32x4 o1 = *reinterpret_cast<const f32x4 *>(&L.dout[w][1][16 * t + 4 * g]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[t][i] = fmaf(w40, o0[i], w41 * o1[i]) * d3[t][i];
+        }
+        bf16x8 err = pack8(x);
+        publish_rows(reinterpret_cast<unsigned *>(&L.act[2][0][0]) + at, err, select);
+        gx3 = mfma(err, *ut, gx3);
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) {
+            gw3[ct] = mfma(err, L.act_t[1][ct][lane], gw3[ct]);
+        }
+        __syncthreads();
+        layer_rows(L.act[2], wb3, lane, x);                 // W3^T dL/dz3
+#pragma unroll
+        for (int t = 0; t < 2; ++t) x[t] *= d2[t];
+        err = pack8(x);
+        publish_rows(reinterpret_cast<unsigned *>(&L.act[3][0][0]) + at, err, select);
+        gx2 = mfma(err, *ut, gx2);
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) {
+            gw2[ct] = mfma(err, L.act_t[0][ct][lane], gw2[ct]);
+        }
+        __syncthreads();
+        layer_rows(L.act[3], wb2, lane, x);                 // W2^T dL/dz2
+#pragma unroll
+        for (int t = 0; t < 2; ++t) x[t] *= d1[t];
+        gx1 = mfma(pack8(x), *ut, gx1);
+    }
+
+    // the workgroup's share of every gradient
+    float *P = a.part + blockIdx.x * kPartRow;
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct) {
+        const int at2 = ((ct * 8 + w) * 64 + lane) * 4;
+        *reinterpret_cast<f32x4 *>(P + kW2 + at2) = gw2[ct];
+        *reinterpret_cast<f32x4 *>(P + kW3 + at2) = gw3[ct];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int fi = 16 * w + 4 * g + i;
+        if (c < 4) P[kW1 + 4 * fi + c] = gx1[i];
+        if (c < 2) P[kW4 + kWidth * c + fi] = gw4[i];
+        if (c == 4) {
+            P[kB1 + fi] = gx1[i];
+            P[kB2 + fi] = gx2[i];
+            P[kB3 + fi] = gx3[i];
+        }
+    }
+    if (w == 0) {
+        // lanes 0 .. 7 of a row hold output 0, the others output 1
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            if (m != 8) gb4 += __shfl_xor(gb4, m);
+            loss += __shfl_xor(loss, m);
+        }
+        if (g == 0 && (c & 7) == 0) P[kB4 + my_out] = gb4;
+        if (lane == 0) a.loss_part[blockIdx.x] = loss;
     }
 }
 
@@ -1065,7 +937,7 @@ struct nv_sur {
     long long max_batch = 0;
     char *mem = nullptr;         // one device allocation
     float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
-    __bf16 *shadow = nullptr, *S = nullptr;
+    __bf16 *shadow = nullptr;
     float *part = nullptr, *loss_part = nullptr, *loss = nullptr;
     unsigned long long *stats = nullptr;
     int *error = nullptr;
@@ -1095,18 +967,13 @@ nv_status refresh_shadow(nv_sur *s) {
     u.shadow = s->shadow;
     u.mode = 0;
     hipLaunchKernelGGL(sur_update_kernel, dim3((kParams + kUpdateParams - 1) / kUpdateParams),
-                       dim3(256), 0, s->stream, u);
+                       dim3(kUpdateThreads), 0, s->stream, u);
     NV_HIP(hipGetLastError());
     return NV_OK;
 }
 
-long long k_per_split(long long n) {
-    long long k = std::max(kMinSplit, (n + kMaxSplits - 1) / kMaxSplits);
-    return (k + 31) / 32 * 32;
-}
-
-// One minibatch: forward and back-propagation, gradient sums, then the update
-// kernel (mode: reduce only, or reduce and Adam step).
+// One minibatch: forward and back-propagation with the gradient sums, then the
+// update kernel (mode: reduce only, or reduce and Adam step).
 nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, long long start,
                     long long n, int mode, float lr, float b1, float b2, float eps,
                     float *loss_out) {
@@ -1118,27 +985,14 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
     ta.n = n;
     ta.params = s->params;
     ta.shadow = s->shadow;
-    ta.S = s->S;
-    ta.ldS = s->max_batch;
+    ta.part = s->part;
     ta.loss_part = s->loss_part;
     fill_norm(s, ta.shift, ta.scale);
     ta.inv_n = float(1.0 / double(n));
     ta.weighted = s->cfg.correction == NV_SUR_STEP_DOUBLING;
-    const long long tiles = n / 16;
-    const int wpb = kTrainThreads / 64;                        // waves per workgroup
-    const int blocks = int(std::min<long long>((tiles + wpb - 1) / wpb, s->n_cu));
+    const long long passes = (n + kTrainPass - 1) / kTrainPass;
+    const int blocks = int(std::min<long long>(passes, std::min(s->n_cu, kMaxSplits)));
     hipLaunchKernelGGL(sur_train_kernel, dim3(blocks), dim3(kTrainThreads), 0, s->stream, ta);
-    NV_HIP(hipGetLastError());
-
-    GemmArgs ga{};
-    ga.S = s->S;
-    ga.ldS = s->max_batch;
-    ga.n = n;
-    ga.k_per_split = k_per_split(n);
-    ga.part = s->part;
-    const int splits = int((n + ga.k_per_split - 1) / ga.k_per_split);
-    hipLaunchKernelGGL(sur_grad_kernel, dim3(2 + kGradSmallBlocks, splits), dim3(256), 0,
-                       s->stream, ga);
     NV_HIP(hipGetLastError());
 
     UpdateArgs ua{};
@@ -1148,7 +1002,7 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
     ua.grad = s->grad;
     ua.shadow = s->shadow;
     ua.part = s->part;
-    ua.splits = splits;
+    ua.splits = blocks;
     ua.mode = mode;
     if (mode & kModeAdam) {
         const long long t = ++s->adam_t;
@@ -1160,13 +1014,12 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
         ua.inv_bc2 = float(1.0 / (1.0 - std::pow(double(b2), double(t))));
     }
     ua.loss_part = s->loss_part;
-    ua.n_loss = tiles;
     ua.inv_n = ta.inv_n;
     ua.loss_out = loss_out;
     // one workgroup per 64 parameters, plus one for the loss
     hipLaunchKernelGGL(sur_update_kernel,
                        dim3((kParams + kUpdateParams - 1) / kUpdateParams + (ua.loss_out ? 1 : 0)),
-                       dim3(256), 0, s->stream, ua);
+                       dim3(kUpdateThreads), 0, s->stream, ua);
     NV_HIP(hipGetLastError());
     return NV_OK;
 }
@@ -1224,12 +1077,11 @@ NV_API nv_status nv_sur_create(const nv_sur_config *cfg, nv_sur **out) try {
     const size_t o_v = off;      off = align256(off + kParams * sizeof(float));
     const size_t o_grad = off;   off = align256(off + kParams * sizeof(float));
     const size_t o_shadow = off; off = align256(off + 4 * kMat * sizeof(__bf16));
-    const size_t o_part = off;   off = align256(off + size_t(kMaxSplits) * kGradEntries * 4);
-    const size_t o_lp = off;     off = align256(off + size_t(mb / 16) * sizeof(float));
+    const size_t o_part = off;   off = align256(off + size_t(kMaxSplits) * kPartRow * 4);
+    const size_t o_lp = off;     off = align256(off + kMaxSplits * sizeof(float));
     const size_t o_loss = off;   off = align256(off + sizeof(float));
     const size_t o_stats = off;  off = align256(off + 4 * sizeof(unsigned long long));
     const size_t o_err = off;    off = align256(off + sizeof(int));
-    const size_t o_S = off;      off = align256(off + size_t(kRowsS) * size_t(mb) * 2);
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&s->mem), off);
     if (e != hipSuccess) {
         delete s;
@@ -1245,8 +1097,7 @@ NV_API nv_status nv_sur_create(const nv_sur_config *cfg, nv_sur **out) try {
     s->loss = reinterpret_cast<float *>(s->mem + o_loss);
     s->stats = reinterpret_cast<unsigned long long *>(s->mem + o_stats);
     s->error = reinterpret_cast<int *>(s->mem + o_err);
-    s->S = reinterpret_cast<__bf16 *>(s->mem + o_S);
-    e = hipMemsetAsync(s->mem, 0, o_S, s->stream);
+    e = hipMemsetAsync(s->mem, 0, off, s->stream);
     if (e == hipSuccess) e = hipEventCreate(&s->ev0);
     if (e == hipSuccess) e = hipEventCreate(&s->ev1);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
