@@ -52,7 +52,7 @@ typedef struct nv_lin nv_lin;
 
 /* Create / destroy.  stream: hipStream_t of every kernel (NULL = null
  * stream).  Device memory is allocated by nv_lin_build and kept for builds of
- * the same or smaller size.  Errors: INVALID_ARG, HIP. */
+ * the same or smaller size, and so is up to 8 MB of pinned host memory.  Errors: INVALID_ARG, HIP. */
 NV_API nv_status nv_lin_create(void *stream, nv_lin **out);
 NV_API nv_status nv_lin_destroy(nv_lin *lin);
 
