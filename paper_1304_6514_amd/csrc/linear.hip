@@ -450,8 +450,8 @@ const LinChainTable lin_chain;
 // the product, k = 0 .. 4 KP - 1 in steps of four, each A fragment of G
 // multiplied with the CB 16-column blocks of states), then c_j added.
 // Lambda_j lives in LDS, double buffered (rows k >= M are zero), one barrier
-// per slice; every wave holds the A fragments of its rows of G_{j+1} in
-// registers while it computes slice j.  Every workgroup reads all N tables, so
+// per slice; every wave holds the A fragments of its rows of G_j in registers
+// and reloads them with those of G_{j+1} as it uses them.  Every workgroup reads all N tables, so
 // the tables' traffic from the caches is (Q / 16 CB) x N x M (M + 1) doubles:
 // CB = 2 halves it for large Q.
 //
@@ -467,7 +467,19 @@ struct ManyArgs {
     int *bad;                   // first map whose state is beyond the limit (atomic min)
     long long Q;
     int groups;                 // workgroups of one block of maps
+    int blocks;                 // blocks of maps
 };
+
+// Workgroups of consecutive numbers run on the kXcds dies in turn, each with an
+// L2 of its own, while the column groups of one block of maps all read the
+// block's tables: block b's workgroups get numbers that are b modulo kXcds (the
+// last row of blocks is filled up with workgroups that return at once).  With
+// the groups of a block next to each other every table came from memory once
+// per group: the products of 1024 maps of 99 points 98 -> 91 us.
+constexpr int kXcds = 8;
+constexpr long long many_rows(long long blocks) {
+    return blocks == 1 ? 1 : (blocks + kXcds - 1) / kXcds * kXcds;
+}
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -480,8 +492,10 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     const int tid = int(threadIdx.x), lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.lv.M, Ms = lin_stride(M), per = Ms * (M + 1);
-    // workgroup = column group + groups x block of maps
-    const int block = int(blockIdx.x / unsigned(a.groups)), group = int(blockIdx.x % unsigned(a.groups));
+    const unsigned spread = a.blocks == 1 ? 1 : kXcds, turn = blockIdx.x / spread;
+    const int block = int(turn / unsigned(a.groups) * spread + blockIdx.x % spread);
+    const int group = int(turn % unsigned(a.groups));
+    if (block >= a.blocks) return;
     const LevelRange rg(a.lv, block);
     const bool product = a.product != nullptr;
     // the maps run through: all of a whole level; of a product all but the
@@ -528,79 +542,84 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
         with_c[cb] = !product || q == M;
         states[cb] = live[cb] && a.boundary ? a.boundary + q * span : nullptr;
     }
-    // the A fragments and the c values of a slice, loaded unconditionally from
+    // The A fragments and the c values of a slice, loaded unconditionally from
     // clamped (in-block) addresses, with no select after the load (which would
     // wait for it): a column k >= M meets the zero row k of Lambda, a row
-    // >= M of the product is never stored.  Two register sets in turn, so that
-    // a slice's operands were loaded during the previous slice and nothing
-    // waits for the prefetch.  (A non-finite table value in column M - 1 thus
-    // also reaches the padded terms; it makes its row non-finite in the exact
-    // sum as well.)
-    double ga[KP], gb[KP], ca[4], cb4[4];
-#define NV_LIN_LOAD(g, cv, j)                                                            \
-    do {                                                                                 \
-        const double *Tj_ = T + (long long)(j) * per;                                    \
-        const int ar_ = arow < M ? arow : M - 1;                                         \
-        _Pragma("unroll") for (int kk = 0; kk < KP; ++kk) {                              \
-            const int k_ = 4 * kk + kq;                                                  \
-            g[kk] = Tj_[(k_ < M ? k_ : M - 1) * Ms + ar_];                               \
-        }                                                                                \
-        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                  \
-            const int r_ = 16 * w + 4 * i + kq;                                          \
-            cv[i] = Tj_[Ms * M + (r_ < M ? r_ : M - 1)];                                 \
-        }                                                                                \
-    } while (0)
-    // one slice: the product on the matrix cores (even and odd k-steps in two
-    // accumulators per column block), c added, the new states to LDS (and the
-    // boundary), barrier
-#define NV_LIN_SLICE(g, cv, j)                                                           \
-    do {                                                                                 \
-        if (active) {                                                                    \
-            v4d acc[CB], acc1[CB];                                                       \
-            _Pragma("unroll") for (int cb = 0; cb < CB; ++cb) {                          \
-                acc[cb] = v4d{0.0, 0.0, 0.0, 0.0};                                       \
-                acc1[cb] = v4d{0.0, 0.0, 0.0, 0.0};                                      \
-            }                                                                            \
-            _Pragma("unroll") for (int kk = 0; kk < KP; ++kk) {                          \
-                _Pragma("unroll") for (int cb = 0; cb < CB; ++cb) {                      \
-                    const double b_ = lam[cur][4 * kk + kq][16 * cb + col];              \
-                    if (kk % 2 == 0)                                                     \
-                        acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[kk], b_, acc[cb],   \
-                                                                       0, 0, 0);         \
-                    else                                                                 \
-                        acc1[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[kk], b_, acc1[cb], \
-                                                                        0, 0, 0);        \
-                }                                                                        \
-            }                                                                            \
-            _Pragma("unroll") for (int cb = 0; cb < CB; ++cb) {                          \
-                const v4d s_ = acc[cb] + acc1[cb];                                       \
-                _Pragma("unroll") for (int i = 0; i < 4; ++i) {                          \
-                    const int r = 16 * w + 4 * i + kq;                                   \
-                    const double v = (with_c[cb] ? cv[i] : 0.0) + s_[i];                 \
-                    if (r < M) {                                                         \
-                        lam[cur ^ 1][r][16 * cb + col] = v;                              \
-                        if (states[cb])                                                  \
-                            states[cb][level_slice(a.lv, rg.first, (j) + 1) * M + r] = v;    \
-                        if (live[cb] && !(fabs(v) <= a.lv.largest) && (j) < bad) bad = (j);  \
-                    }                                                                    \
-                }                                                                        \
-            }                                                                            \
-        }                                                                                \
-        __syncthreads();                                                                 \
-        cur ^= 1;                                                                        \
-    } while (0)
-    int cur = 0;
-    if (active && N > 0) NV_LIN_LOAD(ga, ca, 0);
-    __syncthreads();
-    for (int j = 0; j < N; j += 2) {
-        if (active) NV_LIN_LOAD(gb, cb4, j + 1 < N ? j + 1 : N - 1);
-        NV_LIN_SLICE(ga, ca, j);
-        if (j + 1 >= N) break;
-        if (active) NV_LIN_LOAD(ga, ca, j + 2 < N ? j + 2 : N - 1);
-        NV_LIN_SLICE(gb, cb4, j + 1);
+    // >= M of the product is never stored.  (A non-finite table value in column
+    // M - 1 thus also reaches the padded terms; it makes its row non-finite in
+    // the exact sum as well.)  Each fragment is loaded for the next slice as soon
+    // as its product is issued, into the same registers: the loads go out between
+    // the products instead of ahead of them, and two workgroups fit a CU (at most
+    // 128 registers instead of 224).  1024 maps of 99 points: products of the
+    // first level 91 -> 71 us, 4096 chains 199 -> 169 us.  A slice takes 6,700
+    // clocks of which the matrix cores are busy for 3,200 (two waves per SIMD);
+    // the rest is the sums' way through LDS and the barrier.
+    double g[KP], cv[4];
+    const int ar = arow < M ? arow : M - 1;
+    // byte offsets, so that a load takes a scalar base and one register
+    const unsigned at = 8 * unsigned(kq * Ms + ar);
+    const int k_last = 4 * (KP - 1) + kq;
+    const unsigned at_last = 8 * unsigned((k_last < M ? k_last : M - 1) * Ms + ar);
+    unsigned at_c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 16 * w + 4 * i + kq;
+        at_c[i] = 8 * unsigned(Ms * M + (r < M ? r : M - 1));
     }
-#undef NV_LIN_LOAD
-#undef NV_LIN_SLICE
+    const auto from = [](const double *base, unsigned bytes) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + bytes);
+    };
+    const auto load = [&](const double *Tj, int kk) {
+        return kk < KP - 1 ? from(Tj + 4 * kk * Ms, at) : from(Tj, at_last);
+    };
+    if (active && N > 0) {
+#pragma unroll
+        for (int kk = 0; kk < KP; ++kk) g[kk] = load(T, kk);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cv[i] = from(T, at_c[i]);
+    }
+    int cur = 0;
+    __syncthreads();
+    for (int j = 0; j < N; ++j) {
+        if (active) {
+            const double *next = T + (long long)(j + 1 < N ? j + 1 : N - 1) * per;
+            // the product on the matrix cores (even and odd k-steps in two
+            // accumulators per column block), c added, the new states to LDS (and
+            // the boundary), barrier
+            v4d acc[CB], acc1[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[cb] = acc1[cb] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int kk = 0; kk < KP; ++kk) {
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    const double b = lam[cur][4 * kk + kq][16 * cb + col];
+                    v4d &sum = kk % 2 == 0 ? acc[cb] : acc1[cb];
+                    sum = __builtin_amdgcn_mfma_f64_16x16x4f64(g[kk], b, sum, 0, 0, 0);
+                }
+                g[kk] = load(next, kk);
+            }
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const v4d s = acc[cb] + acc1[cb];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 16 * w + 4 * i + kq;
+                    const double v = (with_c[cb] ? cv[i] : 0.0) + s[i];
+                    if (r < M) {
+                        lam[cur ^ 1][r][16 * cb + col] = v;
+                        if (states[cb])
+                            states[cb][level_slice(a.lv, rg.first, j + 1) * M + r] = v;
+                        if (live[cb] && !(fabs(v) <= a.lv.largest) && j < bad) bad = j;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) cv[i] = from(next, at_c[i]);
+        }
+        __syncthreads();
+        cur ^= 1;
+    }
     if (product) {
         // a column beyond the limit becomes NaN, so that a state formed with it
         // is reported
@@ -629,27 +648,28 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
 
 // With enough chains for two workgroups of two column blocks on every CU, a
 // workgroup carries two blocks that share its table reads; fewer chains keep
-// one block per workgroup, for more workgroups (measured at M = 99, N = 1024:
-// 16,384 chains 9.1 -> 7.4 ms paired, 4096 chains 2.5 -> 3.7 ms).  Two blocks
-// need more registers: up to KP = 29 (M <= 116) the kernel holds them without
-// spilling.
-constexpr int kManyPairMaxKP = 29;
+// one block per workgroup, for more workgroups (measured at M = 99, 32 slices:
+// 16,384 chains 318 -> 281 us paired).  Two blocks need more registers: up to
+// KP = 26 (M <= 104) at most 128, with which two workgroups still fit a CU
+// (beyond, at M = 116, 48 slices, 20,000 chains: 712 us, 740 us paired).
+constexpr int kManyPairMaxKP = 26;
 
 template <int KP>
 void lin_launch_many(ManyArgs a, long long pair_from, hipStream_t st) {
     const long long Q = a.product ? a.lv.M + 1 : a.Q;
     const long long blocks = a.lv.whole ? 1 : (a.lv.maps + kBlock - 1) / kBlock;
+    a.blocks = int(blocks);
     if constexpr (KP <= kManyPairMaxKP) {
         if (!a.product && Q * blocks >= pair_from && Q > 16) {
             a.groups = int((Q + 31) / 32);
-            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), dim3(unsigned(a.groups * blocks)),
+            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), dim3(unsigned(a.groups * many_rows(blocks))),
                                dim3(512), 0, st, a);
             return;
         }
     }
     a.groups = int((Q + 15) / 16);
-    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), dim3(unsigned(a.groups * blocks)), dim3(512), 0,
-                       st, a);
+    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), dim3(unsigned(a.groups * many_rows(blocks))),
+                       dim3(512), 0, st, a);
 }
 
 using ManyLaunch = void (*)(ManyArgs, long long, hipStream_t);
@@ -1055,7 +1075,7 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     int bad = init;
     // by blocks (if one launch can number all its workgroups); then, should a
     // state be beyond what that serves, slice by slice
-    const long long most = ((count + 15) / 16) * ((l->N + kBlock - 1LL) / kBlock);
+    const long long most = ((count + 15) / 16) * many_rows((l->N + kBlock - 1LL) / kBlock);
     for (int levels = boundary_dev && most > 0x7fffffffLL ? 0 : l->levels;; levels = 0) {
         if (levels > 0)
             NV_HIP(launch_products(l));

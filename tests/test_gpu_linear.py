@@ -326,3 +326,25 @@ def test_blocked_chains_beyond_their_range_run_slice_by_slice(lin):
     assert st == nv.NV_ERR_NONFINITE and "slice 0" in nv.nv_last_error()
     yT = yT.cpu().numpy()
     assert not np.all(np.isfinite(yT[17])) and np.all(np.isfinite(np.delete(yT, 17, 0)))
+
+
+def test_results_beyond_the_pinned_staging_are_the_same(lin):
+    """60,000 slices of 20 points: 9.6 MB of boundary states, more than the library
+    stages in pinned memory, copied straight to the caller's arrays.  Every state
+    follows from the one before by its slice's table: |lambda_{j+1} - (c_j + G_j
+    lambda_j)| is at most two summation errors, 2 gamma_22 (|c| + |G| |lambda|),
+    widened by the blocked chains' bound on a state (row sums of |G| at most 1:
+    the same again per level of products, six levels)."""
+    w = HeatWorkload("long", 20, 1e-4, 60000, T=6.0)
+    say("heat M=20 N=60000")
+    lin.build(w)
+    y0 = np.sin(np.pi * np.arange(1, 21) / 21)
+    st, yT, b = lin.compose(y0)
+    st2, yT2, _ = lin.compose(y0, want_boundary=False)
+    assert st == st2 == nv.NV_OK
+    assert np.array_equal(yT, b[-1]) and np.array_equal(yT, yT2) and np.array_equal(b[0], y0)
+    G, c = lin.tables()
+    nxt = c + np.matmul(G, b[:-1, :, None])[:, :, 0]
+    g = 22 * U64
+    size = np.abs(c) + np.matmul(np.abs(G), np.abs(b[:-1, :, None]))[:, :, 0]
+    assert np.all(np.abs(b[1:] - nxt) <= 14 * g * np.max(size, axis=1, keepdims=True))
