@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 using nv::fail;
@@ -269,56 +270,95 @@ __device__ inline void bilinear_row(const ChainArgs &a, int j, double l0, double
 
 // The composition runs one dependent chain of network evaluations, so its
 // latency matters more than its throughput: a workgroup evaluates the network
-// for 16 chains together, one 16-feature tile of every 128-wide layer per wave
-// (eight waves, two per SIMD), the tile's weights in the wave's registers for
-// the whole chain.  What bounds a slice is the issue of the waves' GELUs (four
-// per lane and layer) and the latency of three exchanges through LDS, so a
+// for up to 16 chains together, one 16-feature tile of every 128-wide layer per
+// wave (eight waves, two per SIMD), the tile's weights in the wave's registers for
+// the whole chain.  What bounds a slice is the issue of the waves' GELUs (up to
+// four per lane and layer) and the latency of three exchanges through LDS, so a
 // ninth wave keeps the chains' states and takes the coarse steps, a third of
 // them in the time of each layer, and only the last few operations of a slice
 // wait for the network.  (With four waves of two tiles each, weights read from
-// LDS and the coarse steps after the network, 256 chains of 1024 slices took
+// LDS and the coarse steps after the network, 16 chains of 1024 slices took
 // 2.39 ms; now 1.56 ms.  Of the 1.5 us per slice, the GELUs take 0.58, the eight
 // waves' reads of the operand and the products 0.53; the coarse steps nothing.)
 constexpr int kChainNet = 8;                       // waves of the network
 constexpr int kChainThreads = 64 * (kChainNet + 1);
 
+
+// With C < 16 chains per workgroup (4 or 8) the products' 16 columns hold every
+// chain 16 / C times, and of a lane's four rows each copy takes its own C / 4
+// values through the GELU.  Few chains thus spread over more CUs, and each CU
+// issues a half or a quarter of the GELUs: 1.52 us per slice with 16 chains in a
+// workgroup, 1.14 with 8, 0.96 with 4.  (The matrix products and the reads of
+// their operand stay the same; two accumulators, or the sums over the lane
+// groups by permlane swaps, were no faster.)
+template <int C>
 struct ChainLds {
-    bf16x8 xb[2][4][64];                 // operand k-blocks of layers 2 and 3, by lane
-    alignas(16) float part[2][16][kChainNet];      // output partial sums: output, sample, wave
-    alignas(16) float u[16][4];          // normalised inputs
+    bf16x8 xb[2][4][4 * C];              // operand k-blocks of layers 2 and 3: [g][chain]
+    alignas(16) float part[2][C][kChainNet];       // output partial sums: output, chain, wave
+    alignas(16) float u[C][4];           // normalised inputs
 };
 
-// The wave's four values per lane (rows 4g .. 4g+3 of its tile) as its half of
-// a k-block: tile 2 kb + h is elements 4h .. 4h+3 of block kb.
-__device__ inline void publish_tile(bf16x8 (&xb)[4][64], const f32x4 &x, int w, int lane) {
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    bf16x4 v;
+// The wave's C / 4 values per lane, rows 4g + first .. of its tile, as part of a
+// k-block: tile 2 kb + h is elements 4h .. 4h+3 of block kb.
+template <int C>
+__device__ inline void publish_tile(bf16x8 (&xb)[4][4 * C], const float (&x)[C / 4], int w, int at,
+                                    int first) {
+    typedef __bf16 values __attribute__((ext_vector_type(C / 4)));
+    values v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = __bf16(x[e]);
-    *(reinterpret_cast<bf16x4 *>(&xb[w >> 1][lane]) + (w & 1)) = v;
+    for (int e = 0; e < C / 4; ++e) v[e] = __bf16(x[e]);
+    *reinterpret_cast<values *>(reinterpret_cast<__bf16 *>(&xb[w >> 1][at]) + 4 * (w & 1) + first) =
+        v;
 }
 
-__device__ inline f32x4 layer_tile(const bf16x8 (&weights)[4], const bf16x8 (&xb)[4][64],
-                                   int lane) {
+// The lane's own C / 4 values of a layer's products.
+template <int C>
+__device__ inline void layer_tile(const bf16x8 (&weights)[4], const bf16x8 (&xb)[4][4 * C], int at,
+                                  int copy, float (&x)[C / 4]) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) acc = mfma(weights[kb], xb[kb][lane], acc);
-    return acc;
+    for (int kb = 0; kb < 4; ++kb) acc = mfma(weights[kb], xb[kb][at], acc);
+    if constexpr (C == 16) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = acc[v];
+    } else if constexpr (C == 8) {
+#pragma unroll
+        for (int v = 0; v < 2; ++v) x[v] = copy ? acc[2 + v] : acc[v];
+    } else {
+        const float lo = copy & 1 ? acc[1] : acc[0], hi = copy & 1 ? acc[3] : acc[2];
+        x[0] = copy & 2 ? hi : lo;
+    }
+}
+
+// Sum over the 16 / C copies of a chain and over the lane groups g.
+template <int C>
+__device__ inline float chain_sum(float v) {
+    const auto rotated = [](float x, auto ctrl) {
+        return __uint_as_float(unsigned(__builtin_amdgcn_update_dpp(
+            0, int(__float_as_uint(x)), decltype(ctrl)::value, 0xf, 0xf, true)));
+    };
+    if constexpr (C <= 8) v += rotated(v, std::integral_constant<int, 0x128>());  // row_ror:8
+    if constexpr (C <= 4) v += rotated(v, std::integral_constant<int, 0x124>());  // row_ror:4
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
 }
 
 // Wave w of the network, slice by slice; the barriers are those of chain_states.
-__device__ inline void chain_network(const ChainArgs &a, ChainLds &L, int w, int lane) {
-    const int s = lane & 15, g = lane >> 4, f0 = 16 * w + 4 * g;
+template <int C>
+__device__ inline void chain_network(const ChainArgs &a, ChainLds<C> &L, int w, int lane) {
+    constexpr int V = C / 4;
+    const int r = lane & 15, s = r % C, copy = r / C, g = lane >> 4;
+    const int first = V * copy, f0 = 16 * w + 4 * g + first, at = g * C + s;
     bf16x8 w2[4], w3[4];
-    const __bf16 *row = a.shadow + (16 * w + s) * kWidth + 8 * g;
+    const __bf16 *row = a.shadow + (16 * w + r) * kWidth + 8 * g;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
         w2[kb] = *reinterpret_cast<const bf16x8 *>(row + 32 * kb);
         w3[kb] = *reinterpret_cast<const bf16x8 *>(row + kMat + 32 * kb);
     }
-    float w1[4][4], b1[4], b2[4], b3[4], w40[4], w41[4];
+    float w1[V][4], b1[V], b2[V], b3[V], w40[V], w41[V];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < V; ++i) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) w1[i][k] = a.params[kW1 + 4 * (f0 + i) + k];
         b1[i] = a.params[kB1 + f0 + i];
@@ -330,35 +370,32 @@ __device__ inline void chain_network(const ChainArgs &a, ChainLds &L, int w, int
     for (int j = 0; j < a.n_slices; ++j) {
         __syncthreads();                                    // the inputs
         const f32x4 u = *reinterpret_cast<const f32x4 *>(L.u[s]);
-        f32x4 x;
-        float d;
+        float x[V], d;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < V; ++i) {
             float z = b1[i];
 #pragma unroll
             for (int k = 0; k < 4; ++k) z = fmaf(w1[i][k], u[k], z);
             x[i] = gelu_d(z, d);
         }
-        publish_tile(L.xb[0], x, w, lane);
+        publish_tile<C>(L.xb[0], x, w, at, first);
         __syncthreads();                                    // layer 1
-        x = layer_tile(w2, L.xb[0], lane);
+        layer_tile<C>(w2, L.xb[0], at, copy, x);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = gelu_d(x[i] + b2[i], d);
-        publish_tile(L.xb[1], x, w, lane);
+        for (int i = 0; i < V; ++i) x[i] = gelu_d(x[i] + b2[i], d);
+        publish_tile<C>(L.xb[1], x, w, at, first);
         __syncthreads();                                    // layer 2
-        x = layer_tile(w3, L.xb[1], lane);
+        layer_tile<C>(w3, L.xb[1], at, copy, x);
         float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < V; ++i) {
             const float v = gelu_d(x[i] + b3[i], d);
             s0 = fmaf(w40[i], v, s0);
             s1 = fmaf(w41[i], v, s1);
         }
-        s0 += __shfl_xor(s0, 16);
-        s1 += __shfl_xor(s1, 16);
-        s0 += __shfl_xor(s0, 32);
-        s1 += __shfl_xor(s1, 32);
-        if (g == 0) {
+        s0 = chain_sum<C>(s0);
+        s1 = chain_sum<C>(s1);
+        if (lane < C) {
             L.part[0][s][w] = s0;
             L.part[1][s][w] = s1;
         }
@@ -370,17 +407,18 @@ __device__ inline float chain_output(const float (&p)[kChainNet], float bias) {
     return (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) + bias;
 }
 
-// The wave that holds the chains' states (lane l: chain l % 16).
-__device__ inline void chain_states(const ChainArgs &a, ChainLds &L, int lane) {
+// The wave that holds the chains' states (lane l: chain l % C).
+template <int C>
+__device__ inline void chain_states(const ChainArgs &a, ChainLds<C> &L, int lane) {
 #pragma clang fp contract(off)
-    const int s = lane & 15, g = lane >> 4;
-    const long long q = (long long)blockIdx.x * 16 + s;
+    const int s = lane % C;
+    const long long q = (long long)blockIdx.x * C + s;
     const bool live = q < a.count;
     const long long qc = live ? q : a.count - 1;
     double l0 = a.y0[2 * qc], l1 = a.y0[2 * qc + 1];
     const double mu = a.mu[qc];
     const float muf = float(mu), b40 = a.params[kB4], b41 = a.params[kB4 + 1];
-    const bool writer = live && g == 0;
+    const bool writer = live && lane < C;
     const long long stride = (long long)a.n_slices + 1;
     if (writer && a.boundary) {
         a.boundary[(q * stride) * 2] = l0;
@@ -396,7 +434,7 @@ __device__ inline void chain_states(const ChainArgs &a, ChainLds &L, int lane) {
         const f32x4 u = {(float(l0) - a.shift[0]) * a.scale[0],
                          (float(l1) - a.shift[1]) * a.scale[1], (tj - a.shift[2]) * a.scale[2],
                          (muf - a.shift[3]) * a.scale[3]};
-        if (g == 0) *reinterpret_cast<f32x4 *>(L.u[s]) = u;
+        if (lane < C) *reinterpret_cast<f32x4 *>(L.u[s]) = u;
         __syncthreads();                                    // the inputs
         // G1 (or G), then the 2k half-length steps of G2 in two parts
         double g0 = l0, g1 = l1, e0 = l0, e1 = l1;
@@ -463,14 +501,15 @@ __device__ inline void chain_states(const ChainArgs &a, ChainLds &L, int lane) {
     }
 }
 
+template <int C>
 __global__ __launch_bounds__(kChainThreads) void sur_chain_kernel(ChainArgs a) {
-    __shared__ ChainLds L;
+    __shared__ ChainLds<C> L;
     const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int lane = int(threadIdx.x) & 63;
     if (w < kChainNet)
-        chain_network(a, L, w, lane);
+        chain_network<C>(a, L, w, lane);
     else
-        chain_states(a, L, lane);
+        chain_states<C>(a, L, lane);
 }
 
 // ---- training: forward pass, loss, back-propagation and gradient sums -----
@@ -1373,11 +1412,20 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
     const unsigned long long init[4] = {0ull, 0ull, 0ull, ~0ull};
     NV_HIP(hipMemcpyAsync(s->stats, init, sizeof init, hipMemcpyHostToDevice, s->stream));
     a.stats = s->stats;
-    const long long blocks = (c->count + 15) / 16;
-    if (blocks > 0x7fffffffLL) return fail(NV_ERR_INVALID_ARG, "too many chains");
+    if ((c->count + 15) / 16 > 0x7fffffffLL) return fail(NV_ERR_INVALID_ARG, "too many chains");
+    // as few chains per workgroup as keep one workgroup per CU (two of them take
+    // longer than one of twice the chains: 1500 chains 1.44 us per slice in fours,
+    // 1.21 in eights; 3000 chains 1.85 in eights, 1.57 in sixteens)
+    const int per = c->count <= 4LL * s->n_cu ? 4 : (c->count <= 8LL * s->n_cu ? 8 : 16);
+    const unsigned blocks = unsigned((c->count + per - 1) / per);
     NV_HIP(hipEventRecord(s->ev0, s->stream));
-    hipLaunchKernelGGL(sur_chain_kernel, dim3(unsigned(blocks)), dim3(kChainThreads), 0,
-                       s->stream, a);
+    if (per == 4)
+        hipLaunchKernelGGL(sur_chain_kernel<4>, dim3(blocks), dim3(kChainThreads), 0, s->stream, a);
+    else if (per == 8)
+        hipLaunchKernelGGL(sur_chain_kernel<8>, dim3(blocks), dim3(kChainThreads), 0, s->stream, a);
+    else
+        hipLaunchKernelGGL(sur_chain_kernel<16>, dim3(blocks), dim3(kChainThreads), 0, s->stream,
+                           a);
     NV_HIP(hipGetLastError());
     NV_HIP(hipEventRecord(s->ev1, s->stream));
     unsigned long long st[4];
