@@ -81,7 +81,7 @@ typedef struct {
     int coarse_steps;            /* 0: G(y) = y; 1..16: RK4 steps of the coarse propagator */
     long long max_batch;         /* largest minibatch of nv_sur_loss_grad / nv_sur_train:
                                     a multiple of 16, 16 .. 2^20 (0 = 65536); the training
-                                    workspace is 35 MB whatever it is */
+                                    workspace is 48 MB whatever it is */
     void *stream;                /* hipStream_t of every kernel; NULL = null stream */
     int correction;              /* nv_sur_correction (0 = additive) */
     double gate[NV_SUR_OUT];     /* step-doubling: the gate's scale per component, > 0 */
@@ -134,7 +134,8 @@ typedef struct {
  * once beforehand (nv_sur_dataset_from_batch takes a permutation).  When
  * loss_dev is not NULL it receives one fp32 minibatch loss per step (device,
  * opts->steps values).  Every step is two kernels: forward and
- * back-propagation with the gradient sums, and the Adam update.
+ * back-propagation with the gradient sums, and the Adam update (below 8192
+ * samples the gradient sums are a kernel of their own).
  * Errors: INVALID_ARG, HIP. */
 NV_API nv_status nv_sur_train(nv_sur *sur, const float *x_dev, const float *target_dev,
                               long long n_samples, const nv_sur_train_opts *opts,

@@ -33,6 +33,22 @@ constexpr int kMat = kWidth * kWidth;  // elements of one 128 x 128 matrix
 constexpr int kLdsRow = kWidth + 8;    // padded bf16 row in LDS: 272 bytes, 16-lane reads
                                        // of 16 bytes from 16 rows hit disjoint banks
 
+// Workspace S of a small minibatch: bfloat16 rows of one value per sample.
+constexpr int kRowD = 0;      // 384 rows: dL/dz of layers 1, 2, 3
+constexpr int kRowH = 384;    // 384 rows: bf16 activations a1, a2, a3
+constexpr int kRowXO = 768;   // 16 rows: u0..u3, 1, dL/dout0, dL/dout1, zeros
+constexpr int kRowsS = 784;
+
+// Weight-gradient sums G = A B^T over the minibatch, A and B row blocks of S.
+// Their outputs, concatenated, form one partial vector per split of the sum.
+constexpr int kG_W2 = 0;                    // [128 x 128]  D2 . H1^T
+constexpr int kG_W3 = 16384;                // [128 x 128]  D3 . H2^T
+constexpr int kG_D_XO = 32768;              // [384 x 16]   D . XO^T  (dW1, db1; db2, db3 in column 4)
+constexpr int kG_XO_H3 = 32768 + 384 * 16;  // [16 x 144]   XO . [H3; XO]^T  (dW4, db4)
+constexpr int kGradEntries = kG_XO_H3 + 16 * 144;
+constexpr int kGemmWaveTiles = 16 + 16 + 4 + 5;
+constexpr int kGemmSmallFirst = 32;         // wave tiles of the two small products
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 

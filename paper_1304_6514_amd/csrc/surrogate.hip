@@ -27,7 +27,9 @@ using namespace nv::mlp;
 namespace {
 
 constexpr int kInferThreads = 256;       // 4 waves
-constexpr int kMaxSplits = 256;          // training workgroups, each with its own gradient sums
+constexpr int kMaxSplits = 256;          // shares of the gradient sums: training workgroups
+constexpr int kRowSplits = 128;          // ... or splits of a small minibatch's rows,
+constexpr long long kMinSplit = 512;     // of so many samples at least
 constexpr long long kMaxBatch = 1LL << 20;
 
 // A workgroup's gradient sums: the flat parameter order, except that W2 and W3
@@ -97,25 +99,220 @@ struct TrainArgs {
     const float *params;
     const __bf16 *shadow;        // Wf2, Wf3, Wb2, Wb3 (permuted bf16)
     float *part;                 // [workgroups][kPartRow] gradient sums
+    __bf16 *S;                   // kRowsS rows of ldS samples (small minibatches)
+    long long ldS;
     float *loss_part;            // [workgroups]
     float shift[4], scale[4];
     float inv_n;
     int weighted;                // targets are rho_0, rho_1, w_0, w_1: e = w out - rho
 };
 
+// Weight-gradient sums G = A B^T over samples k0..k1-1 of the minibatch, A and
+// B row blocks of S; blockIdx.y of the launch is the split of the sum.  In the
+// small products each wave computes a 32 x 32 block (wave tiles
+// kGemmSmallFirst.. of kGemmWaveTiles: D1 . XO^T, giving dW1 and db1, and
+// XO . [H3; XO]^T, giving dW4 and db4; db2 and db3 are row sums that the
+// 128 x 128 products form from the rows they stage anyway).
+struct GemmArgs {
+    const __bf16 *S;
+    long long ldS, n, k_per_split;
+    float *part;                 // [splits][kGradEntries]
+};
+
+__device__ inline void grad_small(const GemmArgs &a, int bx) {
+    const int lane = int(threadIdx.x) & 63, r = lane & 15, g = lane >> 4;
+    const int wt = kGemmSmallFirst + bx * 4 + (int(threadIdx.x) >> 6);
+    if (wt >= kGemmWaveTiles) return;
+    int a_row, b_row, M, N, out, t, tiles_n;
+    if (wt < 16) {
+        a_row = kRowD + 128; b_row = kRowH; M = N = 128; out = kG_W2; t = wt; tiles_n = 4;
+    } else if (wt < 32) {
+        a_row = kRowD + 256; b_row = kRowH + 128; M = N = 128; out = kG_W3; t = wt - 16;
+        tiles_n = 4;
+    } else if (wt < 36) {
+        a_row = kRowD; b_row = kRowXO; M = 128; N = 16; out = kG_D_XO; t = wt - 32; tiles_n = 1;
+    } else {
+        a_row = kRowXO; b_row = kRowH + 256; M = 16; N = 144; out = kG_XO_H3; t = wt - 36;
+        tiles_n = 5;
+    }
+    const int mt0 = 2 * (t / tiles_n), nt0 = 2 * (t % tiles_n);
+    const bool m1 = mt0 + 1 < M / 16, n1 = nt0 + 1 < N / 16;
+    const long long k0 = (long long)blockIdx.y * a.k_per_split;
+    const long long k1 = std::min(k0 + a.k_per_split, a.n);
+    const __bf16 *pa0 = a.S + (long long)(a_row + 16 * mt0 + r) * a.ldS + 8 * g;
+    const __bf16 *pa1 = pa0 + 16 * a.ldS;
+    const __bf16 *pb0 = a.S + (long long)(b_row + 16 * nt0 + r) * a.ldS + 8 * g;
+    const __bf16 *pb1 = pb0 + 16 * a.ldS;
+    f32x4 c00 = {0.f, 0.f, 0.f, 0.f}, c01 = c00, c10 = c00, c11 = c00;
+    const bf16x8 zero = {};
+    constexpr int U = 4;                         // k-steps of 32 samples per iteration
+    long long k = k0;
+    for (; k + 32 * U <= k1; k += 32 * U) {
+        bf16x8 A0[U], A1[U], B0[U], B1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            A0[u] = *reinterpret_cast<const bf16x8 *>(pa0 + k + 32 * u);
+            B0[u] = *reinterpret_cast<const bf16x8 *>(pb0 + k + 32 * u);
+            A1[u] = m1 ? *reinterpret_cast<const bf16x8 *>(pa1 + k + 32 * u) : zero;
+            B1[u] = n1 ? *reinterpret_cast<const bf16x8 *>(pb1 + k + 32 * u) : zero;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c00 = mfma(A0[u], B0[u], c00);
+            if (n1) c01 = mfma(A0[u], B1[u], c01);
+            if (m1) c10 = mfma(A1[u], B0[u], c10);
+            if (m1 && n1) c11 = mfma(A1[u], B1[u], c11);
+        }
+    }
+    for (; k < k1; k += 32) {
+        const bool ok = k + 8 * g < k1;          // the minibatch ends on a multiple of 16
+        const bf16x8 A0 = ok ? *reinterpret_cast<const bf16x8 *>(pa0 + k) : zero;
+        const bf16x8 B0 = ok ? *reinterpret_cast<const bf16x8 *>(pb0 + k) : zero;
+        const bf16x8 A1 = (ok && m1) ? *reinterpret_cast<const bf16x8 *>(pa1 + k) : zero;
+        const bf16x8 B1 = (ok && n1) ? *reinterpret_cast<const bf16x8 *>(pb1 + k) : zero;
+        c00 = mfma(A0, B0, c00);
+        if (n1) c01 = mfma(A0, B1, c01);
+        if (m1) c10 = mfma(A1, B0, c10);
+        if (m1 && n1) c11 = mfma(A1, B1, c11);
+    }
+    float *P = a.part + (long long)blockIdx.y * kGradEntries + out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row0 = 16 * mt0 + 4 * g + i, col0 = 16 * nt0 + r;
+        P[row0 * N + col0] = c00[i];
+        if (n1) P[row0 * N + col0 + 16] = c01[i];
+        if (m1) P[(row0 + 16) * N + col0] = c10[i];
+        if (m1 && n1) P[(row0 + 16) * N + col0 + 16] = c11[i];
+    }
+}
+
+// The two 128 x 128 weight gradients, dW2 = D2 . H1^T and dW3 = D3 . H2^T
+// (job 0, 1), over samples k0..k1-1 (blockIdx.y = split), and the
+// bias gradients db2, db3, the row sums of D2 and D3.  The workgroup stages
+// each 32-sample step of its 128 A rows and 128 B rows in LDS once (rows
+// padded to 80 bytes: 16 lanes reading 16 bytes from 16 rows hit disjoint
+// banks) and each wave multiplies a 64 x 64 quadrant; two threads per A row
+// add its 32 staged values into FP32 row sums; the next step's rows are loaded
+// into registers while the current one is multiplied.
+constexpr int kGmPad = 40;                 // bf16 per LDS row
+
+struct GradMatLds {
+    __bf16 As[128 * kGmPad], Bs[128 * kGmPad];
+};
+
+__device__ inline void grad_mat(const GemmArgs &a, GradMatLds &L, int job) {
+    __bf16 *As = L.As, *Bs = L.Bs;
+    const int a_row = job == 0 ? kRowD + 128 : kRowD + 256;
+    const int b_row = job == 0 ? kRowH : kRowH + 128;
+    const int out = job == 0 ? kG_W2 : kG_W3;
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    const int r = lane & 15, g = lane >> 4, mh = wave >> 1, nh = wave & 1;
+    const long long k0 = (long long)blockIdx.y * a.k_per_split;
+    const long long k1 = std::min(k0 + a.k_per_split, a.n);
+    // this thread's share of a step: chunks tid and tid + 256 of 4 x 128 16-byte chunks
+    const int row0 = tid >> 2, part0 = tid & 3, row1 = (tid + 256) >> 2, part1 = (tid + 256) & 3;
+    const bf16x8 zero = {};
+    auto load = [&](long long k, bf16x8 &a0, bf16x8 &a1, bf16x8 &b0, bf16x8 &b1) {
+        const bool ok0 = k + 8 * part0 < k1, ok1 = k + 8 * part1 < k1;
+        a0 = ok0 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(a_row + row0) * a.ldS + k +
+                                                     8 * part0) : zero;
+        a1 = ok1 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(a_row + row1) * a.ldS + k +
+                                                     8 * part1) : zero;
+        b0 = ok0 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(b_row + row0) * a.ldS + k +
+                                                     8 * part0) : zero;
+        b1 = ok1 ? *reinterpret_cast<const bf16x8 *>(a.S + (long long)(b_row + row1) * a.ldS + k +
+                                                     8 * part1) : zero;
+    };
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // row sum of A row tid / 2, samples 16 (tid & 1) .. + 15 of every step
+    const int srow = tid >> 1, shalf = tid & 1;
+    float bsum = 0.0f;
+    bf16x8 ra0, ra1, rb0, rb1;
+    if (k0 < k1) load(k0, ra0, ra1, rb0, rb1);
+    for (long long k = k0; k < k1; k += 32) {
+        *reinterpret_cast<bf16x8 *>(As + row0 * kGmPad + 8 * part0) = ra0;
+        *reinterpret_cast<bf16x8 *>(As + row1 * kGmPad + 8 * part1) = ra1;
+        *reinterpret_cast<bf16x8 *>(Bs + row0 * kGmPad + 8 * part0) = rb0;
+        *reinterpret_cast<bf16x8 *>(Bs + row1 * kGmPad + 8 * part1) = rb1;
+        __syncthreads();
+        if (k + 32 < k1) load(k + 32, ra0, ra1, rb0, rb1);
+        bf16x8 fa[4], fb[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            fa[t] = *reinterpret_cast<const bf16x8 *>(As + (64 * mh + 16 * t + r) * kGmPad + 8 * g);
+            fb[t] = *reinterpret_cast<const bf16x8 *>(Bs + (64 * nh + 16 * t + r) * kGmPad + 8 * g);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(As + srow * kGmPad + 16 * shalf + 8 * h);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bsum += float(v[e]);
+        }
+        __syncthreads();
+    }
+    // the two halves of a row are adjacent lanes
+    const float rsum = bsum + __shfl_xor(bsum, 1);
+    if (shalf == 0)
+        a.part[(long long)blockIdx.y * kGradEntries + kG_D_XO + (128 * (job + 1) + srow) * 16 + 4] =
+            rsum;
+    float *P = a.part + (long long)blockIdx.y * kGradEntries + out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                P[(64 * mh + 16 * i + 4 * g + e) * 128 + 64 * nh + 16 * j + r] = acc[i][j][e];
+}
+
+// All weight-gradient sums of one step in one launch: blockIdx.x 0 and 1 are
+// the two 128 x 128 products (the long-running workgroups, dispatched first),
+// the others the small products; blockIdx.y is the split of the sum.
+constexpr int kGradSmallBlocks = (kGemmWaveTiles - kGemmSmallFirst + 3) / 4;
+
+__global__ __launch_bounds__(256) void sur_grad_kernel(GemmArgs a) {
+    __shared__ GradMatLds L;
+    if (blockIdx.x < 2)
+        grad_mat(a, L, int(blockIdx.x));
+    else
+        grad_small(a, int(blockIdx.x) - 2);
+}
+
+// Offset of parameter p's gradient in the partial vector.
+__device__ inline int grad_source(int p) {
+    if (p < kB1) return kG_D_XO + (p >> 2) * 16 + (p & 3);                 // W1[f][k]
+    if (p < kW2) return kG_D_XO + (p - kB1) * 16 + 4;                      // b1
+    if (p < kB2) return kG_W2 + (p - kW2);                                 // W2
+    if (p < kW3) return kG_D_XO + (128 + p - kB2) * 16 + 4;                // b2
+    if (p < kB3) return kG_W3 + (p - kW3);                                 // W3
+    if (p < kW4) return kG_D_XO + (256 + p - kB3) * 16 + 4;                // b3
+    if (p < kB4) return kG_XO_H3 + (5 + ((p - kW4) >> 7)) * 144 + ((p - kW4) & 127);  // W4
+    return kG_XO_H3 + (5 + (p - kB4)) * 144 + 128 + 4;                     // b4
+}
+
 struct UpdateArgs {
     float *params, *m, *v, *grad;
     __bf16 *shadow;
     const float *part;
     int splits, mode;
+    int rows;                    // the shares are sur_grad_kernel's
     float lr, beta1, beta2, eps, inv_bc1, inv_bc2;
     const float *loss_part;
+    int losses;
     float inv_n;
     float *loss_out;
 };
 
-// 64 parameters per workgroup: wave q (q = 0..7) sums the training workgroups
-// 32q .. 32q+31's shares of each parameter's gradient in order (all 32 loads in
+// 64 parameters per workgroup: wave q (q = 0..7) sums the shares 32q .. 32q+31
+// of each parameter's gradient in order (all 32 loads in
 // flight at once); wave 0 then combines the eight sums as a tree, takes the Adam
 // step and refreshes the permuted bf16 copies.
 constexpr int kUpdateParams = 64;
@@ -129,7 +326,7 @@ __global__ __launch_bounds__(kUpdateThreads) void sur_update_kernel(UpdateArgs a
         // the extra last workgroup: the minibatch loss from the workgroups' sums
         __shared__ float red[kMaxSplits];
         if (int(threadIdx.x) < kMaxSplits)
-            red[threadIdx.x] = int(threadIdx.x) < a.splits ? a.loss_part[threadIdx.x] : 0.0f;
+            red[threadIdx.x] = int(threadIdx.x) < a.losses ? a.loss_part[threadIdx.x] : 0.0f;
         __syncthreads();
         for (int w = kMaxSplits / 2; w > 0; w >>= 1) {
             if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
@@ -141,7 +338,9 @@ __global__ __launch_bounds__(kUpdateThreads) void sur_update_kernel(UpdateArgs a
     __shared__ float sums[kUpdateGroups][kUpdateParams];
     const int pl = int(threadIdx.x) & (kUpdateParams - 1), grp = int(threadIdx.x) >> 6;
     const int e = int(blockIdx.x) * kUpdateParams + pl;
-    const int ec = e < kParams ? e : kParams - 1, p = grad_param(ec);
+    const int ec = e < kParams ? e : kParams - 1;
+    const int p = a.rows ? ec : grad_param(ec), src = a.rows ? grad_source(ec) : ec;
+    const int stride = a.rows ? kGradEntries : kPartRow;
     float th = 0.0f, m0 = 0.0f, v0 = 0.0f;
     if (grp == 0) {
         th = a.params[p];
@@ -151,16 +350,18 @@ __global__ __launch_bounds__(kUpdateThreads) void sur_update_kernel(UpdateArgs a
         }
     }
     if (a.mode & kModeReduce) {
-        float part[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int sp = grp * kPer + u;
-            part[u] = a.part[(sp < a.splits ? sp : a.splits - 1) * kPartRow + ec];
-        }
         float gs = 0.0f;
+        if (grp * kPer < a.splits) {
+            float part[kPer];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u)
-            if (grp * kPer + u < a.splits) gs += part[u];
+            for (int u = 0; u < kPer; ++u) {
+                const int sp = grp * kPer + u;
+                part[u] = a.part[(sp < a.splits ? sp : a.splits - 1) * stride + src];
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (grp * kPer + u < a.splits) gs += part[u];
+        }
         sums[grp][pl] = gs;
     }
     __syncthreads();
@@ -170,8 +371,11 @@ __global__ __launch_bounds__(kUpdateThreads) void sur_update_kernel(UpdateArgs a
                            ((sums[4][pl] + sums[5][pl]) + (sums[6][pl] + sums[7][pl]));
         a.grad[p] = gsum;
         if (a.mode & kModeAdam) {
-            const float m = a.beta1 * m0 + (1.0f - a.beta1) * gsum;
-            const float v = a.beta2 * v0 + (1.0f - a.beta2) * gsum * gsum;
+            // the fused operations spelled out: which product is rounded on its own
+            // must not depend on what the compiler sees around them (the other
+            // choice changes the last bits, which grow from step to step)
+            const float m = fmaf(1.0f - a.beta1, gsum, a.beta1 * m0);
+            const float v = fmaf(gsum, (1.0f - a.beta2) * gsum, a.beta2 * v0);
             a.m[p] = m;
             a.v[p] = v;
             th -= a.lr * (m * a.inv_bc1) / (sqrtf(v * a.inv_bc2) + a.eps);
@@ -515,7 +719,9 @@ __global__ __launch_bounds__(kChainThreads) void sur_chain_kernel(ChainArgs a) {
 // ---- training: forward pass, loss, back-propagation and gradient sums -----
 //
 // One launch does the whole pass over a minibatch and leaves one share of every
-// gradient per workgroup; nothing per sample goes to memory.  (With the bf16
+// gradient per workgroup; nothing per sample goes to memory (Rows: a small
+// minibatch, whose activations and errors go to the workspace instead, see
+// kRowsBelow).  (With the bf16
 // activations and errors of every sample written to a workspace and the
 // gradient products formed from it by a second launch, a step of 65,536
 // samples took 44 + 24 us; it takes 54 us, 4.4 us per pass of 8,192 samples on
@@ -614,6 +820,7 @@ __device__ inline void layer_rows(const __bf16 (&act)[kTrainPass][kActRow], cons
     }
 }
 
+template <bool Rows>
 __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a) {
     __shared__ TrainLds L;
     const int tid = int(threadIdx.x), lane = tid & 63;
@@ -696,8 +903,21 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
                 d1[t][i] = computed(d);
             }
         }
+        // the pass's eight values of the wave's feature, to a row of the workspace
+        const auto store_row = [&](int row0, const bf16x8 &v) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            __bf16 *at_row = a.S + (row0 + f) * a.ldS + kTrainPass * pass + 4 * g;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                if (kTrainPass * pass + 16 * t < count)
+                    *reinterpret_cast<bf16x4 *>(at_row + 16 * t) =
+                        bf16x4{v[4 * t], v[4 * t + 1], v[4 * t + 2], v[4 * t + 3]};
+        };
         bf16x8 h = pack8(x);
-        L.act_t[0][w][lane] = h;
+        if constexpr (Rows)
+            store_row(kRowH, h);
+        else
+            L.act_t[0][w][lane] = h;
         publish_rows(reinterpret_cast<unsigned *>(&L.act[0][0][0]) + at, h, select);
         __syncthreads();
         // layers 2 and 3
@@ -711,7 +931,10 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
                 d2[t][i] = computed(d);
             }
         h = pack8(x);
-        L.act_t[1][w][lane] = h;
+        if constexpr (Rows)
+            store_row(kRowH + 128, h);
+        else
+            L.act_t[1][w][lane] = h;
         publish_rows(reinterpret_cast<unsigned *>(&L.act[1][0][0]) + at, h, select);
         __syncthreads();
         layer_rows(L.act[1], wf3, lane, x);
@@ -766,7 +989,15 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
             gb4 += float(rounded);
         }
         // back-propagation: dL/dz3 = (W4^T dout) * gelu'(z3)
-        gw4 = mfma(h3, *reinterpret_cast<const bf16x8 *>(&L.dout_t[w][c & 1][8 * g]), gw4);
+        if constexpr (Rows) {
+            store_row(kRowH + 256, h3);
+            // rows of XO: u0 .. u3, ones, dL/dout, zeros
+            const int n = tid & (kTrainPass - 1), k = tid / kTrainPass, in = perm32_inv(n);
+            if (kTrainPass * pass + n < count)
+                a.S[(kRowXO + k) * a.ldS + kTrainPass * pass + n] =
+                    k < 5 ? L.u_t[buf][k][in] : (k < 7 ? L.dout_t[w][k - 5][in] : __bf16(0.0f));
+        }
+        if constexpr (!Rows) gw4 = mfma(h3, *reinterpret_cast<const bf16x8 *>(&L.dout_t[w][c & 1][8 * g]), gw4);
         const bf16x8 *ut = reinterpret_cast<const bf16x8 *>(&L.u_t[buf][c < 4 ? c : 4][8 * g]);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -777,10 +1008,12 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
         }
         bf16x8 err = pack8(x);
         publish_rows(reinterpret_cast<unsigned *>(&L.act[2][0][0]) + at, err, select);
-        gx3 = mfma(err, *ut, gx3);
+        if constexpr (Rows) {
+            store_row(kRowD + 256, err);
+        } else {
+            gx3 = mfma(err, *ut, gx3);
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-            gw3[ct] = mfma(err, L.act_t[1][ct][lane], gw3[ct]);
+            for (int ct = 0; ct < 8; ++ct) gw3[ct] = mfma(err, L.act_t[1][ct][lane], gw3[ct]);
         }
         __syncthreads();
         layer_rows(L.act[2], wb3, lane, x);                 // W3^T dL/dz3
@@ -788,35 +1021,42 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
         for (int t = 0; t < 2; ++t) x[t] *= d2[t];
         err = pack8(x);
         publish_rows(reinterpret_cast<unsigned *>(&L.act[3][0][0]) + at, err, select);
-        gx2 = mfma(err, *ut, gx2);
+        if constexpr (Rows) {
+            store_row(kRowD + 128, err);
+        } else {
+            gx2 = mfma(err, *ut, gx2);
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-            gw2[ct] = mfma(err, L.act_t[0][ct][lane], gw2[ct]);
+            for (int ct = 0; ct < 8; ++ct) gw2[ct] = mfma(err, L.act_t[0][ct][lane], gw2[ct]);
         }
         __syncthreads();
         layer_rows(L.act[3], wb2, lane, x);                 // W2^T dL/dz2
 #pragma unroll
         for (int t = 0; t < 2; ++t) x[t] *= d1[t];
-        gx1 = mfma(pack8(x), *ut, gx1);
+        if constexpr (Rows)
+            store_row(kRowD, pack8(x));
+        else
+            gx1 = mfma(pack8(x), *ut, gx1);
     }
 
-    // the workgroup's share of every gradient
     float *P = a.part + blockIdx.x * kPartRow;
+    if constexpr (!Rows) {
+        // the workgroup's share of every gradient
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-        const int at2 = ((ct * 8 + w) * 64 + lane) * 4;
-        *reinterpret_cast<f32x4 *>(P + kW2 + at2) = gw2[ct];
-        *reinterpret_cast<f32x4 *>(P + kW3 + at2) = gw3[ct];
-    }
+        for (int ct = 0; ct < 8; ++ct) {
+            const int at2 = ((ct * 8 + w) * 64 + lane) * 4;
+            *reinterpret_cast<f32x4 *>(P + kW2 + at2) = gw2[ct];
+            *reinterpret_cast<f32x4 *>(P + kW3 + at2) = gw3[ct];
+        }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int fi = 16 * w + 4 * g + i;
-        if (c < 4) P[kW1 + 4 * fi + c] = gx1[i];
-        if (c < 2) P[kW4 + kWidth * c + fi] = gw4[i];
-        if (c == 4) {
-            P[kB1 + fi] = gx1[i];
-            P[kB2 + fi] = gx2[i];
-            P[kB3 + fi] = gx3[i];
+        for (int i = 0; i < 4; ++i) {
+            const int fi = 16 * w + 4 * g + i;
+            if (c < 4) P[kW1 + 4 * fi + c] = gx1[i];
+            if (c < 2) P[kW4 + kWidth * c + fi] = gw4[i];
+            if (c == 4) {
+                P[kB1 + fi] = gx1[i];
+                P[kB2 + fi] = gx2[i];
+                P[kB3 + fi] = gx3[i];
+            }
         }
     }
     if (w == 0) {
@@ -826,7 +1066,7 @@ __global__ __launch_bounds__(kTrainThreads, 2) void sur_train_kernel(TrainArgs a
             if (m != 8) gb4 += __shfl_xor(gb4, m);
             loss += __shfl_xor(loss, m);
         }
-        if (g == 0 && (c & 7) == 0) P[kB4 + my_out] = gb4;
+        if (!Rows && g == 0 && (c & 7) == 0) P[kB4 + my_out] = gb4;
         if (lane == 0) a.loss_part[blockIdx.x] = loss;
     }
 }
@@ -976,7 +1216,7 @@ struct nv_sur {
     long long max_batch = 0;
     char *mem = nullptr;         // one device allocation
     float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
-    __bf16 *shadow = nullptr;
+    __bf16 *shadow = nullptr, *S = nullptr;
     float *part = nullptr, *loss_part = nullptr, *loss = nullptr;
     unsigned long long *stats = nullptr;
     int *error = nullptr;
@@ -1011,6 +1251,22 @@ nv_status refresh_shadow(nv_sur *s) {
     return NV_OK;
 }
 
+// A minibatch that leaves some of the compute units without a pass keeps one order
+// of sums whatever the number of units: its activations and errors go to rows of a
+// workspace, and sur_grad_kernel sums over the rows in splits of 512 samples.  With
+// one share per pass instead a step of 1024 samples takes 20 us, not 30, but a
+// gradient over few samples then differs in its last bits, and Adam, which divides
+// by the gradient's size, and the rounding of the weights to bfloat16 make that up
+// to 4e-5 of the parameters within twenty steps of a few hundred samples (of 190
+// runs below 8192 samples 23 were over 2e-5; above, at most 9e-6).  At 8192 the two
+// take the same time, 34 us.
+constexpr long long kRowsBelow = 8192;
+
+long long k_per_split(long long n) {
+    const long long k = std::max(kMinSplit, (n + kRowSplits - 1) / kRowSplits);
+    return (k + 31) / 32 * 32;
+}
+
 // One minibatch: forward and back-propagation with the gradient sums, then the
 // update kernel (mode: reduce only, or reduce and Adam step).
 nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, long long start,
@@ -1025,14 +1281,26 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
     ta.params = s->params;
     ta.shadow = s->shadow;
     ta.part = s->part;
+    ta.S = s->S;
+    ta.ldS = kRowsBelow;
     ta.loss_part = s->loss_part;
     fill_norm(s, ta.shift, ta.scale);
     ta.inv_n = float(1.0 / double(n));
     ta.weighted = s->cfg.correction == NV_SUR_STEP_DOUBLING;
     const long long passes = (n + kTrainPass - 1) / kTrainPass;
     const int blocks = int(std::min<long long>(passes, std::min(s->n_cu, kMaxSplits)));
-    hipLaunchKernelGGL(sur_train_kernel, dim3(blocks), dim3(kTrainThreads), 0, s->stream, ta);
+    const bool rows = n < kRowsBelow;
+    int shares = blocks;
+    hipLaunchKernelGGL(rows ? sur_train_kernel<true> : sur_train_kernel<false>, dim3(blocks),
+                       dim3(kTrainThreads), 0, s->stream, ta);
     NV_HIP(hipGetLastError());
+    if (rows) {
+        GemmArgs ga{s->S, kRowsBelow, n, k_per_split(n), s->part};
+        shares = int((n + ga.k_per_split - 1) / ga.k_per_split);
+        hipLaunchKernelGGL(sur_grad_kernel, dim3(2 + kGradSmallBlocks, shares), dim3(256), 0,
+                           s->stream, ga);
+        NV_HIP(hipGetLastError());
+    }
 
     UpdateArgs ua{};
     ua.params = s->params;
@@ -1041,7 +1309,8 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
     ua.grad = s->grad;
     ua.shadow = s->shadow;
     ua.part = s->part;
-    ua.splits = blocks;
+    ua.splits = shares;
+    ua.rows = rows;
     ua.mode = mode;
     if (mode & kModeAdam) {
         const long long t = ++s->adam_t;
@@ -1053,6 +1322,7 @@ nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, lon
         ua.inv_bc2 = float(1.0 / (1.0 - std::pow(double(b2), double(t))));
     }
     ua.loss_part = s->loss_part;
+    ua.losses = blocks;
     ua.inv_n = ta.inv_n;
     ua.loss_out = loss_out;
     // one workgroup per 64 parameters, plus one for the loss
@@ -1118,6 +1388,7 @@ NV_API nv_status nv_sur_create(const nv_sur_config *cfg, nv_sur **out) try {
     const size_t o_shadow = off; off = align256(off + 4 * kMat * sizeof(__bf16));
     const size_t o_part = off;   off = align256(off + size_t(kMaxSplits) * kPartRow * 4);
     const size_t o_lp = off;     off = align256(off + kMaxSplits * sizeof(float));
+    const size_t o_S = off;      off = align256(off + size_t(kRowsS) * size_t(kRowsBelow) * 2);
     const size_t o_loss = off;   off = align256(off + sizeof(float));
     const size_t o_stats = off;  off = align256(off + 4 * sizeof(unsigned long long));
     const size_t o_err = off;    off = align256(off + sizeof(int));
@@ -1132,6 +1403,7 @@ NV_API nv_status nv_sur_create(const nv_sur_config *cfg, nv_sur **out) try {
     s->grad = reinterpret_cast<float *>(s->mem + o_grad);
     s->shadow = reinterpret_cast<__bf16 *>(s->mem + o_shadow);
     s->part = reinterpret_cast<float *>(s->mem + o_part);
+    s->S = reinterpret_cast<__bf16 *>(s->mem + o_S);
     s->loss_part = reinterpret_cast<float *>(s->mem + o_lp);
     s->loss = reinterpret_cast<float *>(s->mem + o_loss);
     s->stats = reinterpret_cast<unsigned long long *>(s->mem + o_stats);

@@ -1,7 +1,8 @@
 """The training kernel at the edges of its passes: minibatches of one tile (half a
 pass of 32 samples), one pass, an odd number of tiles, and more passes than there
-are compute units (some workgroups take two passes, the last only half of one),
-with and without per-sample weights.
+are compute units (some workgroups take two passes, the last only half of one), and
+on both sides of 8192 samples, where the gradient sums change from rows of a
+workspace to the training kernel's registers; with and without per-sample weights.
 
 Tolerances against the oracle that rounds to bfloat16 where the kernel does: what
 is left is FP32 against FP64 accumulation (2^-24 per operation, under 1e-5 over
@@ -29,7 +30,7 @@ def torch():
 
 
 @pytest.mark.parametrize("weighted", [False, True])
-@pytest.mark.parametrize("n", [16, 32, 48, 8208])
+@pytest.mark.parametrize("n", [16, 32, 48, 8176, 8192, 8208])
 def test_gradients_at_the_edges_of_a_pass(torch, n, weighted):
     from paper_1304_6514_amd.surrogate import Surrogate
     kw = dict(correction="step-doubling", coarse_steps=1, out_scale=W.SUR_SD_OUT_SCALE,
