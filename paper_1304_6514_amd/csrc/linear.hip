@@ -13,7 +13,9 @@
 // Communication phase: lin_chain_kernel, one workgroup of eight waves, wave r
 // forming the partial sums of residue r of the fixed summation order for
 // every component from table values prefetched into its registers several
-// slices ahead; one LDS exchange and one barrier per slice.
+// slices ahead; one LDS exchange and one barrier per slice.  From kBlockedFrom
+// slices on it runs through products of the slices' maps, formed by
+// lin_many_kernel, which also carries many chains at once.
 #include "nv_internal.h"
 #include "nv_linear.h"
 
@@ -140,8 +142,8 @@ __device__ inline void lin_step(double (&x)[MP], double off, const double (&w)[2
 // step, and of the four lane reads that bring the row's two coefficients into
 // scalar registers (with the coefficients staged in LDS, two to four waves per
 // SIMD waited for a read every other row: 226 us at M = 99, 1024 slices of 20
-// steps, where this takes 115 us; M = 127, 512 slices: 1059 -> 124 us).  Up to MP = 104 two waves share a SIMD;
-// above, a wave has the SIMD's registers to itself.
+// steps, where this takes 115 us; M = 127, 512 slices: 1059 -> 124 us).  Up to
+// MP = 104 two waves share a SIMD; above, a wave has the SIMD's registers to itself.
 template <int MP>
 __global__ __launch_bounds__(128, MP <= 104 ? 2 : 1) void lin_build_kernel(BuildArgs a) {
 #pragma clang fp contract(off)
