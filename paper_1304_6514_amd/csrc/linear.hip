@@ -955,7 +955,9 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
     // the boundary states and the report, next to each other: one copy back
     const size_t o_b = off;    off = off + (size_t(n_slices) + 1) * M * 8;
     const size_t o_bad = off;  off = al(off + sizeof(double));
-    // the products of blocks of slices, level by level
+    // the products of blocks of slices, level by level, where there is room for
+    // them (a seventh of the tables)
+    const size_t without = off;
     size_t o_prod[kMaxLevels] = {};
     int levels = 0;
     if (n_slices >= kBlockedFrom && n_slices <= (1 << 30))
@@ -971,7 +973,16 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
             l->mem = nullptr;
             l->mem_bytes = 0;
         }
-        if (hipMalloc(reinterpret_cast<void **>(&l->mem), off) != hipSuccess) {
+        hipError_t e = hipMalloc(reinterpret_cast<void **>(&l->mem), off);
+        if (e != hipSuccess && levels > 0) {
+            (void)hipGetLastError();
+            levels = 0;
+            off = without;
+            e = hipMalloc(reinterpret_cast<void **>(&l->mem), off);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            l->mem = nullptr;
             l->built = false;
             return fail(NV_ERR_OOM, "device allocation of %zu bytes failed", off);
         }
