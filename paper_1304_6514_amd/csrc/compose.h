@@ -5,6 +5,7 @@
 // result over given tables is specified bit for bit (include/nv.h).
 #pragma once
 
+#include "chain_ring.h"
 #include "nv_internal.h"
 
 #include <cmath>
@@ -288,15 +289,6 @@ __device__ inline void compose_range_bilinear(const ComposeArgs &a, double *fina
 // Hermite, windows 0.33 -> 0.18 us; of 1000 nodes, linear, rows 0.27 -> 0.13 us;
 // 301 slices of 1501 nodes with slopes, rows of 12 KB, 0.37 -> 0.25 us; 1024
 // slices of 8192 nodes whose cells cannot be predicted, 0.43 -> 0.41 us.
-constexpr int kPfHelpers = 8;              // helper waves
-constexpr int kPfThreads = 64 * (1 + kPfHelpers);
-constexpr int kPfMaxSlots = 32;            // slots of the ring, at most
-constexpr int kPfRingBytes = 152 * 1024;
-constexpr int kPfRowBytes = 12 * 1024;     // rows shorter than this are staged whole
-constexpr int kPfWinBytes = 4 * 1024;      // a window's slot
-constexpr int kPfWin = 256;                // nodes of the narrowest window
-constexpr int kPfAhead = 14;               // a window is fetched this many slices ahead
-constexpr int kPfPair = 2;                 // slices a helper stages in one turn
 constexpr int kPfLead = 12;                // a windowed chain's first slices are not staged, and
 constexpr int kPfSeen = 8;                 // this many of them are finished before later ones are
 constexpr int kPfPolls = 24;               // polls the chain waits for a group's slots
@@ -318,27 +310,6 @@ struct PfShared {
                                    // slice j in hist[(j / kPfPublish) % 4]
     int past[64];                  // past[0]: every slice before this one is finished (the
                                    // largest integer once the chain has ended)
-};
-
-// The ring's layout for a table of n nodes of type T per row and C rows per slice.
-template <class T, int C>
-struct PfLayout {
-    bool rows;                     // whole rows (else windows)
-    int width;                     // nodes per slot and component, at most
-    int slots;
-    int row_bytes, slot_bytes;     // of a component in a slot, and of a slot
-    int ahead;                     // slices before a slot's own at which it is fetched
-    __device__ explicit PfLayout(int n) {
-        rows = (long long)n * C * int(sizeof(T)) < kPfRowBytes;
-        width = rows ? n : kPfWinBytes / (C * int(sizeof(T))) - 8;
-        row_bytes = (width * int(sizeof(T)) + 15 + 15) & ~15;
-        slot_bytes = C * row_bytes;
-        slots = kPfRingBytes / slot_bytes;
-        slots = slots < kPfMaxSlots ? slots : kPfMaxSlots;
-        // a slot is free once the slice `slots` before has been finished;
-        // windows wait longer, for the prediction's sake
-        ahead = rows || slots <= kPfAhead ? slots - 1 : kPfAhead;
-    }
 };
 
 // The value of the wave's first active lane, held in scalar registers.  The
@@ -493,7 +464,7 @@ __device__ inline void pf_report(PfShared &sh, int j, long long cell, int lane) 
 
 template <class T, int Interp>
 __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
-                                const PfLayout<T, Interp == 4 ? 2 : 1> &lay,
+                                const PfLayout &lay,
                                 double *final_out) {
     const int lane = int(threadIdx.x) & 63;
     double lam = 0.0, unused = 0.0;
@@ -643,18 +614,20 @@ __device__ inline void pf_copy(const char *src, unsigned char *dst, int bytes, i
 
 __device__ inline void pf_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Helper wave r (0 .. kPfHelpers-1) stages the pairs of slices j_begin +
-// kPfPair (r + m kPfHelpers), m = 0, 1, ...
+// Helper wave r (0 .. helpers-1) stages the pairs of slices j_begin +
+// kPfPair (r + m helpers), m = 0, 1, ...
 template <class T, int Interp>
 __device__ inline void pf_helper(const ComposeArgs &a, PfShared &sh,
-                                 const PfLayout<T, Interp == 4 ? 2 : 1> &lay, int r) {
+                                 const PfLayout &lay, int r) {
     constexpr int C = Interp == 4 ? 2 : 1, kSpan = PfNodes<Interp>::span;
     const int lane = int(threadIdx.x) & 63;
     const int n = a.n0;
     const unsigned slots = unsigned(lay.slots);
-    unsigned at = unsigned(kPfPair * r) % slots;       // the slot of s0
-    for (int s0 = a.j_begin + kPfPair * r; s0 < a.j_end; s0 += kPfPair * kPfHelpers,
-             at = (at + unsigned(kPfPair * kPfHelpers)) % slots) {
+    if (r >= lay.helpers) return;
+    const int round = kPfPair * lay.helpers;           // at most `slots`, which it divides
+    unsigned at = unsigned(kPfPair * r);               // the slot of s0
+    for (int s0 = a.j_begin + kPfPair * r; s0 < a.j_end;
+         s0 += round, at = pf_wrap(at + unsigned(round), slots)) {
         const int pair = s0 + 1 < a.j_end ? 2 : 1;
         if (!lay.rows && s0 < a.j_begin + kPfLead) continue;
         int p = 0;                     // the chain has finished every slice before p
@@ -744,8 +717,7 @@ __device__ inline void pf_helper(const ComposeArgs &a, PfShared &sh,
 template <class T, int Interp>
 __device__ inline void compose_range_staged(const ComposeArgs &a, PfShared &sh,
                                             double *final_out = nullptr) {
-    constexpr int C = Interp == 4 ? 2 : 1;
-    const PfLayout<T, C> lay(a.n0);
+    const PfLayout lay(a.n0, Interp == 4 ? 2 : 1, int(sizeof(T)));
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     if (threadIdx.x < kPfMaxSlots) sh.tag[threadIdx.x] = PfTag{-1, 0, 0, 0};
     if (threadIdx.x < 4) {
@@ -778,12 +750,6 @@ __device__ inline void compose_range_staged(const ComposeArgs &a, PfShared &sh,
 // per slice against 0.47, 0.48 and 0.51 us at 3, 4 and 6).  Cells and window origins are packed 16 bits per axis, so the path
 // serves grids of at most 65,536 points per axis; larger ones take the plain
 // chain.
-constexpr int kPf2Side = 16;                 // window cells per axis
-constexpr int kPf2Win = kPf2Side * kPf2Side;
-constexpr int kPf2Ahead = 2;
-constexpr int kPf2Slots = 15;                // the ring within 64 KB of LDS
-constexpr int kPf2MaxAxis = 65536;
-
 struct PfShared2 {
     double win[kPf2Slots][2][kPf2Win];       // [slot][component][row * 16 + column]
     long long tag[kPf2Slots];                // (slice << 32) | (base0 << 16) | base1; -1 empty

@@ -1,0 +1,76 @@
+"""The staging rings of the composition chains (csrc/chain_ring.h), on the CPU:
+every slot of a ring is filled by one wave only, so that a late load of one wave
+never lands in what another has staged."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1304_6514_amd", "csrc")
+
+SOURCE = r"""
+#include "chain_ring.h"
+using namespace nv::dev;
+extern "C" {
+void layout(int n, int comps, int elem, int *out) {
+    const PfLayout l(n, comps, elem);
+    const int v[] = {l.rows, l.width, l.slots, l.helpers, l.row_bytes, l.slot_bytes, l.ahead};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+void constants(int *out) {
+    const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead};
+    for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+}
+"""
+TABLES = [(comps, elem) for comps in (1, 2) for elem in (4, 8)]
+# every row up to well past the line between rows and windows, and longer ones
+SIZES = [*range(2, 4200), 8191, 65536, 1 << 20]
+
+
+class Ring:
+    def __init__(self, lib, n, comps, elem):
+        out = (ctypes.c_int * 7)()
+        lib.layout(n, comps, elem, out)
+        (self.rows, self.width, self.slots, self.helpers, self.row_bytes, self.slot_bytes,
+         self.ahead) = out
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("ring")
+    (d / "ring.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    str(d / "ring.cpp"), "-o", str(d / "ring.so")], check=True)
+    return ctypes.CDLL(str(d / "ring.so"))
+
+
+@pytest.fixture(scope="module")
+def const(lib):
+    out = (ctypes.c_int * 6)()
+    lib.constants(out)
+    return dict(zip(("pair", "helpers", "max_slots", "ring_bytes", "slots2", "ahead2"), out))
+
+
+@pytest.mark.parametrize("comps,elem", TABLES)
+def test_every_slot_has_one_owner(lib, const, comps, elem):
+    for n in SIZES:
+        r = Ring(lib, n, comps, elem)
+        assert 1 <= r.helpers <= const["helpers"] and r.slots <= const["max_slots"]
+        owner = {}
+        for s in range(6 * r.slots):                  # slices, from the range's first
+            wave = (s // const["pair"]) % r.helpers
+            assert owner.setdefault(s % r.slots, wave) == wave, (n, s)
+        # a slot is filled when the slice before it in the slot is finished
+        assert 0 < r.ahead < r.slots
+        assert r.slots * r.slot_bytes <= const["ring_bytes"]
+
+
+def test_every_slot_of_the_bilinear_ring_has_one_owner(const):
+    owner = {}
+    for s in range(6 * const["slots2"]):
+        wave = s % const["helpers"]
+        assert owner.setdefault(s % const["slots2"], wave) == wave
+    assert const["ahead2"] < const["slots2"]
