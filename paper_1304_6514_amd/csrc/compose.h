@@ -454,8 +454,11 @@ __device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_byte
     return at < tag.cells;
 }
 
-// The chain's progress: slice j finished, in cell `cell`.
+// The chain's progress: slice j finished, in cell `cell`.  The report frees slots,
+// so the reads of their values come before it: a wave's LDS operations are taken
+// in the order of its code, and the empty asm keeps the compiler to that order.
 __device__ inline void pf_report(PfShared &sh, int j, long long cell, int lane) {
+    asm volatile("" ::: "memory");
     const int q = (j / kPfPublish) & 3;
     __hip_atomic_store(&sh.hist[lane == 0 ? q : 4 + lane], pf_pack(j, cell), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -784,6 +787,7 @@ __device__ inline void pf2_chain(const ComposeArgs &a, PfShared2 &sh, double *fi
             const unsigned slot = unsigned(j) % kPf2Slots;
             const long long tg = uniform_i64(__hip_atomic_load(
                 &sh.tag[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            asm volatile("" ::: "memory");  // the values are read after their tag
             const int tag_slice = int(tg >> 32);
             const int b0 = int((tg >> 16) & 0xffff), b1 = int(tg & 0xffff);
             long long i0, i1;
@@ -825,6 +829,7 @@ __device__ inline void pf2_chain(const ComposeArgs &a, PfShared2 &sh, double *fi
             if (!finite(next0) || !finite(next1)) break;
             lam0 = next0;
             lam1 = next1;
+            asm volatile("" ::: "memory");  // the values are read before the report
             // slice j is done (its slot is reused for slice j + kPf2Slots, which
             // no helper fetches before the chain is past slice j + kPf2Slots -
             // kPf2Ahead)
