@@ -92,7 +92,8 @@ NV_API nv_status nv_lin_compose(nv_lin *lin, const double *y0, double *yT, doubl
  * fix (so results are within the FP64 inner-product rounding bound of any
  * order, not bit-equal to nv_lin_compose).
  *   y0_dev        device, count x M doubles (chain q's initial value at q M)
- *   yT_dev        device, count x M doubles: lambda^q_N
+ *   yT_dev        device, count x M doubles: lambda^q_N; may be y0_dev (the chains
+ *                 are then run slice by slice whatever their number of slices)
  *   boundary_dev  device, count x (N + 1) x M doubles, chain-major
  *                 (lambda^q_j at (q (N + 1) + j) M), or NULL
  * Synchronous.  Errors: INVALID_ARG (NULL pointers, count < 1), NOT_BUILT,

@@ -1087,9 +1087,17 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     NV_HIP(hipEventRecord(l->e2, l->stream));
     int bad = init;
     // by blocks (if one launch can number all its workgroups); then, should a
-    // state be beyond what that serves, slice by slice
+    // state be beyond what that serves, slice by slice.  The final states may
+    // overwrite the initial ones (a workgroup reads its chains before it writes
+    // them), but a second pass would then start from the first one's results: such
+    // a call takes the slices at once.
+    const size_t bytes = size_t(count) * l->M * sizeof(double);
+    const uintptr_t from = reinterpret_cast<uintptr_t>(y0_dev),
+                    to = reinterpret_cast<uintptr_t>(yT_dev);
+    const bool in_place = from < to + bytes && to < from + bytes;
     const long long most = ((count + 15) / 16) * many_rows((l->N + kBlock - 1LL) / kBlock);
-    for (int levels = boundary_dev && most > 0x7fffffffLL ? 0 : l->levels;; levels = 0) {
+    for (int levels = in_place || (boundary_dev && most > 0x7fffffffLL) ? 0 : l->levels;;
+         levels = 0) {
         if (levels > 0)
             NV_HIP(launch_products(l));
         else

@@ -1,0 +1,59 @@
+"""GPU parity of the affine basis propagator's less usual calls."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import linear_oracle as lo
+from paper_1304_6514_amd import nv
+from paper_1304_6514_amd.linear import HeatWorkload, LinearPropagator
+from test_gpu_linear import check_chain
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-test]", *a, file=sys.__stderr__, flush=True)
+
+
+@pytest.fixture(scope="module")
+def torch():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    nv.load()
+    return torch
+
+
+@pytest.mark.parametrize("N", [12, 100])
+@pytest.mark.parametrize("boundary", [False, True])
+def test_compose_many_in_place(torch, N, boundary):
+    """The final states may overwrite the initial ones (a workgroup reads its chains
+    before it writes them), also where a chain beyond 1e300, or one that is not finite,
+    takes the chains from the blocks' products back to the slices."""
+    M = 9
+    w = HeatWorkload("in-place", M, 0.01, N, T=0.01 * N)
+    rng = np.random.default_rng(5)
+    y0 = rng.normal(0.0, 1.0, (300, M))
+    for case in ("ordinary", "large", "nan"):
+        say("compose_many in place", N, boundary, case)
+        if case == "large":
+            y0[7] = 1e305
+        elif case == "nan":
+            y0[211, 3] = np.nan
+        with LinearPropagator() as lin:
+            lin.build(w)
+            G, c = lin.tables()
+            y = torch.from_numpy(y0).cuda()
+            b = torch.empty((300, N + 1, M), dtype=torch.float64, device="cuda") \
+                if boundary else None
+            torch.cuda.synchronize()
+            st = nv.nv_lin_compose_many(lin.h, y.data_ptr(), 300, y.data_ptr(),
+                                        b.data_ptr() if boundary else None)
+            assert st == (nv.NV_ERR_NONFINITE if case == "nan" else nv.NV_OK)
+            got = y.cpu().numpy()
+        for q in (0, 7, 15, 16, 299):
+            ref = lo.compose(G, c, y0[q])
+            check_chain(G, c, np.concatenate([ref[:-1], got[q:q + 1]]), ref, f"chain {q}")
+            if boundary:
+                check_chain(G, c, b[q].cpu().numpy(), ref, f"states of chain {q}")
