@@ -158,6 +158,9 @@ __global__ __launch_bounds__(128, MP <= 104 ? 2 : 1) void lin_build_kernel(Build
     // rows lane and 64 + lane of a step's coefficients (0 past row M - 1)
     const int r0 = lane < M ? lane : M - 1, r1 = 64 + lane < M ? 64 + lane : M - 1;
     const bool in0 = lane < M, in1 = 64 + lane < M;
+    // a forcing that is not finite: m times it would reach every lane, so it takes no
+    // part in the sweeps; the forced solve, and it alone, is not finite from there on
+    double lost = 0.0;
     const double s[2] = {in0 ? a.s[r0] : 0.0, in1 ? a.s[r1] : 0.0};
     double w[2], c[2];
     w[0] = a.w[q0 * M + r0];
@@ -166,7 +169,9 @@ __global__ __launch_bounds__(128, MP <= 104 ? 2 : 1) void lin_build_kernel(Build
     c[1] = a.c[q0 * M + r1];
     for (int st = 0; st < a.S_tot; ++st) {
         const long long q = q0 + st;
-        const double off = -a.step[2 * q], hb = a.step[2 * q + 1];
+        const double off = -a.step[2 * q], hb_step = a.step[2 * q + 1];
+        const double hb = isfinite(hb_step) ? hb_step : 0.0;
+        if (!isfinite(hb_step)) lost = hb_step;
         // the next step's coefficients (the last step reloads its own)
         const long long qn = st + 1 < a.S_tot ? q + 1 : q;
         const double wn[2] = {a.w[qn * M + r0], a.w[qn * M + r1]};
@@ -191,6 +196,8 @@ __global__ __launch_bounds__(128, MP <= 104 ? 2 : 1) void lin_build_kernel(Build
 #pragma unroll
     for (int i = 0; i < MP; i += 2)             // row M of an odd M is padding: 0
         if (i < M) col[i / 2] = double2{x[i], x[i + 1]};
+    if (solve == 0 && lost != 0.0)
+        for (int i = 0; i < M; ++i) blk[Ms * M + i] = lost;
 }
 
 template <int MP>

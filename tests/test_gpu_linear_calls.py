@@ -57,3 +57,21 @@ def test_compose_many_in_place(torch, N, boundary):
             check_chain(G, c, np.concatenate([ref[:-1], got[q:q + 1]]), ref, f"chain {q}")
             if boundary:
                 check_chain(G, c, b[q].cpu().numpy(), ref, f"states of chain {q}")
+
+
+def test_a_forcing_beyond_the_numbers_leaves_the_homogeneous_solves(torch):
+    """a(t) = 3e307: h a / dx^2 is finite, beta(t) = pi^2 a(t) cos t - sin t is not.
+    The forced solves (c) are not finite; the homogeneous ones (G) have no forcing
+    and are the oracle's to the bit."""
+    for M in (1, 3, 70):
+        w = HeatWorkload("beyond", M, 1e-5 / (M + 1) ** 2, 3, T=6e-5 / (M + 1) ** 2, a0=3e307,
+                         a1=0.0)
+        say("forcing beyond the numbers", M)
+        with LinearPropagator() as lin:
+            lin.build(w)
+            G, c = lin.tables()
+        with np.errstate(all="ignore"):
+            Go, co = lo.build_tables(M, w.a0, w.a1, True, w.t0, w.T, w.n_slices, w.dt)
+        assert np.all(np.isfinite(Go)) and not np.any(np.isfinite(co))
+        assert np.array_equal(G, Go)
+        assert not np.any(np.isfinite(c))
