@@ -16,6 +16,7 @@
 // slices ahead; one LDS exchange and one barrier per slice.  From kBlockedFrom
 // slices on it runs through products of the slices' maps, formed by
 // lin_many_kernel, which also carries many chains at once.
+#include "launch_limits.h"
 #include "nv_internal.h"
 #include "nv_linear.h"
 
@@ -32,6 +33,8 @@
 #include <vector>
 
 using nv::fail;
+using nv::lin::kBlock;
+using nv::lin::kXcds;
 
 #define NV_HIP(expr)                                                                    \
     do {                                                                                \
@@ -239,7 +242,6 @@ const LinBuildTable lin_build;
 //
 // A state or a map that exceeds kLargest (or is not finite) is reported by the
 // kernels, and the chains are then run slice by slice, which names the slice.
-constexpr int kBlock = 8;               // 16 was no faster: the first products take longer
 constexpr int kTopMaps = 16;            // fewer maps are not worth another level's launches
 constexpr int kBlockedFrom = 64;        // slices; below, the launches cost what the steps save
 constexpr double kLargest = 1e300;
@@ -479,17 +481,6 @@ struct ManyArgs {
     int blocks;                 // blocks of maps
 };
 
-// Workgroups of consecutive numbers run on the kXcds dies in turn, each with an
-// L2 of its own, while the column groups of one block of maps all read the
-// block's tables: block b's workgroups get numbers that are b modulo kXcds (the
-// last row of blocks is filled up with workgroups that return at once).  With
-// the groups of a block next to each other every table came from memory once
-// per group: the products of 1024 maps of 99 points 98 -> 91 us.
-constexpr int kXcds = 8;
-constexpr long long many_rows(long long blocks) {
-    return blocks == 1 ? 1 : (blocks + kXcds - 1) / kXcds * kXcds;
-}
-
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 template <int KP, int CB>
@@ -655,30 +646,22 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     if (bad != kNoSlice) atomicMin(a.bad, bad);
 }
 
-// With enough chains for two workgroups of two column blocks on every CU, a
-// workgroup carries two blocks that share its table reads; fewer chains keep
-// one block per workgroup, for more workgroups (measured at M = 99, 32 slices:
-// 16,384 chains 318 -> 281 us paired).  Two blocks need more registers: up to
-// KP = 26 (M <= 104) at most 128, with which two workgroups still fit a CU
-// (beyond, at M = 116, 48 slices, 20,000 chains: 712 us, 740 us paired).
-constexpr int kManyPairMaxKP = 26;
-
 template <int KP>
 void lin_launch_many(ManyArgs a, long long pair_from, hipStream_t st) {
+    using namespace nv::lin;
     const long long Q = a.product ? a.lv.M + 1 : a.Q;
     const long long blocks = a.lv.whole ? 1 : (a.lv.maps + kBlock - 1) / kBlock;
+    const bool paired = !a.product && many_paired(a.lv.M, Q, blocks, pair_from);
     a.blocks = int(blocks);
+    a.groups = int(many_groups(Q, paired));
+    const dim3 grid(unsigned(a.groups * many_rows(blocks)));
     if constexpr (KP <= kManyPairMaxKP) {
-        if (!a.product && Q * blocks >= pair_from && Q > 16) {
-            a.groups = int((Q + 31) / 32);
-            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), dim3(unsigned(a.groups * many_rows(blocks))),
-                               dim3(512), 0, st, a);
+        if (paired) {
+            hipLaunchKernelGGL((lin_many_kernel<KP, 2>), grid, dim3(kThreads), 0, st, a);
             return;
         }
     }
-    a.groups = int((Q + 15) / 16);
-    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), dim3(unsigned(a.groups * many_rows(blocks))),
-                       dim3(512), 0, st, a);
+    hipLaunchKernelGGL((lin_many_kernel<KP, 1>), grid, dim3(kThreads), 0, st, a);
 }
 
 using ManyLaunch = void (*)(ManyArgs, long long, hipStream_t);
@@ -962,12 +945,12 @@ NV_API nv_status nv_lin_build(nv_lin *l, const nv_heat *p, double t0, double T, 
     // the boundary states and the report, next to each other: one copy back
     const size_t o_b = off;    off = off + (size_t(n_slices) + 1) * M * 8;
     const size_t o_bad = off;  off = al(off + sizeof(double));
-    // the products of blocks of slices, level by level, where there is room for
-    // them (a seventh of the tables)
+    // the products of blocks of slices, level by level, where one launch can form
+    // them and there is room for them (a seventh of the tables)
     const size_t without = off;
     size_t o_prod[kMaxLevels] = {};
     int levels = 0;
-    if (n_slices >= kBlockedFrom && n_slices <= (1 << 30))
+    if (n_slices >= kBlockedFrom && nv::lin::products_fit(M, n_slices))
         for (int maps = n_slices; maps > kTopMaps && levels < kMaxLevels; ++levels) {
             maps = (maps + kBlock - 1) / kBlock;
             o_prod[levels] = off;
@@ -1093,7 +1076,7 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     a.Q = count;
     NV_HIP(hipEventRecord(l->e2, l->stream));
     int bad = init;
-    // by blocks (if one launch can number all its workgroups); then, should a
+    // by blocks (if one launch can hold the states inside them); then, should a
     // state be beyond what that serves, slice by slice.  The final states may
     // overwrite the initial ones (a workgroup reads its chains before it writes
     // them), but a second pass would then start from the first one's results: such
@@ -1102,9 +1085,8 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     const uintptr_t from = reinterpret_cast<uintptr_t>(y0_dev),
                     to = reinterpret_cast<uintptr_t>(yT_dev);
     const bool in_place = from < to + bytes && to < from + bytes;
-    const long long most = ((count + 15) / 16) * many_rows((l->N + kBlock - 1LL) / kBlock);
-    for (int levels = in_place || (boundary_dev && most > 0x7fffffffLL) ? 0 : l->levels;;
-         levels = 0) {
+    const bool fits = !boundary_dev || nv::lin::states_fit(l->M, l->N, count, pair_from);
+    for (int levels = in_place || !fits ? 0 : l->levels;; levels = 0) {
         if (levels > 0)
             NV_HIP(launch_products(l));
         else

@@ -75,3 +75,25 @@ def test_a_forcing_beyond_the_numbers_leaves_the_homogeneous_solves(torch):
         assert np.all(np.isfinite(Go)) and not np.any(np.isfinite(co))
         assert np.array_equal(G, Go)
         assert not np.any(np.isfinite(c))
+
+
+def test_more_chains_than_one_launch_by_blocks_holds(torch):
+    """2,200,000 chains of 1024 slices with their states (18 GB): over the blocks'
+    states this would be 8.8 million workgroups of 512, more than a launch holds;
+    the chains run slice by slice, as a few of them alone do through the blocks."""
+    w = HeatWorkload("many", 1, 0.01, 1024, T=10.24)
+    Q = 2_200_000
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GB of device memory")
+    say("compose_many", Q)
+    with LinearPropagator() as lin:
+        lin.build(w)
+        G, c = lin.tables()
+        y0 = torch.linspace(-1.0, 1.0, Q, dtype=torch.float64, device="cuda").reshape(Q, 1)
+        st, yT, b = lin.compose_many(y0, want_boundary=True)
+        assert st == nv.NV_OK
+        for q in (0, 31, 1_100_000, Q - 1):
+            got = b[q].cpu().numpy()
+            check_chain(G, c, got, lo.compose(G, c, y0[q].cpu().numpy()), f"chain {q}")
+            assert np.array_equal(yT[q].cpu().numpy(), got[-1])
+        del b
