@@ -2,6 +2,7 @@
 // matrix cores, weight-gradient sums, Adam), inference inside the composition,
 // and the training set drawn from the tables of the computation phase.
 #include "compose.h"
+#include "launch_limits.h"
 #include "mlp.h"
 #include "nv_surrogate.h"
 
@@ -1642,9 +1643,6 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
     fill_norm(s, a.shift, a.scale);
     a.os0 = s->cfg.out_scale[0];
     a.os1 = s->cfg.out_scale[1];
-    a.y0 = c->y0;
-    a.mu = c->mu;
-    a.count = c->count;
     a.t0 = c->t0;
     a.L = (c->T - c->t0) / double(c->n_slices);
     if (std::fabs(a.L - s->cfg.slice_length) > 1e-9 * s->cfg.slice_length)
@@ -1655,8 +1653,6 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
     a.tau2_0 = s->cfg.gate[0] * s->cfg.gate[0];
     a.tau2_1 = s->cfg.gate[1] * s->cfg.gate[1];
     a.n_slices = c->n_slices;
-    a.final_state = c->final_state;
-    a.boundary = c->boundary;
     a.blo0 = c->box_lo[0];
     a.blo1 = c->box_lo[1];
     a.bhi0 = c->box_hi[0];
@@ -1681,36 +1677,46 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
         a.inv0 = double(g.n[0] - 1) / (g.hi[0] - g.lo[0]);
         a.inv1 = double(g.n[1] - 1) / (g.hi[1] - g.lo[1]);
     }
-    const unsigned long long init[4] = {0ull, 0ull, 0ull, ~0ull};
-    NV_HIP(hipMemcpyAsync(s->stats, init, sizeof init, hipMemcpyHostToDevice, s->stream));
-    a.stats = s->stats;
     if ((c->count + 15) / 16 > 0x7fffffffLL) return fail(NV_ERR_INVALID_ARG, "too many chains");
     // as few chains per workgroup as keep one workgroup per CU (two of them take
     // longer than one of twice the chains: 1500 chains 1.44 us per slice in fours,
     // 1.21 in eights; 3000 chains 1.85 in eights, 1.57 in sixteens)
     const int per = c->count <= 4LL * s->n_cu ? 4 : (c->count <= 8LL * s->n_cu ? 8 : 16);
-    const unsigned blocks = unsigned((c->count + per - 1) / per);
-    NV_HIP(hipEventRecord(s->ev0, s->stream));
-    if (per == 4)
-        hipLaunchKernelGGL(sur_chain_kernel<4>, dim3(blocks), dim3(kChainThreads), 0, s->stream, a);
-    else if (per == 8)
-        hipLaunchKernelGGL(sur_chain_kernel<8>, dim3(blocks), dim3(kChainThreads), 0, s->stream, a);
-    else
-        hipLaunchKernelGGL(sur_chain_kernel<16>, dim3(blocks), dim3(kChainThreads), 0, s->stream,
-                           a);
-    NV_HIP(hipGetLastError());
-    NV_HIP(hipEventRecord(s->ev1, s->stream));
-    unsigned long long st[4];
-    NV_HIP(hipMemcpyAsync(st, s->stats, sizeof st, hipMemcpyDeviceToHost, s->stream));
-    NV_HIP(hipStreamSynchronize(s->stream));
-    NV_HIP(hipEventElapsedTime(&s->last_ms, s->ev0, s->ev1));
-    info->n_fallback = (long long)st[0];
-    info->n_outside = (long long)st[1];
-    double md;
-    std::memcpy(&md, &st[2], sizeof md);
-    info->max_deviation = md;
-    info->bad_chain = st[3] == ~0ull ? -1 : (long long)st[3];
-    info->ms = s->last_ms;
+    const auto run = per == 4   ? sur_chain_kernel<4>
+                     : per == 8 ? sur_chain_kernel<8>
+                                : sur_chain_kernel<16>;
+    *info = nv_sur_compose_info{};
+    info->bad_chain = -1;
+    a.stats = s->stats;
+    // one launch, or several of as many chains as one can hold
+    const long long most = nv::max_workgroups(kChainThreads) * per;
+    for (long long first = 0; first < c->count; first += most) {
+        a.count = std::min(most, c->count - first);
+        a.y0 = c->y0 + 2 * first;
+        a.mu = c->mu + first;
+        a.final_state = c->final_state + 2 * first;
+        a.boundary = c->boundary ? c->boundary + 2 * first * (c->n_slices + 1LL) : nullptr;
+        const unsigned long long init[4] = {0ull, 0ull, 0ull, ~0ull};
+        NV_HIP(hipMemcpyAsync(s->stats, init, sizeof init, hipMemcpyHostToDevice, s->stream));
+        NV_HIP(hipEventRecord(s->ev0, s->stream));
+        hipLaunchKernelGGL(run, dim3(unsigned((a.count + per - 1) / per)), dim3(kChainThreads), 0,
+                           s->stream, a);
+        NV_HIP(hipGetLastError());
+        NV_HIP(hipEventRecord(s->ev1, s->stream));
+        unsigned long long st[4];
+        NV_HIP(hipMemcpyAsync(st, s->stats, sizeof st, hipMemcpyDeviceToHost, s->stream));
+        NV_HIP(hipStreamSynchronize(s->stream));
+        float ms = 0.f;
+        NV_HIP(hipEventElapsedTime(&ms, s->ev0, s->ev1));
+        double md;
+        std::memcpy(&md, &st[2], sizeof md);
+        info->n_fallback += (long long)st[0];
+        info->n_outside += (long long)st[1];
+        info->max_deviation = std::max(info->max_deviation, md);
+        if (info->bad_chain < 0 && st[3] != ~0ull) info->bad_chain = first + (long long)st[3];
+        info->ms += ms;
+    }
+    s->last_ms = info->ms;
     if (info->bad_chain >= 0)
         return fail(NV_ERR_NONFINITE, "chain %lld became non-finite", info->bad_chain);
     return NV_OK;
