@@ -423,7 +423,9 @@ __device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_byte
     asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(fl));
     const unsigned at = unsigned(i - PfNodes<Interp>::below - tag.base);
     const unsigned o = (at < tag.cells ? at : tag.cells) + tag.shift;
-    const double w = u - fl;
+    // u - cell with the cell as a whole number, which is +0 where fl is -0 (u = -0
+    // keeps its sign in w)
+    const double w = u - (fl + 0.0);
     const T *e = slot + o;
     if constexpr (Interp == 0) {
         const double ta = double(e[0]), tb = double(e[1]);

@@ -1,0 +1,59 @@
+"""GPU parity of the 1-D composition chain where its lookups meet the grid's ends."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1304_6514_amd import nv
+from paper_1304_6514_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[gpu-test]", *a, file=sys.__stderr__, flush=True)
+
+
+@pytest.fixture(scope="module")
+def torch():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    nv.load()
+    return torch
+
+
+def compose_both(orc, torch, tab, precision, interp, y0, lo, hi):
+    from paper_1304_6514_amd.propagator import Propagator
+    C, N, n = tab.shape
+    tab = tab.astype(np.float32 if precision == "fp32" else np.float64)
+    w = W.Workload("chain", "linear", (0.5,), 0.0, 1.0, N, (n,), (lo,), (hi,), 1, (y0,),
+                   precision, interp)
+    with Propagator("cuda:0") as p:
+        p.build(w)
+        for c in range(C):
+            p.table_tensor(c).copy_(torch.from_numpy(tab[c]))
+        torch.cuda.synchronize()
+        r = p.compose(y0)
+    o = orc.compose_tables(orc.make_grid((n,), (lo,), (hi,)), interp, tab.astype(np.float64),
+                           (y0,))
+    assert r.status == nv.NV_OK and o.status == 0
+    assert r.n_out_of_grid == o.n_out_of_grid
+    assert np.array_equal(r.boundary.view(np.int64), o.boundary.view(np.int64))
+    return r
+
+
+@pytest.mark.parametrize("n", [64, 9000])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("interp", ["linear", "hermite", "hermite_slopes"])
+def test_the_sign_of_a_zero_is_kept(orc, torch, n, precision, interp):
+    """A state of -0.0 at a grid that starts at 0, over tables that hold -0.0 there:
+    u = -0.0 lies in cell 0 at w = u - 0 = -0.0, and the state stays -0.0."""
+    say("sign of zero", n, precision, interp)
+    x = np.linspace(0.0, 1.0, n)
+    val = np.tile(-0.9 * x if interp != "linear" else 0.9 * x, (100, 1))
+    val[:, 0] = -0.0
+    tab = np.stack([val, np.full_like(val, 0.9)]) if interp == "hermite_slopes" else val[None]
+    r = compose_both(orc, torch, tab, precision, interp, -0.0, 0.0, 1.0)
+    if interp == "linear":
+        assert np.all(np.signbit(r.boundary))
