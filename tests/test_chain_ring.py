@@ -20,8 +20,8 @@ void layout(int n, int comps, int elem, int *out) {
     for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
 void constants(int *out) {
-    const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead};
-    for (int i = 0; i < 6; ++i) out[i] = v[i];
+    const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead, kPfWin};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
 }
 """
@@ -49,9 +49,9 @@ def lib(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def const(lib):
-    out = (ctypes.c_int * 6)()
+    out = (ctypes.c_int * 7)()
     lib.constants(out)
-    return dict(zip(("pair", "helpers", "max_slots", "ring_bytes", "slots2", "ahead2"), out))
+    return dict(zip(("pair", "helpers", "max_slots", "ring_bytes", "slots2", "ahead2", "window"), out))
 
 
 @pytest.mark.parametrize("comps,elem", TABLES)
@@ -74,3 +74,19 @@ def test_every_slot_of_the_bilinear_ring_has_one_owner(const):
         wave = s % const["helpers"]
         assert owner.setdefault(s % const["slots2"], wave) == wave
     assert const["ahead2"] < const["slots2"]
+
+
+@pytest.mark.parametrize("comps,elem", TABLES)
+def test_a_window_holds_the_narrowest_one_and_its_slack(lib, const, comps, elem):
+    """A helper stages a window of at least kPfWin nodes, or none: a slot that is
+    narrower would never serve a slice."""
+    seen = 0
+    for n in SIZES:
+        r = Ring(lib, n, comps, elem)
+        assert r.row_bytes >= r.width * elem + 15 and r.row_bytes % 16 == 0   # any alignment
+        assert r.slot_bytes == comps * r.row_bytes
+        if not r.rows:
+            seen += 1
+            assert const["window"] <= r.width < n
+            assert r.slots > r.ahead
+    assert seen
