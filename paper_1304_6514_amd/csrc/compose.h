@@ -9,6 +9,7 @@
 #include "nv_internal.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace nv {
 namespace dev {
@@ -279,7 +280,9 @@ __device__ inline void compose_range_bilinear(const ComposeArgs &a, double *fina
 // in groups of four without a branch; the state stays in vector registers;
 // the cell is floor(u) itself, and a lookup outside the grid or the slot (the
 // one unsigned comparison) is noticed after the group, which is then taken
-// again slice by slice; no value is tested for finiteness inside a block of 64
+// again with the general lookup (clamped and counted, one-sided slopes at the
+// row's ends), still from the slots, and slice by slice from global memory only
+// where a slot does not hold its slice's nodes; no value is tested for finiteness inside a block of 64
 // slices, and the helpers are told of the progress once per group.  A state
 // that is not finite stays so (every interpolant turns an infinite or NaN
 // coordinate into one), so it is found at the end of its block at the latest,
@@ -288,7 +291,10 @@ __device__ inline void compose_range_bilinear(const ComposeArgs &a, double *fina
 // nodes only, every value tested): 4096 slices of 4096 FP32 nodes, cubic
 // Hermite, windows 0.33 -> 0.18 us; of 1000 nodes, linear, rows 0.27 -> 0.13 us;
 // 301 slices of 1501 nodes with slopes, rows of 12 KB, 0.37 -> 0.25 us; 1024
-// slices of 8192 nodes whose cells cannot be predicted, 0.43 -> 0.41 us.
+// slices of 8192 nodes whose cells cannot be predicted, 0.43 -> 0.41 us.  A state
+// that rests at the end of the grid or outside it, rows of 1000 nodes: linear
+// 0.28 -> 0.17 us, cubic Hermite 0.43 -> 0.29 us (slice by slice after each group
+// it was 0.63 and 0.77 us).
 constexpr int kPfLead = 12;                // a windowed chain's first slices are not staged, and
 constexpr int kPfSeen = 8;                 // this many of them are finished before later ones are
 constexpr int kPfPolls = 24;               // polls the chain waits for a group's slots
@@ -411,30 +417,62 @@ struct PfFields {
 // One slice from state lam out of a slot that holds the nodes of tag.cells
 // cells from node tag.base on.  next is the new state when lam's cell is one of them
 // (the result, the same in every lane); otherwise a value that means nothing
-// is formed from what the ring holds at the first cell past them.
-template <class T, int Interp>
-__device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_bytes,
-                                const ComposeArgs &a, double lam, double &next, int &i) {
+// is formed from what the ring holds at the first cell past them.  With Ends the
+// lookup is the general one: the cell is clamped to the grid, a state outside it is
+// counted, and the cells at the row's ends take their one-sided slopes.
+template <class T, int Interp, bool Ends>
+__device__ inline bool pf_slice(const T *slot, const PfFields &tag, const PfLayout &lay,
+                                const ComposeArgs &a, double lam, double &next, int &i,
+                                int &oog) {
 #pragma clang fp contract(off)
-    const double u = (lam - a.lo0) * a.inv0;
-    const double fl = floor(u);
-    // the hardware's conversion saturates (and gives 0 for a NaN), where the
-    // language leaves a value outside the integer's range undefined
-    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(fl));
-    const unsigned at = unsigned(i - PfNodes<Interp>::below - tag.base);
-    const unsigned o = (at < tag.cells ? at : tag.cells) + tag.shift;
-    // u - cell with the cell as a whole number, which is +0 where fl is -0 (u = -0
-    // keeps its sign in w)
-    const double w = u - (fl + 0.0);
-    const T *e = slot + o;
+    double w;
+    int first;                  // the first node that is read
+    unsigned at;                // and its place in the slot, `within` of which are served
+    unsigned within = tag.cells;
+    if constexpr (Ends) {
+        long long cell;
+        oog += locate(a.lo0, a.inv0, a.n0, lam, cell, w);
+        i = int(cell);
+        first = Interp == 1 ? int(node_below(cell)) : i;
+        const int last = Interp == 1 ? int(node_above(cell, a.n0)) : i + 1;
+        // a row holds every cell; a window holds `cells` + span - 1 nodes
+        const unsigned nodes = lay.rows ? unsigned(a.n0)
+                                        : tag.cells + unsigned(PfNodes<Interp>::span - 1);
+        at = unsigned(first - tag.base);
+        within = lay.rows || tag.cells != 0 ? nodes - unsigned(last - first) : 0;
+    } else {
+        const double u = (lam - a.lo0) * a.inv0;
+        const double fl = floor(u);
+        // the hardware's conversion saturates (and gives 0 for a NaN), where the
+        // language leaves a value outside the integer's range undefined
+        asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(fl));
+        // u - cell with the cell as a whole number, which is +0 where fl is -0 (u = -0
+        // keeps its sign in w)
+        w = u - (fl + 0.0);
+        first = i - PfNodes<Interp>::below;
+        at = unsigned(first - tag.base);
+    }
+    const T *e = slot + ((at < within ? at : within) + tag.shift);
     if constexpr (Interp == 0) {
         const double ta = double(e[0]), tb = double(e[1]);
         next = ta + w * (tb - ta);
     } else {
         double ta, tb, da, db;
-        const T e0 = e[0], e1 = e[1];
-        const T *f = Interp == 4 ? e + row_bytes / int(sizeof(T)) : e + 2;
-        const T f0 = f[0], f1 = f[1];
+        T e0, e1, f0, f1;
+        if constexpr (Ends && Interp == 1) {
+            // nodes i - 1 .. i + 2, those past the row's ends replaced by its last ones
+            const int up = i + 2 < a.n0 ? 2 : 1, down = i > 0 ? 1 : 0;
+            e0 = e[0];
+            e1 = e[down];
+            f0 = e[down + 1];
+            f1 = e[down + up];
+        } else {
+            e0 = e[0];
+            e1 = e[1];
+            const T *f = Interp == 4 ? e + lay.row_bytes / int(sizeof(T)) : e + 2;
+            f0 = f[0];
+            f1 = f[1];
+        }
         // the weights do not depend on the table: formed while the reads are
         // in flight (the empty asm keeps them there)
         HermiteBasis hb = hermite_basis(w);
@@ -444,6 +482,10 @@ __device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_byte
             tb = double(e1);
             da = a.dxi0 * double(f0);
             db = a.dxi0 * double(f1);
+        } else if constexpr (Ends) {
+            interp_1d_values<1>(double(e0), double(e1), double(f0), double(f1), i, w, hb, a.n0,
+                                next);
+            return at < within;
         } else {
             const double tm = double(e0), tp = double(f1);
             ta = double(e1);
@@ -453,7 +495,7 @@ __device__ inline bool pf_slice(const T *slot, const PfFields &tag, int row_byte
         }
         next = ((hb.h00 * ta + hb.h10 * da) + hb.h01 * tb) + hb.h11 * db;
     }
-    return at < tag.cells;
+    return at < within;
 }
 
 // The chain's progress: slice j finished, in cell `cell`.  The report frees slots,
@@ -480,8 +522,44 @@ __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
     const int j_begin = a.j_begin, j_end = a.j_end;
     const int lq = lane & (kGroup - 1);
     int oog = 0, bad_slice = -1, backoff = lay.rows ? 0 : kPfLead;
+    int ends_run = 0;                   // one less than the groups taken with the general lookup
     int staged_from = lay.rows ? j_begin : j_begin + kPfLead;   // groups are tried from here on
     int j = j_begin;
+    PfTag tag;                          // lane l: of slice j + l % kGroup
+    // The group's slots hold its slices; slots that are about to be filled are waited for,
+    // a bounded number of polls: less than the general path would take.
+    const auto there = [&](int j) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(tag.x != j + lq) != 0, 0)) {
+            bool now = false;
+#pragma unroll 1
+            for (int spin = 0; spin < kPfPolls && !now; ++spin) {
+                tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
+                now = __builtin_amdgcn_ballot_w64(tag.x != j + lq) == 0;
+            }
+            return now;
+        }
+        return true;
+    };
+    // kGroup slices from state l without a branch; the next group's tags are read half way.
+    // All ones when every slice was served.
+    const auto group = [&](auto ends, int j, int jb, double &l, int &i, int &out, double &keep) {
+        const PfTag now = tag;
+        asm volatile("" ::: "memory");  // the values are read after their tags
+        unsigned long long served = ~0ull;
+#pragma unroll
+        for (int q = 0; q < kGroup; ++q) {
+            if (q == kGroup / 2)
+                tag = pf_tag(sh.tag, pf_wrap(at + unsigned(kGroup + lq), slots));
+            double next;
+            served &= __builtin_amdgcn_ballot_w64(pf_slice<T, Interp, decltype(ends)::value>(
+                reinterpret_cast<const T *>(sh.ring + pf_wrap(at + unsigned(q), slots) *
+                                                          unsigned(lay.slot_bytes)),
+                PfFields(now, q), lay, a, l, next, i, out));
+            l = next;
+            if (lane == j + q - jb) keep = l;
+        }
+        return served;
+    };
     // the first slot, if its helper delivers it within a bounded number of polls
     if (lay.rows) pf_wait(sh.tag, 0, j);
     while (j < j_end && bad_slice < 0) {
@@ -493,46 +571,43 @@ __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
         double keep = 0.0;
         bool failed = false;
         while (j < stop) {
-            // kGroup slices without a branch, lane l holding the tag of slice
-            // j + l % kGroup; the next group's tags are read half way
             j = __builtin_amdgcn_readfirstlane(j);
             at = unsigned(__builtin_amdgcn_readfirstlane(int(at)));
-            PfTag tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
+            const int j_first = j;
+            // groups of slices within the grid, lane l holding the tag of slice
+            // j + l % kGroup
+            tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
             while (j >= staged_from && j + kGroup <= stop) {
-                // slots that are about to be filled are waited for, a bounded
-                // number of polls: less than the general path would take
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(tag.x != j + lq) != 0, 0)) {
-                    bool there = false;
-#pragma unroll 1
-                    for (int spin = 0; spin < kPfPolls && !there; ++spin) {
-                        tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
-                        there = __builtin_amdgcn_ballot_w64(tag.x != j + lq) == 0;
-                    }
-                    if (!there) break;
-                }
-                const PfTag now = tag;
-                asm volatile("" ::: "memory");  // the values are read after their tags
-                unsigned long long served = ~0ull;
+                if (!there(j)) break;
                 double l = lam;
-                int i = 0;
-#pragma unroll
-                for (int q = 0; q < kGroup; ++q) {
-                    if (q == kGroup / 2)
-                        tag = pf_tag(sh.tag, pf_wrap(at + unsigned(kGroup + lq), slots));
-                    double next;
-                    served &= __builtin_amdgcn_ballot_w64(pf_slice<T, Interp>(
-                        reinterpret_cast<const T *>(sh.ring + pf_wrap(at + unsigned(q), slots) *
-                                                                  unsigned(lay.slot_bytes)),
-                        PfFields(now, q), lay.row_bytes, a, l, next, i));
-                    l = next;
-                    if (lane == j + q - jb) keep = l;
-                }
+                int i = 0, none = 0;
+                const unsigned long long served = group(std::false_type(), j, jb, l, i, none, keep);
                 if (__builtin_expect(served == 0, 0)) break;    // the same in every lane
                 lam = l;
                 j += kGroup;
-                backoff = 0;
                 at = pf_wrap(at + kGroup, slots);
                 pf_report(sh, j - 1, i, lane);
+            }
+            if (j != j_first) backoff = ends_run = 0;
+            // groups with the general lookup, a growing number of them while no group of
+            // the others comes between
+            int done_at_ends = 0;
+            while (done_at_ends <= ends_run && j >= staged_from && j + kGroup <= stop) {
+                tag = pf_tag(sh.tag, pf_wrap(at + unsigned(lq), slots));
+                if (!there(j)) break;
+                double l = lam;
+                int i = 0, out = 0;
+                if (group(std::true_type(), j, jb, l, i, out, keep) == 0) break;
+                lam = l;
+                oog += out;
+                j += kGroup;
+                at = pf_wrap(at + kGroup, slots);
+                pf_report(sh, j - 1, i, lane);
+                ++done_at_ends;
+            }
+            if (done_at_ends != 0) {
+                ends_run = ends_run < 8 ? 2 * ends_run + 1 : 15;
+                continue;
             }
             // Slices that the slots do not serve, one at a time: those of this
             // group, each from its slot where that has it after all (a staged
@@ -561,10 +636,11 @@ __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
                     if (__builtin_amdgcn_readfirstlane(tg.x) == j) {
                         double next;
                         int i;
-                        done = __builtin_amdgcn_ballot_w64(pf_slice<T, Interp>(
+                        int out = 0;
+                        done = __builtin_amdgcn_ballot_w64(pf_slice<T, Interp, false>(
                                    reinterpret_cast<const T *>(sh.ring +
                                                                at * unsigned(lay.slot_bytes)),
-                                   PfFields(tg, 0), lay.row_bytes, a, lam, next, i)) != 0;
+                                   PfFields(tg, 0), lay, a, lam, next, i, out)) != 0;
                         if (done) {
                             lam = next;
                             cell = i;
