@@ -75,21 +75,20 @@ __global__ void __launch_bounds__(kBuildBlock)
 template <class T>
 __global__ __launch_bounds__(kPfThreads) void batch_compose_kernel(
     const BatchProblem *__restrict__ probs, int count) {
-    __shared__ union {
-        PfShared one;
-        PfShared2 two;
-    } sh;
+    extern __shared__ __attribute__((aligned(16))) unsigned char pf_lds[];
+    PfShared &one = *reinterpret_cast<PfShared *>(pf_lds);
+    PfShared2 &two = *reinterpret_cast<PfShared2 *>(pf_lds);
     const int b = int(blockIdx.x);
     if (b >= count) return;
     const BatchProblem &pr = probs[b];
     const bool windows = pr.compose.n0 <= kPf2MaxAxis && pr.compose.n1 <= kPf2MaxAxis;
     double fin[2] = {0.0, 0.0};
     switch (pr.interp) {
-    case NV_INTERP_LINEAR: compose_range_staged<T, 0>(pr.compose, sh.one, fin); break;
-    case NV_INTERP_HERMITE: compose_range_staged<T, 1>(pr.compose, sh.one, fin); break;
+    case NV_INTERP_LINEAR: compose_range_staged<T, 0>(pr.compose, one, fin); break;
+    case NV_INTERP_HERMITE: compose_range_staged<T, 1>(pr.compose, one, fin); break;
     default:
         if (windows)
-            compose_range_staged2<T>(pr.compose, sh.two, fin);
+            compose_range_staged2<T>(pr.compose, two, fin);
         else if (threadIdx.x < 64)
             compose_range_bilinear<T>(pr.compose, fin);
         break;
@@ -119,15 +118,22 @@ hipError_t launch_batch_build(int precision, int accumulation, const BatchProble
     return hipGetLastError();
 }
 
-hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count,
+// LDS of the workgroup that composes the problem.
+size_t batch_compose_lds(const BatchProblem &p, int precision) {
+    const ComposeArgs &c = p.compose;
+    if (p.dim == 2)
+        return c.n0 <= kPf2MaxAxis && c.n1 <= kPf2MaxAxis ? sizeof(PfShared2) : 0;
+    return size_t(PfLayout(c.n0, 1, precision == NV_FP64 ? 8 : 4).lds_bytes());
+}
+
+hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, size_t lds,
                                 hipStream_t s) {
     if (count <= 0) return hipSuccess;
+    const dim3 grid{unsigned(count)}, block(kPfThreads);
     if (precision == NV_FP64)
-        hipLaunchKernelGGL((batch_compose_kernel<double>), dim3(unsigned(count)), dim3(kPfThreads), 0,
-                           s, probs, count);
+        hipLaunchKernelGGL((batch_compose_kernel<double>), grid, block, lds, s, probs, count);
     else
-        hipLaunchKernelGGL((batch_compose_kernel<float>), dim3(unsigned(count)), dim3(kPfThreads), 0,
-                           s, probs, count);
+        hipLaunchKernelGGL((batch_compose_kernel<float>), grid, block, lds, s, probs, count);
     return hipGetLastError();
 }
 
@@ -296,7 +302,11 @@ nv_status ensure_graph(nv_batch *b) {
     if (e == hipSuccess)
         e = nv::launch_batch_build(b->precision, b->accumulation, probs, items, b->n_items, counter,
                                    kCus * b->sched.workgroups_per_cu, b->stream);
-    if (e == hipSuccess) e = nv::launch_batch_compose(b->precision, probs, b->count, b->stream);
+    size_t lds = 0;
+    for (const nv::BatchProblem &p : b->hp)
+        lds = std::max(lds, nv::batch_compose_lds(p, b->precision));
+    if (e == hipSuccess)
+        e = nv::launch_batch_compose(b->precision, probs, b->count, lds, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->stage, b->work + b->off_status,
                            b->off_result - b->off_status + size_t(b->count) * 2 * sizeof(double),

@@ -23,7 +23,9 @@ namespace dev {
 constexpr int kPfHelpers = 8;              // helper waves
 constexpr int kPfThreads = 64 * (1 + kPfHelpers);
 constexpr int kPfMaxSlots = 32;            // slots of the ring, at most
-constexpr int kPfRingBytes = 152 * 1024;
+constexpr int kPfRingBytes = 148 * 1024;   // of the ring, at most,
+constexpr int kPfManyBytes = 64 * 1024;    // and with more slots than a round's
+constexpr int kPfControlBytes = 1312;      // tags and reports, in front of it
 constexpr int kPfRowBytes = 12 * 1024;     // rows shorter than this are staged whole
 constexpr int kPfWin = 256;                // nodes of the narrowest window
 // A window's slot: 4 KB, which hold 1016 to 504 nodes of up to 8 bytes; 8 KB where a node
@@ -32,6 +34,19 @@ constexpr int kPfWin = 256;                // nodes of the narrowest window
 NV_HOST_DEVICE constexpr int pf_window_bytes(int node) { return node <= 8 ? 4 * 1024 : 8 * 1024; }
 constexpr int kPfAhead = 14;               // a window is fetched this many slices ahead
 constexpr int kPfPair = 2;                 // slices a helper stages in one turn
+
+// How much LDS.  The chain of an overlapped solve starts beside a build whose
+// workgroups fill every CU, eight each, with a granule of 1280 bytes of LDS apiece at
+// the bottom of the CU's 160 KB.  It gets in when three of the eight have ended (their
+// twelve waves make room for its nine), wherever the others' granules lie, as long as it
+// asks for no more than what lies above all eight, 153,600 bytes.  With 157,024 bytes
+// it had to wait for the three topmost granules to be free at once: of the headline
+// solve (4096 slices of 4096 points, linear, 7.96 ms a step with the first chain's 33 KB),
+// 0.32 ms of composition was left when the build ended, and the step took 8.52 ms.  The
+// ring therefore takes what its table needs: a round of slots (windows are fetched at most
+// kPfAhead slices ahead), two where those fit 64 KB.
+constexpr int kPfBesideBuild = 160 * 1024 - 8 * 1280;
+static_assert(kPfControlBytes + kPfRingBytes + 64 <= kPfBesideBuild, "beside a running build");
 
 // The ring's layout for a table of n nodes of elem bytes per row and rows per
 // slice (2 when slopes are stored).
@@ -53,6 +68,7 @@ struct PfLayout {
         constexpr int kRound = kPfPair * kPfHelpers;
         slots = kPfRingBytes / slot_bytes;
         slots = slots < kPfMaxSlots ? slots : kPfMaxSlots;
+        if (slots > kRound && (!rows || slots * slot_bytes > kPfManyBytes)) slots = kRound;
         // one owner per slot: whole rounds, of fewer helpers where the ring does
         // not hold a round of all
         slots = slots >= kRound ? slots / kRound * kRound : slots / kPfPair * kPfPair;
@@ -60,6 +76,10 @@ struct PfLayout {
         // a slot is free once the slice `slots` before has been finished;
         // windows wait longer, for the prediction's sake
         ahead = rows || slots <= kPfAhead ? slots - 1 : kPfAhead;
+    }
+    // LDS of the chain's workgroup (the last slot's reads may pass its end)
+    NV_HOST_DEVICE constexpr int lds_bytes() const {
+        return kPfControlBytes + slots * slot_bytes + 64;
     }
 };
 

@@ -308,7 +308,6 @@ typedef int PfTag __attribute__((ext_vector_type(4)));      // slice, base, cell
 typedef __attribute__((address_space(3))) volatile PfTag PfLdsTag;
 
 struct PfShared {
-    alignas(16) unsigned char ring[kPfRingBytes + 64];
     PfTag tag[kPfMaxSlots];
     // the chain's reports, written by its whole wave without a branch: lane 0's
     // words are the report, the other lanes' (from index 4 and 1 on) are not read
@@ -316,7 +315,10 @@ struct PfShared {
                                    // slice j in hist[(j / kPfPublish) % 4]
     int past[64];                  // past[0]: every slice before this one is finished (the
                                    // largest integer once the chain has ended)
+    // the slots lie behind it
+    __device__ unsigned char *ring() { return reinterpret_cast<unsigned char *>(this + 1); }
 };
+static_assert(sizeof(PfShared) == kPfControlBytes && kPfControlBytes % 16 == 0, "the ring's layout");
 
 // The value of the wave's first active lane, held in scalar registers.  The
 // chain computes the same values in every lane; taking them from one lane
@@ -552,7 +554,7 @@ __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
                 tag = pf_tag(sh.tag, pf_wrap(at + unsigned(kGroup + lq), slots));
             double next;
             served &= __builtin_amdgcn_ballot_w64(pf_slice<T, Interp, decltype(ends)::value>(
-                reinterpret_cast<const T *>(sh.ring + pf_wrap(at + unsigned(q), slots) *
+                reinterpret_cast<const T *>(sh.ring() + pf_wrap(at + unsigned(q), slots) *
                                                           unsigned(lay.slot_bytes)),
                 PfFields(now, q), lay, a, l, next, i, out));
             l = next;
@@ -638,7 +640,7 @@ __device__ inline void pf_chain(const ComposeArgs &a, PfShared &sh,
                         int i;
                         int out = 0;
                         done = __builtin_amdgcn_ballot_w64(pf_slice<T, Interp, false>(
-                                   reinterpret_cast<const T *>(sh.ring +
+                                   reinterpret_cast<const T *>(sh.ring() +
                                                                at * unsigned(lay.slot_bytes)),
                                    PfFields(tg, 0), lay, a, lam, next, i, out)) != 0;
                         if (done) {
@@ -778,7 +780,7 @@ __device__ inline void pf_helper(const ComposeArgs &a, PfShared &sh,
                         (long long)(s0 + t) * a.M + base[t]);
                     const int over = int(reinterpret_cast<uintptr_t>(row) & 15);
                     shift[t] = over / int(sizeof(T));   // the same for both components
-                    pf_copy(row - over, sh.ring + slot * unsigned(lay.slot_bytes) +
+                    pf_copy(row - over, sh.ring() + slot * unsigned(lay.slot_bytes) +
                                             unsigned(c * lay.row_bytes),
                             over + width[t] * int(sizeof(T)), lane);
                 }

@@ -29,18 +29,18 @@ __global__ void compose_kernel(ComposeArgs a) {
 }
 
 // The 1-D chain with its table windows staged in LDS by helper waves: one
-// workgroup of 1 + kPfHelpers waves.
+// workgroup of 1 + kPfHelpers waves, with the LDS that the table's layout takes.
 template <class T, int Interp>
 __global__ __launch_bounds__(kPfThreads) void compose_staged_kernel(ComposeArgs a) {
-    __shared__ PfShared sh;
+    extern __shared__ __attribute__((aligned(16))) unsigned char pf_lds[];
     if (blockIdx.x != 0) return;
-    compose_range_staged<T, Interp>(a, sh);
+    compose_range_staged<T, Interp>(a, *reinterpret_cast<PfShared *>(pf_lds));
 }
 
 // The bilinear chain with its windows staged in LDS: one workgroup of
 // 1 + kPfHelpers waves.
 template <class T>
-__global__ __launch_bounds__(64 * (1 + kPfHelpers)) void compose_staged2_kernel(ComposeArgs a) {
+__global__ __launch_bounds__(kPfThreads) void compose_staged2_kernel(ComposeArgs a) {
     __shared__ PfShared2 sh;
     if (blockIdx.x != 0) return;
     compose_range_staged2<T>(a, sh);
@@ -59,40 +59,38 @@ __global__ void locate_kernel(double lo, double inv, int n, const double *x, lon
 
 }  // namespace
 
-hipError_t launch_compose(int interp, int precision, const ComposeArgs &a, hipStream_t s) {
-    const dim3 grid(1), block(64), staged(kPfThreads), staged_2d(64 * (1 + kPfHelpers));
+namespace {
+
+template <class T>
+hipError_t launch_compose_of(int interp, const ComposeArgs &a, hipStream_t s) {
+    const dim3 grid(1), block(64), staged(kPfThreads);
+    const size_t lds =
+        interp == 2 || interp == 3
+            ? 0
+            : size_t(PfLayout(a.n0, interp == 4 ? 2 : 1, int(sizeof(T))).lds_bytes());
     // cells and window origins of the staged bilinear chain are packed 16 bits per axis
     const bool staged2 = a.n0 <= kPf2MaxAxis && a.n1 <= kPf2MaxAxis;
-    if (precision == 0) {
-        switch (interp) {
-        case 0: hipLaunchKernelGGL((compose_staged_kernel<double, 0>), grid, staged, 0, s, a); break;
-        case 1: hipLaunchKernelGGL((compose_staged_kernel<double, 1>), grid, staged, 0, s, a); break;
-        case 2:
-            if (staged2)
-                hipLaunchKernelGGL((compose_staged2_kernel<double>), grid, staged_2d, 0, s, a);
-            else
-                hipLaunchKernelGGL((compose_kernel<double, 2>), grid, block, 0, s, a);
-            break;
-        case 3: hipLaunchKernelGGL((compose_kernel<double, 3>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((compose_staged_kernel<double, 4>), grid, staged, 0, s, a); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        switch (interp) {
-        case 0: hipLaunchKernelGGL((compose_staged_kernel<float, 0>), grid, staged, 0, s, a); break;
-        case 1: hipLaunchKernelGGL((compose_staged_kernel<float, 1>), grid, staged, 0, s, a); break;
-        case 2:
-            if (staged2)
-                hipLaunchKernelGGL((compose_staged2_kernel<float>), grid, staged_2d, 0, s, a);
-            else
-                hipLaunchKernelGGL((compose_kernel<float, 2>), grid, block, 0, s, a);
-            break;
-        case 3: hipLaunchKernelGGL((compose_kernel<float, 3>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((compose_staged_kernel<float, 4>), grid, staged, 0, s, a); break;
-        default: return hipErrorInvalidValue;
-        }
+    switch (interp) {
+    case 0: hipLaunchKernelGGL((compose_staged_kernel<T, 0>), grid, staged, lds, s, a); break;
+    case 1: hipLaunchKernelGGL((compose_staged_kernel<T, 1>), grid, staged, lds, s, a); break;
+    case 2:
+        if (staged2)
+            hipLaunchKernelGGL((compose_staged2_kernel<T>), grid, staged, 0, s, a);
+        else
+            hipLaunchKernelGGL((compose_kernel<T, 2>), grid, block, 0, s, a);
+        break;
+    case 3: hipLaunchKernelGGL((compose_kernel<T, 3>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((compose_staged_kernel<T, 4>), grid, staged, lds, s, a); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_compose(int interp, int precision, const ComposeArgs &a, hipStream_t s) {
+    return precision == 0 ? launch_compose_of<double>(interp, a, s)
+                          : launch_compose_of<float>(interp, a, s);
 }
 
 hipError_t launch_locate(double lo, double inv, int n, const double *x, long long count,

@@ -121,7 +121,8 @@ hipError_t launch_locate(double lo, double inv, int n, const double *x, long lon
 hipError_t launch_batch_build(int precision, int accumulation, const BatchProblem *probs,
                               const BatchItem *items, int n_items, unsigned *counter,
                               int n_workgroups, hipStream_t s);
-hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count,
+size_t batch_compose_lds(const BatchProblem &p, int precision);
+hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, size_t lds,
                                 hipStream_t s);
 
 // Shared by the C-ABI translation units: record the calling thread's error

@@ -16,12 +16,13 @@ using namespace nv::dev;
 extern "C" {
 void layout(int n, int comps, int elem, int *out) {
     const PfLayout l(n, comps, elem);
-    const int v[] = {l.rows, l.width, l.slots, l.helpers, l.row_bytes, l.slot_bytes, l.ahead};
-    for (int i = 0; i < 7; ++i) out[i] = v[i];
+    const int v[] = {l.rows, l.width, l.slots, l.helpers, l.row_bytes, l.slot_bytes, l.ahead,
+                     l.lds_bytes()};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
 }
 void constants(int *out) {
-    const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead, kPfWin};
-    for (int i = 0; i < 7; ++i) out[i] = v[i];
+    const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead, kPfWin, kPfBesideBuild};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
 }
 }
 """
@@ -32,10 +33,10 @@ SIZES = [*range(2, 4200), 8191, 65536, 1 << 20]
 
 class Ring:
     def __init__(self, lib, n, comps, elem):
-        out = (ctypes.c_int * 7)()
+        out = (ctypes.c_int * 8)()
         lib.layout(n, comps, elem, out)
         (self.rows, self.width, self.slots, self.helpers, self.row_bytes, self.slot_bytes,
-         self.ahead) = out
+         self.ahead, self.lds) = out
 
 
 @pytest.fixture(scope="module")
@@ -49,9 +50,9 @@ def lib(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def const(lib):
-    out = (ctypes.c_int * 7)()
+    out = (ctypes.c_int * 8)()
     lib.constants(out)
-    return dict(zip(("pair", "helpers", "max_slots", "ring_bytes", "slots2", "ahead2", "window"), out))
+    return dict(zip(("pair", "helpers", "max_slots", "ring_bytes", "slots2", "ahead2", "window", "beside"), out))
 
 
 @pytest.mark.parametrize("comps,elem", TABLES)
@@ -90,3 +91,16 @@ def test_a_window_holds_the_narrowest_one_and_its_slack(lib, const, comps, elem)
             assert const["window"] <= r.width < n
             assert r.slots > r.ahead
     assert seen
+
+
+@pytest.mark.parametrize("comps,elem", TABLES)
+def test_the_ring_takes_what_the_table_needs(lib, const, comps, elem):
+    """Never more LDS than lies above the granules of eight build workgroups (a chain
+    that overlaps a build starts beside five of them), about 64 KB for windows of up to
+    8 bytes per node and for rows of up to 4 KB."""
+    for n in SIZES:
+        r = Ring(lib, n, comps, elem)
+        assert r.slots * r.slot_bytes + 64 < r.lds <= const["beside"]
+        if (not r.rows and comps * elem <= 8) or n * comps * elem <= 4000:
+            assert r.lds <= 67 * 1024
+        assert r.slots <= 16 or r.rows
