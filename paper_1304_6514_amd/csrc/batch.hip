@@ -5,8 +5,8 @@
 // of 256*P grid points of one slice of one problem, longest items first), runs
 // the same integration body as the single-problem build (build_tile), and
 // exits when the list is exhausted -- every workgroup reaches that exit.
-// Communication phase: one launch, one wave per problem, each running its own
-// dependent chain.  Counter reset, both launches and the copy of the results
+// Communication phase: one launch, one workgroup per problem, each running its own
+// dependent chain: staged, or one wave alone when there are many.  Counter reset, both launches and the copy of the results
 // are captured once into a HIP graph and replayed.
 #include "compose.h"
 #include "integrate.h"
@@ -68,6 +68,23 @@ __global__ void __launch_bounds__(kBuildBlock)
     }
 }
 
+// One wave per problem.
+template <class T>
+__global__ __launch_bounds__(64) void batch_compose_wave_kernel(
+    const BatchProblem *__restrict__ probs, int count) {
+    const int b = int(blockIdx.x);
+    if (b >= count) return;
+    const BatchProblem &pr = probs[b];
+    double fin[2] = {0.0, 0.0};
+    switch (pr.interp) {
+    case NV_INTERP_LINEAR: compose_range_1d<T, 0>(pr.compose, fin); break;
+    case NV_INTERP_HERMITE: compose_range_1d<T, 1>(pr.compose, fin); break;
+    default: compose_range_bilinear<T>(pr.compose, fin); break;
+    }
+    if (threadIdx.x == 0)
+        for (int d = 0; d < pr.dim; ++d) pr.result[d] = fin[d];
+}
+
 // One workgroup per problem: the chain's wave and the waves that stage table
 // rows or windows for it, as in a single composition (one wave per problem that
 // read global memory at every lookup took 0.51 ms for 32 problems of up to
@@ -126,14 +143,24 @@ size_t batch_compose_lds(const BatchProblem &p, int precision) {
     return size_t(PfLayout(c.n0, 1, precision == NV_FP64 ? 8 : 4).lds_bytes());
 }
 
-hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, size_t lds,
-                                hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    const dim3 grid{unsigned(count)}, block(kPfThreads);
-    if (precision == NV_FP64)
-        hipLaunchKernelGGL((batch_compose_kernel<double>), grid, block, lds, s, probs, count);
+template <class T>
+void launch_batch_compose_of(const BatchProblem *probs, int count, bool staged, size_t lds,
+                             hipStream_t s) {
+    const dim3 grid{unsigned(count)};
+    if (staged)
+        hipLaunchKernelGGL((batch_compose_kernel<T>), grid, dim3(kPfThreads), lds, s, probs, count);
     else
-        hipLaunchKernelGGL((batch_compose_kernel<float>), grid, block, lds, s, probs, count);
+        hipLaunchKernelGGL((batch_compose_wave_kernel<T>), grid, dim3(64), 0, s, probs, count);
+}
+
+// lds: the largest of the problems' (staged chains).
+hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, bool staged,
+                                size_t lds, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    if (precision == NV_FP64)
+        launch_batch_compose_of<double>(probs, count, staged, lds, s);
+    else
+        launch_batch_compose_of<float>(probs, count, staged, lds, s);
     return hipGetLastError();
 }
 
@@ -306,7 +333,8 @@ nv_status ensure_graph(nv_batch *b) {
     for (const nv::BatchProblem &p : b->hp)
         lds = std::max(lds, nv::batch_compose_lds(p, b->precision));
     if (e == hipSuccess)
-        e = nv::launch_batch_compose(b->precision, probs, b->count, lds, b->stream);
+        e = nv::launch_batch_compose(b->precision, probs, b->count,
+                                     nv::dev::batch_staged(b->count, kCus), lds, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->stage, b->work + b->off_status,
                            b->off_result - b->off_status + size_t(b->count) * 2 * sizeof(double),

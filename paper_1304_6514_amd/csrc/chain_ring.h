@@ -92,5 +92,15 @@ constexpr int kPf2MaxAxis = 65536;
 static_assert(kPf2Slots % kPfHelpers == 0, "one owner per slot");
 static_assert(kPf2Slots > kPf2Ahead, "a slot is finished before it is filled again");
 
+// A batch's chains run staged, a workgroup of nine waves and a ring each, while two of
+// them per CU are enough, and by one wave without LDS, all at once, when there are more
+// (a CU holds two or three rings).  Problems of 256 slices, the whole run, staged and by
+// one wave: 512 of 64 points 1632 and 1704 us, 512 of 1000 points 6.16 and 6.21 ms, 512 of
+// 24 x 24 points 4.76 and 4.77 ms; 768 of 64 points 2424 and 2471 us, but 768 of 1000
+// points 9.22 and 9.20 ms, 1024 of 24 x 24 points 9.59 and 9.29 ms and 4096 of them 37.9
+// and 36.4 ms.
+constexpr int kPfChainsPerCu = 2;
+constexpr bool batch_staged(int count, int cus) { return count <= kPfChainsPerCu * cus; }
+
 }  // namespace dev
 }  // namespace nv

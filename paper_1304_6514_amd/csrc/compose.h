@@ -390,6 +390,31 @@ __device__ inline bool slice_general(const ComposeArgs &a, int j, double &lam, l
     return true;
 }
 
+// The 1-D chain by one wave alone, every slice by the general path (where more
+// chains run at once than staged ones would fit the chip).
+template <class T, int Interp>
+__device__ inline void compose_range_1d(const ComposeArgs &a, double *final_out) {
+    const int lane = int(threadIdx.x) & 63;
+    double lam = 0.0, unused = 0.0, keep = 0.0;
+    if (!uniform_bool(range_begin<1>(a, lane, lam, unused))) return;
+    int oog = 0, bad_slice = -1, jb = a.j_begin, j = a.j_begin;
+    for (; j < a.j_end; ++j) {
+        long long cell;
+        if (!slice_general<T, Interp>(a, j, lam, cell, oog)) {
+            bad_slice = j;
+            break;
+        }
+        if (lane == j - jb) keep = lam;
+        if (j - jb == 63) {
+            a.boundary[jb + lane + 1] = keep;
+            jb += 64;
+        }
+    }
+    if (lane < j - jb) a.boundary[jb + lane + 1] = keep;
+    range_end(a, lane, lam, 0.0, oog, bad_slice);
+    final_out[0] = lam;
+}
+
 // Waits, a bounded number of polls, until the slot holds slice j.
 __device__ inline bool pf_wait(const PfTag *tag, unsigned slot, int j) {
     for (int spin = 0; spin < 4096; ++spin) {

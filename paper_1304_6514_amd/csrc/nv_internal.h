@@ -122,8 +122,8 @@ hipError_t launch_batch_build(int precision, int accumulation, const BatchProble
                               const BatchItem *items, int n_items, unsigned *counter,
                               int n_workgroups, hipStream_t s);
 size_t batch_compose_lds(const BatchProblem &p, int precision);
-hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, size_t lds,
-                                hipStream_t s);
+hipError_t launch_batch_compose(int precision, const BatchProblem *probs, int count, bool staged,
+                                size_t lds, hipStream_t s);
 
 // Shared by the C-ABI translation units: record the calling thread's error
 // message and return s; check one problem's description (host only).

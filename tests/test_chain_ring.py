@@ -20,6 +20,7 @@ void layout(int n, int comps, int elem, int *out) {
                      l.lds_bytes()};
     for (int i = 0; i < 8; ++i) out[i] = v[i];
 }
+int staged(int count, int cus) { return batch_staged(count, cus); }
 void constants(int *out) {
     const int v[] = {kPfPair, kPfHelpers, kPfMaxSlots, kPfRingBytes, kPf2Slots, kPf2Ahead, kPfWin, kPfBesideBuild};
     for (int i = 0; i < 8; ++i) out[i] = v[i];
@@ -104,3 +105,7 @@ def test_the_ring_takes_what_the_table_needs(lib, const, comps, elem):
         if (not r.rows and comps * elem <= 8) or n * comps * elem <= 4000:
             assert r.lds <= 67 * 1024
         assert r.slots <= 16 or r.rows
+
+
+def test_a_batch_is_staged_up_to_two_problems_per_cu(lib):
+    assert lib.staged(1, 256) and lib.staged(512, 256) and not lib.staged(513, 256)
