@@ -693,6 +693,7 @@ struct nv_lin {
     int *bad = nullptr;
     int M = 0, N = 0, S_tot = 0;
     bool built = false;
+    bool fixed_order = false;           // one chain slice by slice, to the bit
     hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, e3 = nullptr;
     float build_ms = 0.f, compose_ms = 0.f;
     // pinned staging of the step scalars and of a composition's results; none
@@ -1024,7 +1025,7 @@ NV_API nv_status nv_lin_compose(nv_lin *l, const double *y0, double *yT, double 
     const size_t first = boundary ? 0 : size_t(N) * M;
     const size_t results = ((size_t(N) + 1) * M - first) * 8 + sizeof(double);
     // by blocks; then, should a state be beyond what that serves, slice by slice
-    for (int levels = l->levels;; levels = 0) {
+    for (int levels = l->fixed_order ? 0 : l->levels;; levels = 0) {
         if (levels > 0) NV_HIP(launch_products(l));
         NV_HIP(launch_chain(l, levels, true));
         for (int v = levels - 1; v >= 0; --v) NV_HIP(launch_chain(l, v, false));
@@ -1108,6 +1109,12 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     NV_HIP(hipEventElapsedTime(&l->compose_ms, l->e2, l->e3));
     if (bad != init)
         return fail(NV_ERR_NONFINITE, "a state became non-finite in slice %d", bad);
+    return NV_OK;
+}
+
+NV_API nv_status nv_lin_set_fixed_order(nv_lin *l, int on) {
+    if (!l) return fail(NV_ERR_INVALID_ARG, "NULL argument");
+    l->fixed_order = on != 0;
     return NV_OK;
 }
 

@@ -56,6 +56,11 @@ class LinearPropagator:
                         w.dt)
         self.workload = w
 
+    def fixed_order(self, on=True):
+        """One chain slice by slice whatever the number of slices: the states are
+        then specified to the bit."""
+        nv.nv_lin_set_fixed_order(self.h, on)
+
     def compose(self, y0, want_boundary=True):
         w = self.workload
         return nv.nv_lin_compose(self.h, y0, w.M, w.n_slices, want_boundary)

@@ -657,6 +657,7 @@ _SIGNATURES.update({
                      ctypes.c_int, ctypes.c_double],
     "nv_lin_compose": [_P, _P, _P, _P],
     "nv_lin_compose_many": [_P, _P, ctypes.c_longlong, _P, _P],
+    "nv_lin_set_fixed_order": [_P, ctypes.c_int],
     "nv_lin_get_tables": [_P, _P, _P],
     "nv_lin_last_timing": [_P, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_float)],
 })
@@ -703,6 +704,10 @@ def nv_lin_compose_many(lin, y0_dev, count, yT_dev, boundary_dev=None):
     if st not in (NV_OK, NV_ERR_NONFINITE):
         _check(st)
     return st
+
+
+def nv_lin_set_fixed_order(lin, on=True):
+    _check(load().nv_lin_set_fixed_order(lin, int(bool(on))))
 
 
 def nv_lin_get_tables(lin, M, n_slices):

@@ -97,3 +97,34 @@ def test_more_chains_than_one_launch_by_blocks_holds(torch):
             check_chain(G, c, got, lo.compose(G, c, y0[q].cpu().numpy()), f"chain {q}")
             assert np.array_equal(yT[q].cpu().numpy(), got[-1])
         del b
+
+
+def stated_order(G, c, y0):
+    """lambda_{j+1} = c + (((p0 + p1) + (p2 + p3)) + ((p4 + p5) + (p6 + p7))), p_r =
+    G_i,r l_r + G_i,r+8 l_r+8 + ... summed left to right from 0."""
+    lam, out = np.array(y0), [np.array(y0)]
+    for Gj, cj in zip(G, c):
+        p = np.zeros((8, len(lam)))
+        for k in range(len(lam)):
+            p[k % 8] = p[k % 8] + Gj[:, k] * lam[k]
+        lam = cj + (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])))
+        out.append(lam)
+    return np.array(out)
+
+
+@pytest.mark.parametrize("M,N", [(1, 70), (9, 63), (9, 64), (30, 300), (127, 128)])
+def test_the_stated_order_holds_to_the_bit_for_any_number_of_slices(torch, M, N):
+    w = HeatWorkload("order", M, 0.0013, N, T=0.0031 * N)
+    say("fixed order", M, N)
+    y0 = np.random.default_rng(3).normal(0.0, 1.0, M)
+    with LinearPropagator() as lin:
+        lin.build(w)
+        G, c = lin.tables()
+        ref = stated_order(G, c, y0)
+        lin.fixed_order()
+        st, yT, bnd = lin.compose(y0)
+        assert st == nv.NV_OK and np.array_equal(bnd, ref) and np.array_equal(yT, ref[-1])
+        lin.fixed_order(False)
+        st, yT, bnd = lin.compose(y0)
+        assert st == nv.NV_OK and (N >= 64 or np.array_equal(bnd, ref))
+        check_chain(G, c, bnd, ref, "by blocks")
