@@ -717,6 +717,197 @@ __global__ __launch_bounds__(kChainThreads) void sur_chain_kernel(ChainArgs a) {
         chain_states<C>(a, L, lane);
 }
 
+// More chains than one workgroup of sixteen per CU, of a form whose coarse steps
+// cost little: then the chip's throughput counts, not one workgroup's latency.
+// Four waves evaluate the network for 16 chains, wave w output tiles 2w and
+// 2w+1 (features 32w .. 32w+31) of every 128-wide layer, which is exactly
+// k-block w of the next layer's operand in the permuted order; the four blocks
+// are exchanged through LDS, where the weights lie, and every wave takes the coarse
+// steps itself.  Two workgroups share a CU, with fewer exchanges and barriers per chain
+// than two of nine waves (four_waves says where).
+struct FourWaveLds {
+    __bf16 w[2 * kWidth * kLdsRow];      // Wf2, Wf3
+    SmallParams sp;
+    bf16x8 xb[4][64];                    // operand k-block of each wave, by lane
+    float part[4][2][16];                // output partial sums: wave, output, sample
+};
+
+// One 128 x 128 layer's tiles 2w, 2w+1 from the four operand blocks.
+__device__ inline void layer_split(const __bf16 *M, const bf16x8 (&b)[4], int w, int lane,
+                                   f32x4 (&out)[2]) {
+    const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        const __bf16 *row = M + (16 * (2 * w + t) + r) * kLdsRow + 8 * g;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+            acc = mfma(*reinterpret_cast<const bf16x8 *>(row + 32 * kb), b[kb], acc);
+        out[t] = acc;
+    }
+}
+
+// Publish this wave's block and gather all four (two barriers: the previous
+// round's reads are complete before the block is overwritten).
+__device__ inline void exchange(FourWaveLds &L, const bf16x8 &mine, int w, int lane,
+                                bf16x8 (&b)[4]) {
+    __syncthreads();
+    L.xb[w][lane] = mine;
+    __syncthreads();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) b[kb] = L.xb[kb][lane];
+}
+
+__device__ inline void forward_split(FourWaveLds &L, const float (&u)[4], int w, int lane,
+                                     float &o0, float &o1) {
+    const int s = lane & 15, g = lane >> 4;
+    f32x4 x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 16 * (2 * w + t) + 4 * g + i;
+            float z = L.sp.b1[f];
+            z = fmaf(L.sp.w1[4 * f + 0], u[0], z);
+            z = fmaf(L.sp.w1[4 * f + 1], u[1], z);
+            z = fmaf(L.sp.w1[4 * f + 2], u[2], z);
+            z = fmaf(L.sp.w1[4 * f + 3], u[3], z);
+            float d;
+            x[t][i] = gelu_d(z, d);
+        }
+    }
+    bf16x8 b[4], blk;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        blk[e] = __bf16(x[0][e]);
+        blk[e + 4] = __bf16(x[1][e]);
+    }
+    exchange(L, blk, w, lane, b);
+#pragma unroll
+    for (int layer = 0; layer < 2; ++layer) {
+        const __bf16 *M = L.w + layer * kWidth * kLdsRow;
+        const float *bias = layer == 0 ? L.sp.b2 : L.sp.b3;
+        layer_split(M, b, w, lane, x);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d;
+                x[t][i] = gelu_d(x[t][i] + bias[16 * (2 * w + t) + 4 * g + i], d);
+            }
+        }
+        if (layer == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                blk[e] = __bf16(x[0][e]);
+                blk[e + 4] = __bf16(x[1][e]);
+            }
+            exchange(L, blk, w, lane, b);
+        }
+    }
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 16 * (2 * w + t) + 4 * g + i;
+            s0 = fmaf(L.sp.w4[f], x[t][i], s0);
+            s1 = fmaf(L.sp.w4[kWidth + f], x[t][i], s1);
+        }
+    }
+    s0 += __shfl_xor(s0, 16);
+    s1 += __shfl_xor(s1, 16);
+    s0 += __shfl_xor(s0, 32);
+    s1 += __shfl_xor(s1, 32);
+    if (g == 0) {
+        L.part[w][0][s] = s0;
+        L.part[w][1][s] = s1;
+    }
+    __syncthreads();
+    o0 = ((L.part[0][0][s] + L.part[1][0][s]) + (L.part[2][0][s] + L.part[3][0][s])) + L.sp.b4[0];
+    o1 = ((L.part[0][1][s] + L.part[1][1][s]) + (L.part[2][1][s] + L.part[3][1][s])) + L.sp.b4[1];
+}
+
+__global__ __launch_bounds__(kInferThreads) void sur_chain_four_kernel(ChainArgs a) {
+#pragma clang fp contract(off)
+    __shared__ FourWaveLds L;
+    const int tid = int(threadIdx.x);
+    load_mats<2, kInferThreads>(L.w, a.shadow, tid);
+    load_small<kInferThreads>(L.sp, a.params, tid);
+    __syncthreads();
+    const int lane = tid & 63, w = tid >> 6, s = lane & 15, g = lane >> 4;
+    const long long q = (long long)blockIdx.x * 16 + s;        // the 4 waves share 16 chains
+    const bool live = q < a.count;
+    const long long qc = live ? q : a.count - 1;
+    double l0 = a.y0[2 * qc], l1 = a.y0[2 * qc + 1];
+    const float muf = float(a.mu[qc]);
+    const bool writer = live && g == 0 && w == 0;
+    const long long stride = (long long)a.n_slices + 1;
+    if (writer && a.boundary) {
+        a.boundary[(q * stride) * 2] = l0;
+        a.boundary[(q * stride) * 2 + 1] = l1;
+    }
+    unsigned long long nfb = 0, nout = 0;
+    double maxdev = 0.0;
+    bool bad = false;
+    for (int j = 0; j < a.n_slices; ++j) {
+        asm volatile("" ::: "memory");  // keep the weight reads inside the loop
+        if (!(isfinite(l0) && isfinite(l1))) bad = true;
+        const float tj = float(a.t0 + double(j) * a.L);
+        float u[4] = {(float(l0) - a.shift[0]) * a.scale[0], (float(l1) - a.shift[1]) * a.scale[1],
+                      (tj - a.shift[2]) * a.scale[2], (muf - a.shift[3]) * a.scale[3]};
+        float o0, o1;
+        forward_split(L, u, w, lane, o0, o1);
+        double n0, n1;
+        if (a.step_doubling) {
+            const StepDoubling sd = step_doubling(a.mu[qc], a.L, a.coarse, l0, l1, a.tau2_0,
+                                                  a.tau2_1);
+            n0 = sd.g0 + sd.d0 * (kRichardson + (a.os0 * sd.gt0) * double(o0));
+            n1 = sd.g1 + sd.d1 * (kRichardson + (a.os1 * sd.gt1) * double(o1));
+        } else {
+            double g0 = l0, g1 = l1;
+            coarse_rk4(double(a.mu[qc]), a.L / double(a.coarse), a.coarse, g0, g1);
+            n0 = g0 + a.os0 * double(o0);
+            n1 = g1 + a.os1 * double(o1);
+        }
+        const bool outside = !(l0 >= a.blo0 && l0 <= a.bhi0 && l1 >= a.blo1 && l1 <= a.bhi1);
+        if (a.tab0) {
+            double p, pq;
+            if (a.fb_fp64)
+                bilinear_row<double>(a, j, l0, l1, p, pq);
+            else
+                bilinear_row<float>(a, j, l0, l1, p, pq);
+            const double d0 = fabs(n0 - p), dd1 = fabs(n1 - pq);
+            const double dev = d0 > dd1 ? d0 : dd1;
+            if (dev == dev && dev > maxdev) maxdev = dev;
+            if (!(dev <= a.guard) || outside) {
+                n0 = p;
+                n1 = pq;
+                ++nfb;
+            }
+        } else if (outside) {
+            ++nout;
+        }
+        if (!bad) {
+            l0 = n0;
+            l1 = n1;
+        }
+        if (writer && a.boundary) {
+            a.boundary[(q * stride + j + 1) * 2] = l0;
+            a.boundary[(q * stride + j + 1) * 2 + 1] = l1;
+        }
+    }
+    if (!(isfinite(l0) && isfinite(l1))) bad = true;
+    if (writer) {
+        a.final_state[2 * q] = l0;
+        a.final_state[2 * q + 1] = l1;
+        if (nfb) atomicAdd(&a.stats[0], nfb);
+        if (nout) atomicAdd(&a.stats[1], nout);
+        if (maxdev > 0.0) atomicMax(&a.stats[2], (unsigned long long)__double_as_longlong(maxdev));
+        if (bad) atomicMin(&a.stats[3], (unsigned long long)q);
+    }
+}
+
 // ---- training: forward pass, loss, back-propagation and gradient sums -----
 //
 // One launch does the whole pass over a minibatch and leaves one share of every
@@ -1268,6 +1459,21 @@ long long k_per_split(long long n) {
     return (k + 31) / 32 * 32;
 }
 
+// Whether a composition runs with four waves per 16 chains instead of nine: with more
+// than one workgroup per CU, where the network bounds the time (additive) or the chip is
+// full several times over, except where the ninth wave's coarse steps weigh most (two
+// to four with step doubling: four waves take each of them four times, nine hide them
+// behind the network).  Nine against four waves, us per slice, on 256 CUs: additive, one
+// coarse step, 4096 chains 1.82 and 2.36, 5000 chains 3.34 and 2.96, 65,536 chains 24.9 and
+// 20.5; step doubling, one step, 8192 chains 3.41 and 3.52, 65,536 chains 25.3 and 24.1;
+// four steps, 65,536 chains 33.3 and 34.4; sixteen, 5000 chains 11.2 and 11.1, 65,536
+// chains 89.5 and 78.9.
+bool four_waves(const nv_sur_config &cfg, long long count, int n_cu) {
+    if (count <= 16LL * n_cu) return false;
+    if (cfg.correction == NV_SUR_ADDITIVE || cfg.coarse_steps > 8) return true;
+    return (cfg.coarse_steps == 1 || cfg.coarse_steps > 4) && count > 64LL * n_cu;
+}
+
 // One minibatch: forward and back-propagation with the gradient sums, then the
 // update kernel (mode: reduce only, or reduce and Adam step).
 nv_status minibatch(nv_sur *s, const float *x, const float *t, long long ld, long long start,
@@ -1682,14 +1888,17 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
     // longer than one of twice the chains: 1500 chains 1.44 us per slice in fours,
     // 1.21 in eights; 3000 chains 1.85 in eights, 1.57 in sixteens)
     const int per = c->count <= 4LL * s->n_cu ? 4 : (c->count <= 8LL * s->n_cu ? 8 : 16);
-    const auto run = per == 4   ? sur_chain_kernel<4>
+    const bool four = four_waves(s->cfg, c->count, s->n_cu);
+    const int threads = four ? kInferThreads : kChainThreads;
+    const auto run = four       ? sur_chain_four_kernel
+                     : per == 4 ? sur_chain_kernel<4>
                      : per == 8 ? sur_chain_kernel<8>
                                 : sur_chain_kernel<16>;
     *info = nv_sur_compose_info{};
     info->bad_chain = -1;
     a.stats = s->stats;
     // one launch, or several of as many chains as one can hold
-    const long long most = nv::max_workgroups(kChainThreads) * per;
+    const long long most = nv::max_workgroups(threads) * per;
     for (long long first = 0; first < c->count; first += most) {
         a.count = std::min(most, c->count - first);
         a.y0 = c->y0 + 2 * first;
@@ -1699,7 +1908,7 @@ NV_API nv_status nv_sur_compose(nv_sur *s, const nv_sur_chains *c, nv_sur_compos
         const unsigned long long init[4] = {0ull, 0ull, 0ull, ~0ull};
         NV_HIP(hipMemcpyAsync(s->stats, init, sizeof init, hipMemcpyHostToDevice, s->stream));
         NV_HIP(hipEventRecord(s->ev0, s->stream));
-        hipLaunchKernelGGL(run, dim3(unsigned((a.count + per - 1) / per)), dim3(kChainThreads), 0,
+        hipLaunchKernelGGL(run, dim3(unsigned((a.count + per - 1) / per)), dim3(threads), 0,
                            s->stream, a);
         NV_HIP(hipGetLastError());
         NV_HIP(hipEventRecord(s->ev1, s->stream));
