@@ -95,7 +95,8 @@ NV_API nv_status nv_lin_set_fixed_order(nv_lin *lin, int on);
  * 16 chains per workgroup (32, sharing the workgroup's table reads, when
  * count fills two such workgroups per compute unit and M <= 104), from 64
  * slices on through the products of blocks of slices as above (only those
- * when no boundary states are asked for).  Each component's sum c_i + sum_k
+ * when no boundary states are asked for; with them, slice by slice above 12 to 32
+ * chains per compute unit, by the number of slices).  Each component's sum c_i + sum_k
  * G_ik l_k is formed by the matrix cores in an order this interface does not
  * fix (so results are within the FP64 inner-product rounding bound of any
  * order, not bit-equal to nv_lin_compose).

@@ -34,7 +34,6 @@
 
 using nv::fail;
 using nv::lin::kBlock;
-using nv::lin::kXcds;
 
 #define NV_HIP(expr)                                                                    \
     do {                                                                                \
@@ -479,6 +478,7 @@ struct ManyArgs {
     long long Q;
     int groups;                 // workgroups of one block of maps
     int blocks;                 // blocks of maps
+    int spread;                 // many_spread
 };
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(512) void lin_many_kernel(ManyArgs a) {
     const int tid = int(threadIdx.x), lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.lv.M, Ms = lin_stride(M), per = Ms * (M + 1);
-    const unsigned spread = a.blocks == 1 ? 1 : kXcds, turn = blockIdx.x / spread;
+    const unsigned spread = unsigned(a.spread), turn = blockIdx.x / spread;
     const int block = int(turn / unsigned(a.groups) * spread + blockIdx.x % spread);
     const int group = int(turn % unsigned(a.groups));
     if (block >= a.blocks) return;
@@ -654,7 +654,8 @@ void lin_launch_many(ManyArgs a, long long pair_from, hipStream_t st) {
     const bool paired = !a.product && many_paired(a.lv.M, Q, blocks, pair_from);
     a.blocks = int(blocks);
     a.groups = int(many_groups(Q, paired));
-    const dim3 grid(unsigned(a.groups * many_rows(blocks)));
+    a.spread = many_spread(blocks, a.product != nullptr);
+    const dim3 grid(unsigned(a.groups * many_rows(blocks, a.product != nullptr)));
     if constexpr (KP <= kManyPairMaxKP) {
         if (paired) {
             hipLaunchKernelGGL((lin_many_kernel<KP, 2>), grid, dim3(kThreads), 0, st, a);
@@ -1077,7 +1078,8 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     a.Q = count;
     NV_HIP(hipEventRecord(l->e2, l->stream));
     int bad = init;
-    // by blocks (if one launch can hold the states inside them); then, should a
+    // by blocks (with states: while the chains are few, and if one launch can hold the
+    // states inside the blocks); then, should a
     // state be beyond what that serves, slice by slice.  The final states may
     // overwrite the initial ones (a workgroup reads its chains before it writes
     // them), but a second pass would then start from the first one's results: such
@@ -1086,8 +1088,10 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     const uintptr_t from = reinterpret_cast<uintptr_t>(y0_dev),
                     to = reinterpret_cast<uintptr_t>(yT_dev);
     const bool in_place = from < to + bytes && to < from + bytes;
-    const bool fits = !boundary_dev || nv::lin::states_fit(l->M, l->N, count, pair_from);
-    for (int levels = in_place || !fits ? 0 : l->levels;; levels = 0) {
+    const bool by_blocks = !boundary_dev ||
+                           (nv::lin::states_by_blocks(l->N, count, n_cu) &&
+                            nv::lin::states_fit(l->M, l->N, count, pair_from));
+    for (int levels = in_place || !by_blocks ? 0 : l->levels;; levels = 0) {
         if (levels > 0)
             NV_HIP(launch_products(l));
         else

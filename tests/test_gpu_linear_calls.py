@@ -128,3 +128,23 @@ def test_the_stated_order_holds_to_the_bit_for_any_number_of_slices(torch, M, N)
         st, yT, bnd = lin.compose(y0)
         assert st == nv.NV_OK and (N >= 64 or np.array_equal(bnd, ref))
         check_chain(G, c, bnd, ref, "by blocks")
+
+
+@pytest.mark.parametrize("N", [72, 100, 130])
+@pytest.mark.parametrize("more", [0, 1])
+def test_states_on_either_side_of_the_number_of_chains_for_blocks(torch, N, more):
+    """The states of as many chains as run through the blocks (12, 24, 32 per compute
+    unit by the number of slices), ragged last blocks among them, and of one more."""
+    M = 19
+    w = HeatWorkload("line", M, 0.0013, N, T=0.0031 * N)
+    per_cu = 12 if N < 96 else 24 if N < 128 else 32
+    Q = per_cu * torch.cuda.get_device_properties(0).multi_processor_count + more
+    say("compose_many states", N, Q)
+    y0 = np.random.default_rng(N).normal(0.0, 1.0, (Q, M))
+    with LinearPropagator() as lin:
+        lin.build(w)
+        G, c = lin.tables()
+        st, yT, b = lin.compose_many(y0, want_boundary=True)
+    assert st == nv.NV_OK and torch.equal(yT, b[:, -1])
+    for q in (0, 15, 16, 17, Q // 2, Q - 2, Q - 1):
+        check_chain(G, c, b[q].cpu().numpy(), lo.compose(G, c, y0[q]), f"chain {q}")

@@ -19,7 +19,8 @@ long long groups(long long Q, int paired) { return many_groups(Q, paired); }
 int paired(int M, long long Q, long long blocks, long long from) {
     return many_paired(M, Q, blocks, from);
 }
-long long rows(long long blocks) { return many_rows(blocks); }
+long long rows(long long blocks, int product) { return many_rows(blocks, product); }
+int by_blocks(long long N, long long Q, int cus) { return states_by_blocks(N, Q, cus); }
 }
 """
 PAIR_FROM = 2 * 256 * 32
@@ -37,7 +38,8 @@ def lib(tmp_path_factory):
     lib.states.argtypes = [ctypes.c_int, ll, ll, ll]
     lib.groups.argtypes, lib.groups.restype = [ll, ctypes.c_int], ll
     lib.paired.argtypes = [ctypes.c_int, ll, ll, ll]
-    lib.rows.argtypes, lib.rows.restype = [ll], ll
+    lib.rows.argtypes, lib.rows.restype = [ll, ctypes.c_int], ll
+    lib.by_blocks.argtypes = [ll, ll, ctypes.c_int]
     return lib
 
 
@@ -45,7 +47,7 @@ def items(lib, M, N, Q, product):
     """Work-items of the launch over every block of 8 of N maps."""
     blocks = (N + 7) // 8
     paired = not product and lib.paired(M, Q, blocks, PAIR_FROM)
-    return lib.groups(M + 1 if product else Q, paired) * lib.rows(blocks) * 512
+    return lib.groups(M + 1 if product else Q, paired) * lib.rows(blocks, product) * 512
 
 
 @pytest.mark.parametrize("M", [1, 2, 15, 16, 99, 104, 105, 127])
@@ -58,3 +60,25 @@ def test_a_launch_by_blocks_is_taken_exactly_where_it_fits(lib, M):
                 (M, N, Q)
     # 2,200,000 chains of 1024 slices: one launch over the blocks does not hold them
     assert not lib.states(M, 1024, 2_200_000, PAIR_FROM)
+
+
+def test_many_chains_with_states_run_slice_by_slice(lib):
+    for N, most in ((64, 12), (95, 12), (96, 24), (127, 24), (128, 32), (1 << 20, 32)):
+        assert lib.by_blocks(N, most * 256, 256) and not lib.by_blocks(N, most * 256 + 1, 256)
+
+
+def test_every_block_has_its_groups(lib):
+    """The numbers of a launch, block by block or in turns over eight dies, cover every
+    (block, group) once (the kernel's own arithmetic)."""
+    for blocks in (1, 2, 8, 9, 13):
+        for product in (0, 1):
+            rows, groups = lib.rows(blocks, product), 3
+            spread = 8 if product and blocks > 1 else 1
+            seen = set()
+            for wg in range(rows * groups):
+                turn = wg // spread
+                block, group = turn // groups * spread + wg % spread, turn % groups
+                if block < blocks:
+                    assert (block, group) not in seen
+                    seen.add((block, group))
+            assert len(seen) == blocks * groups
