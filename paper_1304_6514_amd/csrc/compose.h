@@ -176,17 +176,6 @@ __device__ inline void range_end(const ComposeArgs &a, int lane, double l0, doub
     }
 }
 
-// Composes slices j_begin .. j_end-1, run by one whole wave: every lane takes
-// the same chain (uniform values, uniform loads, so the result is that of one
-// lane), and lane l keeps the boundary state of slice jb + l + 1 of the current
-// block of 64 slices; a block is written out with one coalesced store.  No
-// store then sits between one slice's loads and the next's (the memory counter
-// is in order, so a load issued after a store would also wait for the store):
-// the chain waits for a store once per 64 slices.  A launch that starts at
-// slice 0 takes y0 from its arguments and resets the status; a later launch
-// resumes from the boundary state the previous one left in memory and adds to
-// the status.  With final_out, the last state (that of the failing slice's
-// start when one fails) is also returned there ([dim]).
 // Cubic Hermite with stored slopes (Interp 4): node values ta, tb of cell i0
 // and the slopes ma, mb the build stored for them (component 1), each times
 // the grid spacing, in the basis and order of the finite-difference form.
@@ -198,6 +187,17 @@ __device__ inline bool hermite_slopes_values(double ta, double tb, double ma, do
     return all_finite(ta, tb, da, db);
 }
 
+// Composes slices j_begin .. j_end-1, run by one whole wave: every lane takes
+// the same chain (uniform values, uniform loads, so the result is that of one
+// lane), and lane l keeps the boundary state of slice jb + l + 1 of the current
+// block of 64 slices; a block is written out with one coalesced store.  No
+// store then sits between one slice's loads and the next's (the memory counter
+// is in order, so a load issued after a store would also wait for the store):
+// the chain waits for a store once per 64 slices.  A launch that starts at
+// slice 0 takes y0 from its arguments and resets the status; a later launch
+// resumes from the boundary state the previous one left in memory and adds to
+// the status.  With final_out, the last state (that of the failing slice's
+// start when one fails) is also returned there ([dim]).
 template <class T>
 __device__ inline void compose_range_bilinear(const ComposeArgs &a, double *final_out = nullptr) {
 #pragma clang fp contract(off)

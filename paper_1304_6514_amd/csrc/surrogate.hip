@@ -125,12 +125,7 @@ __device__ inline void grad_small(const GemmArgs &a, int bx) {
     const int wt = kGemmSmallFirst + bx * 4 + (int(threadIdx.x) >> 6);
     if (wt >= kGemmWaveTiles) return;
     int a_row, b_row, M, N, out, t, tiles_n;
-    if (wt < 16) {
-        a_row = kRowD + 128; b_row = kRowH; M = N = 128; out = kG_W2; t = wt; tiles_n = 4;
-    } else if (wt < 32) {
-        a_row = kRowD + 256; b_row = kRowH + 128; M = N = 128; out = kG_W3; t = wt - 16;
-        tiles_n = 4;
-    } else if (wt < 36) {
+    if (wt < 36) {
         a_row = kRowD; b_row = kRowXO; M = 128; N = 16; out = kG_D_XO; t = wt - 32; tiles_n = 1;
     } else {
         a_row = kRowXO; b_row = kRowH + 256; M = 16; N = 144; out = kG_XO_H3; t = wt - 36;
