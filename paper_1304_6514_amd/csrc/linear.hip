@@ -1076,7 +1076,6 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     a.boundary = boundary_dev;
     a.bad = l->bad;
     a.Q = count;
-    NV_HIP(hipEventRecord(l->e2, l->stream));
     int bad = init;
     // by blocks (with states: while the chains are few, and if one launch can hold the
     // states inside the blocks); then, should a
@@ -1091,11 +1090,13 @@ NV_API nv_status nv_lin_compose_many(nv_lin *l, const double *y0_dev, long long 
     const bool by_blocks = !boundary_dev ||
                            (nv::lin::states_by_blocks(l->N, count, n_cu) &&
                             nv::lin::states_fit(l->M, l->N, count, pair_from));
-    for (int levels = in_place || !by_blocks ? 0 : l->levels;; levels = 0) {
-        if (levels > 0)
-            NV_HIP(launch_products(l));
-        else
+    const int first = in_place || !by_blocks ? 0 : l->levels;
+    for (int levels = first;; levels = 0) {
+        // (the products' first launch clears the report itself)
+        if (levels == 0)
             NV_HIP(hipMemcpyAsync(l->bad, &init, sizeof(int), hipMemcpyHostToDevice, l->stream));
+        if (levels == first) NV_HIP(hipEventRecord(l->e2, l->stream));
+        if (levels > 0) NV_HIP(launch_products(l));
         a.lv = level_args(l, levels, levels > 0, true);
         run(a, pair_from, l->stream);
         NV_HIP(hipGetLastError());
