@@ -1445,8 +1445,11 @@ nv_status refresh_shadow(nv_sur *s) {
 // gradient over few samples then differs in its last bits, and Adam, which divides
 // by the gradient's size, and the rounding of the weights to bfloat16 make that up
 // to 4e-5 of the parameters within twenty steps of a few hundred samples (of 190
-// runs below 8192 samples 23 were over 2e-5; above, at most 9e-6).  At 8192 the two
-// take the same time, 34 us.
+// runs below 8192 samples 23 were over 2e-5; above, at most 9e-6).  It is kept for
+// the results it has always given, not for their accuracy: the gradients of 16 to 4096
+// samples are equally far from 64 bits in both orders (3.2e-5 of their size in the median
+// at 1024, bfloat16 roundings that FP32 sums flip).  At 8192 the two take the same time,
+// 34 us.
 constexpr long long kRowsBelow = 8192;
 
 long long k_per_split(long long n) {
