@@ -931,11 +931,13 @@ __global__ __launch_bounds__(kInferThreads) void sur_chain_four_kernel(ChainArgs
 // and use the FP32 matrix instruction, which takes its four products in order
 // as a chain of fused multiply-adds.
 //
-// What bounds it: issue of vector instructions (the GELU and its derivative, 16
-// per value, are about half of them), then the reads of the operands from LDS, 64 KB for each of the six products and pass, and the
-// latency of the exchange for the outputs.  Products of the gradients delayed
-// into the next pass's vector phases, and the output weights in registers,
-// measured the same.  A third of a step is fixed: weights in, sums out, update.
+// What bounds it (counters of 65,536 samples): no unit is full.  Of the cycles that a wave
+// lives it has a vector instruction under way in 22 %, with two waves per SIMD (the GELU and
+// its derivative, 16 instructions per value, are about half of that), LDS is busy in 37 %
+// (64 KB of operand for each of the six products and pass; two fifths of the time bank
+// conflicts), the matrix cores in 18 %, and a wave waits in 43 %: six barriers per pass.  Products of the gradients
+// delayed into the next pass's vector phases, and the output weights in registers, measured
+// the same.  A third of a step is fixed: weights in, sums out, update.
 constexpr int kTrainWaves = 8;
 constexpr int kTrainThreads = 64 * kTrainWaves;
 constexpr int kTrainPass = 32;                          // samples per pass
